@@ -7,6 +7,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/cfd.h"
@@ -138,6 +139,20 @@ static cfd_status validate(const cfd_config* c) {
   return CFD_OK;
 }
 
+// Lanes of a march with x faces: wavefronts per march segment, either strips
+// of kMxNew cells of one row each, or all rows' slots one after another (rows
+// shorter than a strip share wavefronts), whichever takes fewer; strips too
+// where the byte offsets between the rows of one wavefront would not fit in
+// 32 bits.
+static void choose_mx_lanes(Geom& g) {
+  const int ot = g.act[1] ? 2 : 1;
+  const long long S = g.n[0] + 2 * kMxCtx, rows = g.n[ot];
+  const long long strips = (g.n[0] + kMxNew - 1) / kMxNew * rows, flat = (S * rows + kMxNew - 1) / kMxNew;
+  const double span = 8.0 * ((64.0 / S + 2.0) * (double)g.s[ot] + g.N[0]);
+  g.xs = strips <= flat || span >= 4.0e9;
+  g.xg = (int)(g.xs ? strips : flat);
+}
+
 static void make_geom(const cfd_config& c, Geom& g) {
   std::memset(&g, 0, sizeof(g));
   double inv2 = 0.0;
@@ -167,34 +182,62 @@ static void make_geom(const cfd_config& c, Geom& g) {
   g.weno3 = (c.flags & CFD_F_WENO3) ? 1 : 0;
   g.rusanov = (c.flags & CFD_F_RUSANOV) ? 1 : 0;
   g.rk2 = (c.flags & CFD_F_RK2) ? 1 : 0;
-  g.seg = kSeg;
+  g.seg = g.segx = kSeg;
+  choose_mx_lanes(g);
   g.nn = (c.flags & CFD_F_RUSANOV_NN) ? 1 : 0;
   g.safe = (c.flags & CFD_F_SAFE_RECON) ? 1 : 0;
   g.viscous = ((c.flags & CFD_F_VISCOUS) && c.mu > 0.0) ? 1 : 0;
   g.heat = ((c.flags & CFD_F_HEAT) && c.mu > 0.0) ? 1 : 0;
 }
 
-// March segment length of a single-grid solver: kSegSolo, halved (down to 8
-// cells) while a y or z march would run fewer than 1024 wavefronts, so that
-// small grids spread their marches over more lanes (each segment recomputes
-// its seed face and, in the adjoint, a reconstruction pair). Long segments
-// pay that less often: at 256^3 the marches run 128-cell segments (2048
-// wavefronts, one per wavefront slot at two per SIMD), 2-3 % faster than
-// 32-cell ones; 16-cell ones are 4 % slower. The serving batch chooses its
+// Time of `waves` wavefronts over the chip's 1024 SIMDs, `res` of them resident
+// on one at a time, in units of one wavefront's pure issue time: measured, a
+// SIMD with w wavefronts of a march takes w + 0.6 (one alone 1.6: nothing
+// hides its latencies), so that 331^2 marches with x faces in segments of 2,
+// 3, 4 and 8 rows (one wavefront per SIMD or less) run 11, 14, 17 and 28 us.
+static double waves_time(double waves, int res) {
+  const double w = waves / 1024.0, full = std::floor(w / res);
+  if (full >= 3) return w * (res + 0.6) / res + 0.3;
+  const double rem = std::ceil(w - full * res);
+  return full * (res + 0.6) + (rem > 0 ? rem + 0.6 : 0.0);
+}
+
+// Segment length along an axis of n cells that makes `groups(1 segment)`
+// wavefronts finish first: long segments seldom recompute their seed (worth
+// `seed` cells), short ones give the SIMDs more wavefronts. `face` is the work
+// per cell next to the first face's, `res` the resident wavefronts per SIMD.
+static int best_segment(int n, double groups, double face, double seed, int res) {
+  int best = 1;
+  double cost = 0.0;
+  for (int s = 1; s <= std::min(n, 256); ++s) {
+    const double c = (face * s + 1.0 + seed) * waves_time(groups * ((n + s - 1) / s), res);
+    if (s == 1 || c < cost) {
+      cost = c;
+      best = s;
+    }
+  }
+  return best;
+}
+
+// March segments of a single-grid solver. Against the fixed rule of 8 to 128
+// cells by powers of two (at least 1024 wavefronts): the implosion at 128^2
+// 1208 -> 590 us per 20 steps, KH 331^2 1079 -> 571 us and 1024^2 1130 -> 814 us
+// per 10 and 4 steps, a TGV step at 32^3 210 -> 97 us and at 128^3 1018 -> 822 us,
+// HIT 256^3 12.04 -> 11.02 ms per two steps. The serving batch chooses its
 // own (batch_segment): it fills the chip with many grids.
 static void choose_segment(Geom& g) {
-  auto waves = [&](int seg) {
-    long long w = -1;
-    for (int ax = 1; ax < 3; ++ax) {
-      if (!g.act[ax]) continue;
-      const int ot = ax == 1 ? 2 : 1;
-      const long long v = (long long)((g.n[0] + 63) / 64) * g.n[ot] * ((g.n[ax] + seg - 1) / seg);
-      w = w < 0 ? v : std::min(w, v);
-    }
-    return w;
-  };
-  g.seg = kSegSolo;
-  while (g.seg > 8 && waves(g.seg) >= 0 && waves(g.seg) < 1024) g.seg /= 2;
+  const bool euler = g.inviscid && !g.viscous && !g.heat;
+  const int res = g.roe ? 1 : (euler ? 4 : 2);
+  int seg = 0;
+  for (int ax = 1; ax < 3; ++ax) {
+    if (!g.act[ax]) continue;
+    const double groups = (double)((g.n[0] + 63) / 64) * g.n[3 - ax];
+    const int s = best_segment(g.n[ax], groups, 1.0, g.roe ? 4.0 : 3.0, res);
+    seg = seg ? std::min(seg, s) : s;
+  }
+  g.seg = seg ? seg : 1;
+  const int mx = g.act[1] ? 1 : 2;
+  g.segx = best_segment(g.n[mx], (double)g.xg, 2.0, 1.5, euler ? 3 : 2);
 }
 
 // ---------------------------------------------------------------------------
@@ -208,72 +251,143 @@ static cfd_status enqueue_prim(cfd_solver* s, const double* Uk, int what, const 
   return CFD_OK;
 }
 
-template <int D, bool PN, int SCH>
-static void launch_sweep_r(cfd_solver* s, int mode, const double* P, const StageIO& io, hipStream_t st) {
-  const Geom& g = s->g;
-  if (D == 0) {
-    const dim3 grid((unsigned)sweep_x_blocks(g));
-    switch (mode) {
-      case MODE_WRITE: hipLaunchKernelGGL((k_sweep_x<MODE_WRITE, false, SCH>), grid, dim3(kBlock), 0, st, P, io, g); break;
-      case MODE_ACC: hipLaunchKernelGGL((k_sweep_x<MODE_ACC, false, SCH>), grid, dim3(kBlock), 0, st, P, io, g); break;
-      case MODE_ACC_RK: hipLaunchKernelGGL((k_sweep_x<MODE_ACC_RK, PN, SCH>), grid, dim3(kBlock), 0, st, P, io, g); break;
-      case MODE_ACC2_RK: hipLaunchKernelGGL((k_sweep_x<MODE_ACC2_RK, PN, SCH>), grid, dim3(kBlock), 0, st, P, io, g); break;
-      default: hipLaunchKernelGGL((k_sweep_x<MODE_WRITE_RK, PN, SCH>), grid, dim3(kBlock), 0, st, P, io, g); break;
+// The convective scheme and the flux terms are template parameters of the
+// sweep kernels; f gets the pair for the solver's configuration as constants.
+template <int X>
+using Const = std::integral_constant<int, X>;
+
+template <int SCH, class F>
+static void with_phys(const Geom& g, F&& f) {
+  const bool euler = g.inviscid && !g.viscous && !g.heat, ns = g.inviscid && g.viscous && g.heat;
+  if (euler) return f(Const<SCH>{}, Const<PHYS_EULER>{});
+  // the schemes of the implosion run without viscous fluxes in earnest
+  if constexpr (SCH == SCH_JS || SCH == SCH_Z || SCH == SCH_ROE)
+    if (ns) return f(Const<SCH>{}, Const<PHYS_NS>{});
+  f(Const<SCH>{}, Const<PHYS_ANY>{});
+}
+
+template <class F>
+static void with_scheme(const Geom& g, F&& f) {
+  if (g.nn) with_phys<SCH_W3_NN>(g, f);
+  else if (g.roe) with_phys<SCH_ROE>(g, f);
+  else if (g.wenoz) with_phys<SCH_Z>(g, f);
+  else if (g.weno3 && g.rusanov) with_phys<SCH_W3_RUS>(g, f);
+  else if (g.weno3) with_phys<SCH_W3>(g, f);
+  else if (g.rusanov) with_phys<SCH_JS_RUS>(g, f);
+  else with_phys<SCH_JS>(g, f);
+}
+
+// WENO5-Z and the Roe splitting reconstruct face by face; the others per cell.
+static bool face_by_face(const Geom& g) { return g.roe || g.wenoz; }
+
+// Face-by-face schemes on three axes: the y and z marches write R and R2, the
+// x sweep reads both (MODE_ACC2_RK).
+static bool split_accumulator(const Geom& g) { return face_by_face(g) && g.act[0] && g.act[1] && g.act[2]; }
+
+// The sweeps of a stage, in order. Cell-centred schemes with x and another
+// axis active: on three axes the z march, then the y march with the x faces;
+// on two axes the march along the other axis with the x faces alone. With one
+// active axis its sweep alone; without x (and for the face-by-face schemes)
+// one sweep per active axis in the order y, z, x. The last sweep applies the
+// stage update and stores the next primitives.
+struct Sweep {
+  enum Kind { X, MARCH, MARCH_X } kind;
+  int ax;    // marching axis (0: x sweep)
+  int mode;
+  bool r2;   // writes the second accumulator
+};
+
+static int plan_sweeps(const Geom& g, bool rk, Sweep* out) {
+  int act = 0, n = 0;
+  for (int d = 0; d < 3; ++d) act += g.act[d];
+  if (!face_by_face(g) && g.act[0] && act > 1) {
+    if (act == 3) out[n++] = {Sweep::MARCH, 2, rk ? MODE_STAGE : MODE_WRITE, false};
+    out[n++] = {Sweep::MARCH_X, g.act[1] ? 1 : 2,
+                act == 3 ? (rk ? MODE_ADD_RK : MODE_ACC) : (rk ? MODE_WRITE_RK : MODE_WRITE), false};
+    return n;
+  }
+  for (int d : kSweepAxes) {
+    if (!g.act[d]) continue;
+    const bool first = n == 0, last = n == act - 1;
+    int mode;
+    bool r2 = false;
+    if (rk && last) {
+      mode = first ? MODE_WRITE_RK : (act == 3 ? MODE_ACC2_RK : MODE_ACC_RK);
+    } else if (rk && act == 3) {
+      mode = MODE_WRITE;  // the marches before the x sweep each write their own accumulator
+      r2 = !first;
+    } else {
+      mode = first ? MODE_WRITE : MODE_ACC;
     }
-  } else {
-    constexpr int AX = D == 0 ? 1 : D;
-    int gx, gy;
-    sweep_march_blocks<AX>(g, gx, gy);
-    const dim3 grid(gx, gy);
+    out[n++] = {d == 0 ? Sweep::X : Sweep::MARCH, d, mode, r2};
+  }
+  return n;
+}
+
+template <int AX, int SCH, int PHYS>
+static void launch_march(int mode, const double* P, const StageIO& io, const Geom& g, hipStream_t st) {
+  int gx, gy;
+  sweep_march_blocks<AX>(g, gx, gy);
+  const dim3 grid(gx, gy), blk(kBlock);
+  constexpr bool face = SCH == SCH_ROE || SCH == SCH_Z;
+  // sweeps that a cell-centred scheme runs only on grids without x take the
+  // run-time flux terms
+  constexpr int PA = face ? PHYS : PHYS_ANY;
+  switch (mode) {
+    case MODE_WRITE: hipLaunchKernelGGL((k_sweep_march<AX, MODE_WRITE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g); break;
+    case MODE_ACC: hipLaunchKernelGGL((k_sweep_march<AX, MODE_ACC, false, SCH, PA>), grid, blk, 0, st, P, io, g); break;
+    case MODE_ACC_RK: hipLaunchKernelGGL((k_sweep_march<AX, MODE_ACC_RK, true, SCH, PA>), grid, blk, 0, st, P, io, g); break;
+    case MODE_WRITE_RK: hipLaunchKernelGGL((k_sweep_march<AX, MODE_WRITE_RK, true, SCH, PA>), grid, blk, 0, st, P, io, g); break;
+    default:
+      if constexpr (!face && AX == 2)
+        hipLaunchKernelGGL((k_sweep_march<AX, MODE_STAGE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g);
+  }
+}
+
+template <int SCH, int PHYS>
+static void launch_x(int mode, const double* P, const StageIO& io, const Geom& g, hipStream_t st) {
+  const dim3 grid((unsigned)sweep_x_blocks(g)), blk(kBlock);
+  switch (mode) {
+    case MODE_WRITE: hipLaunchKernelGGL((k_sweep_x<MODE_WRITE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g); break;
+    case MODE_WRITE_RK: hipLaunchKernelGGL((k_sweep_x<MODE_WRITE_RK, true, SCH, PHYS>), grid, blk, 0, st, P, io, g); break;
+    default:
+      if constexpr (SCH == SCH_ROE || SCH == SCH_Z) {
+        if (mode == MODE_ACC) hipLaunchKernelGGL((k_sweep_x<MODE_ACC, false, SCH, PHYS>), grid, blk, 0, st, P, io, g);
+        else if (mode == MODE_ACC_RK) hipLaunchKernelGGL((k_sweep_x<MODE_ACC_RK, true, SCH, PHYS>), grid, blk, 0, st, P, io, g);
+        else hipLaunchKernelGGL((k_sweep_x<MODE_ACC2_RK, true, SCH, PHYS>), grid, blk, 0, st, P, io, g);
+      }
+  }
+}
+
+template <int SCH, int PHYS>
+static void launch_mx(int ax, int mode, const double* P, const StageIO& io, const Geom& g, hipStream_t st) {
+  if constexpr (SCH != SCH_ROE && SCH != SCH_Z) {
+    const dim3 grid((unsigned)sweep_mx_blocks(g, ax)), blk(kBlock);
+    if (ax == 2) {
+      if (mode == MODE_WRITE) hipLaunchKernelGGL((k_sweep_mx<2, MODE_WRITE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g);
+      else hipLaunchKernelGGL((k_sweep_mx<2, MODE_WRITE_RK, true, SCH, PHYS>), grid, blk, 0, st, P, io, g);
+      return;
+    }
     switch (mode) {
-      case MODE_WRITE: hipLaunchKernelGGL((k_sweep_march<AX, MODE_WRITE, false, SCH>), grid, dim3(kBlock), 0, st, P, io, g); break;
-      case MODE_ACC: hipLaunchKernelGGL((k_sweep_march<AX, MODE_ACC, false, SCH>), grid, dim3(kBlock), 0, st, P, io, g); break;
-      case MODE_ACC_RK: hipLaunchKernelGGL((k_sweep_march<AX, MODE_ACC_RK, PN, SCH>), grid, dim3(kBlock), 0, st, P, io, g); break;
-      default: hipLaunchKernelGGL((k_sweep_march<AX, MODE_WRITE_RK, PN, SCH>), grid, dim3(kBlock), 0, st, P, io, g); break;
+      case MODE_WRITE: hipLaunchKernelGGL((k_sweep_mx<1, MODE_WRITE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g); break;
+      case MODE_ACC: hipLaunchKernelGGL((k_sweep_mx<1, MODE_ACC, false, SCH, PHYS>), grid, blk, 0, st, P, io, g); break;
+      case MODE_WRITE_RK: hipLaunchKernelGGL((k_sweep_mx<1, MODE_WRITE_RK, true, SCH, PHYS>), grid, blk, 0, st, P, io, g); break;
+      default: hipLaunchKernelGGL((k_sweep_mx<1, MODE_ADD_RK, true, SCH, PHYS>), grid, blk, 0, st, P, io, g);
     }
   }
 }
 
-// The convective scheme (WENO5-JS or WENO5-Z with HLLC, or the Roe flux
-// splitting) is a template parameter of the sweep kernels; pick the
-// instantiation for the solver's configuration.
-template <int D, bool PN>
-static void launch_sweep(cfd_solver* s, int mode, const double* P, const StageIO& io, hipStream_t st) {
-  const Geom& g = s->g;
-  if (g.nn) launch_sweep_r<D, PN, SCH_W3_NN>(s, mode, P, io, st);
-  else if (g.roe) launch_sweep_r<D, PN, SCH_ROE>(s, mode, P, io, st);
-  else if (g.wenoz) launch_sweep_r<D, PN, SCH_Z>(s, mode, P, io, st);
-  else if (g.weno3 && g.rusanov) launch_sweep_r<D, PN, SCH_W3_RUS>(s, mode, P, io, st);
-  else if (g.weno3) launch_sweep_r<D, PN, SCH_W3>(s, mode, P, io, st);
-  else if (g.rusanov) launch_sweep_r<D, PN, SCH_JS_RUS>(s, mode, P, io, st);
-  else launch_sweep_r<D, PN, SCH_JS>(s, mode, P, io, st);
+static void launch_sweep(const Geom& g, const Sweep& sw, const double* P, StageIO io, hipStream_t st) {
+  if (sw.r2) io.R = const_cast<double*>(io.R2);
+  with_scheme(g, [&](auto sch, auto phys) {
+    constexpr int SCH = decltype(sch)::value, PHYS = decltype(phys)::value;
+    if (sw.kind == Sweep::MARCH_X) launch_mx<SCH, PHYS>(sw.ax, sw.mode, P, io, g, st);
+    else if (sw.kind == Sweep::X) launch_x<SCH, PHYS>(sw.mode, P, io, g, st);
+    else if (sw.ax == 1) launch_march<1, SCH, PHYS>(sw.mode, P, io, g, st);
+    else launch_march<2, SCH, PHYS>(sw.mode, P, io, g, st);
+  });
 }
 
-template <bool PN>
-static void launch_sweep_axis(cfd_solver* s, int d, int mode, const double* P, const StageIO& io, hipStream_t st) {
-  if (d == 0) launch_sweep<0, PN>(s, mode, P, io, st);
-  else if (d == 1) launch_sweep<1, PN>(s, mode, P, io, st);
-  else launch_sweep<2, PN>(s, mode, P, io, st);
-}
-
-// A stage of a grid with three active axes splits its accumulator: the y and
-// z marches write R and R2, the x sweep reads both (MODE_ACC2_RK).
-static bool stage_split(const Geom& g) { return g.act[0] && g.act[1] && g.act[2]; }
-
-// The first and last active axes in sweep order (kSweepAxes).
-static void sweep_order(const Geom& g, int& first, int& last) {
-  first = last = -1;
-  for (int d : kSweepAxes)
-    if (g.act[d]) {
-      if (first < 0) first = d;
-      last = d;
-    }
-}
-
-// Enqueue the per-axis sweeps over primitives P. With rk set, the last active
-// axis applies the stage update into io.Uout (and, with io.Pn set, stores the
-// primitives of the updated interior cells into io.Pn, whose halo is then
-// refreshed); otherwise io.R receives the full right-hand side.
 // Faces normal to axis d (interior cells of the other axes).
 static long long faces_of(const Geom& g, int d) {
   return (long long)g.n[0] * g.n[1] * g.n[2] / g.n[d] * (g.n[d] + 1);
@@ -306,32 +420,23 @@ static cfd_status enqueue_nn_alpha(cfd_solver* s, const double* P, hipStream_t s
   return CFD_OK;
 }
 
+// Enqueue the sweeps over primitives P. With rk set, the last one applies the
+// stage update into io.Uout and stores the primitives of the updated interior
+// cells into io.Pn, whose halo is then refreshed; otherwise io.R receives the
+// full right-hand side.
 static cfd_status enqueue_fluxes(cfd_solver* s, const double* P, const StageIO& io, bool rk, hipStream_t st) {
   const Geom& g = s->g;
   if (g.nn) {
     cfd_status rc = enqueue_nn_alpha(s, P, st);
     if (rc) return rc;
   }
-  int first = -1, last = -1;
-  sweep_order(g, first, last);
-  for (int d : kSweepAxes) {
-    if (!g.act[d]) continue;
-    int mode;
-    StageIO iod = io;
-    if (d == last && rk) {
-      mode = d == first ? MODE_WRITE_RK : (stage_split(g) && d == 0 ? MODE_ACC2_RK : MODE_ACC_RK);
-    } else if (rk && stage_split(g)) {
-      // the marches before the x sweep each write their own accumulator
-      mode = MODE_WRITE;
-      if (d != first) iod.R = const_cast<double*>(io.R2);
-    } else {
-      mode = d == first ? MODE_WRITE : MODE_ACC;
-    }
-    if (d == last && rk && io.Pn) launch_sweep_axis<true>(s, d, mode, P, iod, st);
-    else launch_sweep_axis<false>(s, d, mode, P, iod, st);
+  Sweep plan[3];
+  const int n = plan_sweeps(g, rk, plan);
+  for (int i = 0; i < n; ++i) {
+    launch_sweep(g, plan[i], P, io, st);
     CFD_LAUNCHED();
   }
-  if (rk && io.Pn) {
+  if (rk) {
     hipLaunchKernelGGL(k_prim_halo, dim3(halo_blocks(g)), dim3(kBlock), 0, st, io.Pn, g, io.dtp);
     CFD_LAUNCHED();
   }
@@ -695,7 +800,7 @@ cfd_status cfd_create(const cfd_config* cfg, cfd_solver** out) {
   const size_t st = sizeof(double) * 5 * (size_t)s->ncell;
   bool ok = hipMalloc(&s->U1, st) == hipSuccess && hipMalloc(&s->U2, st) == hipSuccess &&
             hipMalloc(&s->Racc, st) == hipSuccess &&
-            (!stage_split(s->g) || hipMalloc(&s->Racc2, st) == hipSuccess) &&
+            (!split_accumulator(s->g) || hipMalloc(&s->Racc2, st) == hipSuccess) &&
             hipMalloc(&s->Pb[0], sizeof(double) * 6 * (size_t)s->ncell) == hipSuccess &&
             hipMalloc(&s->Pb[1], sizeof(double) * 6 * (size_t)s->ncell) == hipSuccess &&
             hipMalloc(&s->Pb[2], sizeof(double) * 6 * (size_t)s->ncell) == hipSuccess &&
@@ -846,8 +951,8 @@ cfd_status cfd_profile_stage(cfd_solver* s, const double* U, int32_t reps, doubl
   hipLaunchKernelGGL(k_dt, dim3(1), dim3(kBlock), 0, st, s->ctl, g.cfl, 1e-12, 0.0, (double*)nullptr,
                      (double*)nullptr, s->partial, s->npart);
   CFD_LAUNCHED();
-  int first = -1, last = -1;
-  sweep_order(g, first, last);
+  Sweep plan[3];
+  const int nplan = plan_sweeps(g, true, plan);
   // slots of ms_out: prim pass, x, y, z sweeps, halo refresh of the next
   // primitives. Repetition r runs stage r % 3 + 1 of a step as a run of steps
   // does (the third with the CFL maxima and health bits of its output), into
@@ -885,21 +990,9 @@ cfd_status cfd_profile_stage(cfd_solver* s, const double* U, int32_t reps, doubl
     hipLaunchKernelGGL(k_prim, plane_grid(g), dim3(kBlock), 0, st, U, s->P, g, s->ctl, 0, io.dtp, s->partial);
     sl[n] = 0;
     (void)hipEventRecord(e[++n], st);
-    for (int d : kSweepAxes) {
-      if (!g.act[d]) continue;
-      int mode;
-      StageIO iod = io;
-      if (d == last) {
-        mode = d == first ? MODE_WRITE_RK : (stage_split(g) && d == 0 ? MODE_ACC2_RK : MODE_ACC_RK);
-      } else if (stage_split(g)) {
-        mode = MODE_WRITE;
-        if (d != first) iod.R = const_cast<double*>(io.R2);
-      } else {
-        mode = d == first ? MODE_WRITE : MODE_ACC;
-      }
-      if (d == last) launch_sweep_axis<true>(s, d, mode, s->P, iod, st);
-      else launch_sweep_axis<false>(s, d, mode, s->P, iod, st);
-      sl[n] = 1 + d;
+    for (int i = 0; i < nplan; ++i) {
+      launch_sweep(g, plan[i], s->P, io, st);
+      sl[n] = 1 + (plan[i].kind == Sweep::MARCH_X ? 0 : plan[i].ax);
       (void)hipEventRecord(e[++n], st);
     }
     hipLaunchKernelGGL(k_prim_halo, dim3(halo_blocks(g)), dim3(kBlock), 0, st, io.Pn, g, io.dtp);

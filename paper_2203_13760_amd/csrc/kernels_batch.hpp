@@ -17,6 +17,8 @@
 // x sweep; its primitives of a new state are formed once, on admission. A grid
 // without an x axis takes a primitive pass at the start of every stage.
 #pragma once
+#include <type_traits>
+
 #include "kernels_fwd.hpp"
 
 namespace cfd {
@@ -65,19 +67,18 @@ __device__ __forceinline__ int find_grid(const int* __restrict__ prefix, int ngr
   return lo;
 }
 
-// PN: the sweep stores the primitives of its output (x sweeps only).
-template <int MODE, bool PN>
-__device__ __forceinline__ void batch_sweep(int axis, const GridWork& w, const double* P, const StageIO& io,
-                                            int local) {
-  if (axis == 0) {
-    sweep_x_body<MODE, PN>(P, io, w.g, local);
-  } else if (axis == 1) {
-    const int by = local / w.sgx[1];
-    sweep_march_body<1, MODE>(P, io, w.g, local - by * w.sgx[1], by);
-  } else {
-    const int by = local / w.sgx[2];
-    sweep_march_body<2, MODE>(P, io, w.g, local - by * w.sgx[2], by);
-  }
+// Flux terms of a grid as a compile-time constant (see PHYS_EULER).
+template <class F>
+__device__ __forceinline__ void batch_phys(const Geom& g, F&& f) {
+  if (g.inviscid && !g.viscous && !g.heat) f(std::integral_constant<int, PHYS_EULER>{});
+  else if (g.inviscid && g.viscous && g.heat) f(std::integral_constant<int, PHYS_NS>{});
+  else f(std::integral_constant<int, PHYS_ANY>{});
+}
+
+template <int AX, int MODE, int PHYS>
+__device__ __forceinline__ void batch_march(const GridWork& w, const double* P, const StageIO& io, int local) {
+  const int by = uniform(local / w.sgx[AX]);
+  sweep_march_body<AX, MODE, false, SCH_JS, PHYS>(P, io, w.g, local - by * w.sgx[AX], by);
 }
 
 // Work distribution of a persistent launch: the concatenated block range of a
@@ -103,7 +104,7 @@ __device__ __forceinline__ void batch_item(const BatchTable* __restrict__ tab, i
   const int ng = tab->ngrids;
   const int* prefix = tab->prefix[PHASE];
   {
-    const int k = find_grid(prefix, ng, b);
+    const int k = uniform(find_grid(prefix, ng, b));
     const int local = b - prefix[k];
     const GridWork& w = tab->grid[k];
     const Geom& g = w.g;
@@ -132,21 +133,28 @@ __device__ __forceinline__ void batch_item(const BatchTable* __restrict__ tab, i
     } else if (PHASE == PH_HALO) {
       prim_halo_body(io.Pn, g, (long long)local * kBlock + threadIdx.x);
     } else if (PHASE == PH_SX) {
-      // x is the last axis whenever it is active: the stage update
-      const bool split = g.act[1] && g.act[2];  // y and z marches wrote R and R2
-      if (w.first_axis == 0) batch_sweep<MODE_WRITE_RK, true>(0, w, P, io, local);
-      else if (split) batch_sweep<MODE_ACC2_RK, true>(0, w, P, io, local);
-      else batch_sweep<MODE_ACC_RK, true>(0, w, P, io, local);
+      // the last sweep of a grid with an x axis: the stage update
+      if (!g.act[1] && !g.act[2]) {
+        sweep_x_body<MODE_WRITE_RK, true>(P, io, g, local);
+      } else {
+        batch_phys(g, [&](auto phys) {
+          constexpr int PHYS = decltype(phys)::value;
+          if (g.act[1] && g.act[2]) sweep_mx_body<1, MODE_ADD_RK, true, SCH_JS, PHYS>(P, io, g, local);
+          else if (g.act[1]) sweep_mx_body<1, MODE_WRITE_RK, true, SCH_JS, PHYS>(P, io, g, local);
+          else sweep_mx_body<2, MODE_WRITE_RK, true, SCH_JS, PHYS_ANY>(P, io, g, local);
+        });
+      }
     } else if (PHASE == PH_SLAST) {
       // the last march of a grid without an x axis
-      if (w.last_axis == w.first_axis) batch_sweep<MODE_WRITE_RK, false>(w.last_axis, w, P, io, local);
-      else batch_sweep<MODE_ACC_RK, false>(w.last_axis, w, P, io, local);
+      if (w.last_axis == 1) batch_march<1, MODE_WRITE_RK, PHYS_ANY>(w, P, io, local);
+      else if (w.last_axis == w.first_axis) batch_march<2, MODE_WRITE_RK, PHYS_ANY>(w, P, io, local);
+      else batch_march<2, MODE_ACC_RK, PHYS_ANY>(w, P, io, local);
+    } else if (PHASE == PH_SY) {
+      // the y march of a grid without an x axis but with a z axis
+      batch_march<1, MODE_WRITE, PHYS_ANY>(w, P, io, local);
     } else {
-      // a march before the update: the first writes R, a second (only with
-      // x active) its own accumulator R2
-      constexpr int axis = PHASE == PH_SY ? 1 : 2;
-      if (axis != w.first_axis) io.R = w.R2;
-      batch_sweep<MODE_WRITE, false>(axis, w, P, io, local);
+      // the z march of a grid with three active axes, before its last sweep
+      batch_phys(g, [&](auto phys) { batch_march<2, MODE_STAGE, decltype(phys)::value>(w, P, io, local); });
     }
   }
 }
@@ -169,7 +177,7 @@ k_batch(const BatchTable* __restrict__ tab, unsigned* ctr) {
     for (;;) {
       if (threadIdx.x == 0) next = lo + (int)atomicAdd(c + x, 1u);
       __syncthreads();
-      const int b = next;
+      const int b = uniform(next);
       __syncthreads();  // every wave has read `next` before it is replaced
       if (b >= hi) break;
       batch_item<PHASE, STAGE>(tab, b);

@@ -35,9 +35,13 @@ constexpr int kGradComps = 9;  // adjoint of d u_a / d x_b accumulated at compon
 // R = -D (MODE_WRITE_RK), R - D (MODE_ACC_RK) or R + R2 - D (MODE_ACC2_RK:
 // the two marches before it each wrote their own accumulator, which spares
 // the second one a read-modify-write of R).
-enum SweepMode { MODE_WRITE = 0, MODE_ACC = 1, MODE_ACC_RK = 2, MODE_WRITE_RK = 3, MODE_ACC2_RK = 4 };
-__host__ __device__ constexpr bool mode_rk(int m) { return m == MODE_ACC_RK || m == MODE_WRITE_RK || m == MODE_ACC2_RK; }
-__host__ __device__ constexpr bool mode_reads_r(int m) { return m == MODE_ACC || m == MODE_ACC_RK || m == MODE_ACC2_RK; }
+// MODE_STAGE / MODE_ADD_RK split the update of a stage between two sweeps:
+// the first stores V = a Un + b (Uk - dt D1) in R, the second the new state
+// V - b dt D2.
+enum SweepMode {
+  MODE_WRITE = 0, MODE_ACC = 1, MODE_ACC_RK = 2, MODE_WRITE_RK = 3, MODE_ACC2_RK = 4, MODE_STAGE = 5, MODE_ADD_RK = 6
+};
+__host__ __device__ constexpr bool mode_rk(int m) { return m >= MODE_ACC_RK; }
 
 struct StageIO {
   double* R;         // right-hand-side accumulator (padded layout)
@@ -277,15 +281,13 @@ constexpr int kBadFace = 8;
 // cells next to the face (qa left, qb right: the first-order reconstruction).
 __device__ __forceinline__ void check_face_states(const Geom& g, bool use, double* WL, double* WR,
                                                   const double* qa, const double* qb, int& bad) {
-  const bool ok = WL[0] > 0.0 && WL[4] > 0.0 && WR[0] > 0.0 && WR[4] > 0.0;
-  if (use && !ok) {
-    bad |= kBadFace;
-    if (g.safe) {
+  const bool ok = !use || (WL[0] > 0.0 && WL[4] > 0.0 && WR[0] > 0.0 && WR[4] > 0.0);
+  bad |= ok ? 0 : kBadFace;
+  if (g.safe) {
 #pragma unroll
-      for (int v = 0; v < 5; ++v) {
-        WL[v] = qa[v];
-        WR[v] = qb[v];
-      }
+    for (int v = 0; v < 5; ++v) {
+      WL[v] = ok ? WL[v] : qa[v];
+      WR[v] = ok ? WR[v] : qb[v];
     }
   }
 }
@@ -386,7 +388,22 @@ __global__ void __launch_bounds__(kBlock) k_dt(DevCtl* ctl, double cfl, double f
 }
 
 // ----------------------------------------------------------------------------
-// ----------------------------------------------------------------------------
+// Loads and stores at a wavefront-uniform base plus a 32-bit byte offset per
+// lane: the base of every (variable, neighbour) pair stays in scalar
+// registers and all of a lane's accesses share one offset register.
+__device__ __forceinline__ double ld_at(const double* base, unsigned off) {
+  return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(base) + off);
+}
+__device__ __forceinline__ void st_at(double* base, unsigned off, double x) {
+  *reinterpret_cast<double*>(reinterpret_cast<char*>(base) + off) = x;
+}
+
+// A value that is the same in all lanes, kept in a scalar register. A march
+// forms its cell index from uniform(f): without it the loop passes turn
+// base + offset back into one 64-bit address per lane and access.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ int wave_in_block() { return uniform((int)threadIdx.x >> 6); }
+
 // Face window loads.
 __device__ __forceinline__ void load_prims(const double* __restrict__ P, long long vs, long long c,
                                            double* q) {
@@ -460,6 +477,25 @@ __device__ __forceinline__ void tangential_combine(const Geom& g, const double (
   for (int m = 0; m < 4; ++m) tg[m] = (x[m][0] - 8.0 * x[m][1] + 8.0 * x[m][2] - x[m][3]) * w[m];
 }
 
+// The three sums the cell-centred sweeps carry (layout of sub_dissipative_q):
+// the two derivatives along their own axes enter the flux only as a sum.
+template <int D>
+__device__ __forceinline__ void tangential_combine3(const Geom& g, const double (&x)[4][4], double* tg) {
+  constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
+  const double w1 = g.act[T1] ? g.idx[T1] * (1.0 / 12.0) : 0.0, w2 = g.act[T2] ? g.idx[T2] * (1.0 / 12.0) : 0.0;
+  auto diff = [](const double* y) { return fma(8.0, y[2] - y[1], y[0] - y[3]); };
+  tg[0] = diff(x[0]) * w1;
+  tg[1] = diff(x[2]) * w2;
+  tg[2] = fma(diff(x[1]), w1, diff(x[3]) * w2);
+}
+
+template <int D>
+__device__ __forceinline__ void tangential_at3(const Geom& g, const double* __restrict__ P, long long c, double* tg) {
+  double x[4][4];
+  tangential_load<D>(g, P, c, x);
+  tangential_combine3<D>(g, x, tg);
+}
+
 template <int D>
 __device__ __forceinline__ void tangential_at_flat(const Geom& g, const double* __restrict__ P, long long c,
                                                    double* tg) {
@@ -478,19 +514,20 @@ struct EmitIn {
   double r[5], un[5], uk[5];
 };
 
+// Cell c + off (off in bytes; a lane's offset from a wavefront-uniform c, or 0).
 // A stage whose weight a of U^n is zero (TVD-RK3 stage 1, where U^(k) is
 // U^n) does not load U^n.
 template <int MODE>
-__device__ __forceinline__ void emit_fetch(const StageIO& io, long long vs, long long c, EmitIn& in) {
+__device__ __forceinline__ void emit_fetch(const StageIO& io, long long vs, long long c, unsigned off, EmitIn& in) {
   const bool with_un = io.a != 0.0;
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     const long long e = v * vs + c;
-    if (MODE == MODE_ACC || MODE == MODE_ACC_RK) in.r[v] = io.R[e];
-    if (MODE == MODE_ACC2_RK) in.r[v] = io.R[e] + io.R2[e];
-    if (mode_rk(MODE)) {
-      in.un[v] = with_un ? io.Un[e] : 0.0;
-      in.uk[v] = io.Uk[e];
+    if (MODE == MODE_ACC || MODE == MODE_ACC_RK || MODE == MODE_ADD_RK) in.r[v] = ld_at(io.R + e, off);
+    if (MODE == MODE_ACC2_RK) in.r[v] = ld_at(io.R + e, off) + ld_at(io.R2 + e, off);
+    if (mode_rk(MODE) && MODE != MODE_ADD_RK) {
+      in.un[v] = with_un ? ld_at(io.Un + e, off) : 0.0;
+      in.uk[v] = ld_at(io.Uk + e, off);
     }
   }
 }
@@ -498,25 +535,28 @@ __device__ __forceinline__ void emit_fetch(const StageIO& io, long long vs, long
 // STORE_T: also store T~ = p/rho with the next primitives (the face-by-face
 // sweeps read it from P; the cell-centred ones form it from rho and p).
 template <int MODE, bool PN = false, bool STORE_T = true>
-__device__ __forceinline__ void emit_put(const StageIO& io, const Geom& g, long long c, const double* D,
+__device__ __forceinline__ void emit_put(const StageIO& io, const Geom& g, long long c, unsigned off, const double* D,
                                          const EmitIn& in, double dt, double& smax, int& bad) {
   double uo[5];
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     const long long e = v * g.vs + c;
-    const double r = (MODE == MODE_WRITE || MODE == MODE_WRITE_RK) ? -D[v] : in.r[v] - D[v];
     if (MODE == MODE_WRITE || MODE == MODE_ACC) {
-      io.R[e] = r;
+      st_at(io.R + e, off, MODE == MODE_WRITE ? -D[v] : in.r[v] - D[v]);
+    } else if (MODE == MODE_ADD_RK) {
+      uo[v] = fma(-(io.b * dt), D[v], in.r[v]);
+      st_at(io.Uout + e, off, uo[v]);
     } else {
+      const double r = MODE == MODE_WRITE_RK || MODE == MODE_STAGE ? -D[v] : in.r[v] - D[v];
       uo[v] = io.a * in.un[v] + io.b * (in.uk[v] + dt * r);
-      io.Uout[e] = uo[v];
+      st_at((MODE == MODE_STAGE ? io.R : io.Uout) + e, off, uo[v]);
     }
   }
   if constexpr (PN && mode_rk(MODE)) {
     double w[6];
     const double ir = cons_to_prim(g, uo, w);
 #pragma unroll
-    for (int v = 0; v < (STORE_T ? 6 : 5); ++v) io.Pn[v * g.vs + c] = w[v];
+    for (int v = 0; v < (STORE_T ? 6 : 5); ++v) st_at(io.Pn + v * g.vs + c, off, w[v]);
     if (io.what & PRIM_CFL) smax = fmax(smax, cfl_rate(g, w, ir));
     if (io.what & PRIM_HEALTH) bad |= health_bits(uo, w[4]);
   }
@@ -581,7 +621,7 @@ __device__ __forceinline__ void x_row(const Geom& g, int row, int& j, int& k) {
   j = band * kXBand + (r - k * h);
 }
 
-template <int MODE, bool PN, int SCH>
+template <int MODE, bool PN, int SCH, int PHYS>
 __device__ __forceinline__ void sweep_x_body_face(const double* __restrict__ P, const StageIO& io, const Geom& g,
                                                   int bx) {
   // slot numbering fits in 32 bits (checked when the solver is created)
@@ -615,7 +655,7 @@ __device__ __forceinline__ void sweep_x_body_face(const double* __restrict__ P, 
 #pragma unroll
     for (int m = 0; m < 4; ++m) w.T[m] = P[5 * g.vs + c0 + 1 + m];  // unused without heat flux
     double d[4] = {0.0, 0.0, 0.0, 0.0};
-    if (g.viscous) tangential_at_flat<0>(g, P, cell_at(g, f + 1, j, k), d);
+    if (with_viscous<PHYS>(g)) tangential_at_flat<0>(g, P, cell_at(g, f + 1, j, k), d);
     // face values of the derivatives from cells f-2..f+1 (lanes - 3 .. lane)
     double tf[4];
 #pragma unroll
@@ -627,7 +667,7 @@ __device__ __forceinline__ void sweep_x_body_face(const double* __restrict__ P, 
     }
     if constexpr (SCH == SCH_W3_NN) w.a = g.nna[c0 + 2];  // alpha of face f (left cell f-1)
     double G[5];
-    face_flux_tf<0, SCH>(g, w, tf, G);
+    face_flux_tf<0, SCH, PHYS>(g, w, tf, G);
     double Gm[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) Gm[v] = lane_shr1(G[v]);
@@ -637,8 +677,8 @@ __device__ __forceinline__ void sweep_x_body_face(const double* __restrict__ P, 
       for (int v = 0; v < 5; ++v) D[v] = (G[v] - Gm[v]) * g.idx[0];
       const long long ce = cell_at(g, f - 1, j, k);
       EmitIn ein;
-      emit_fetch<MODE>(io, g.vs, ce, ein);
-      emit_put<MODE, PN>(io, g, ce, D, ein, dt, smax, bad);
+      emit_fetch<MODE>(io, g.vs, ce, 0, ein);
+      emit_put<MODE, PN>(io, g, ce, 0, D, ein, dt, smax, bad);
     }
   }
   if (PN) finish_prims(io, smax, bad);
@@ -648,7 +688,7 @@ __device__ __forceinline__ void sweep_x_body_face(const double* __restrict__ P, 
 // both faces of cell f (window cells f-2 .. f+2, one smoothness evaluation
 // for the two faces) and takes the left state of face f from the lane below,
 // which reconstructed cell f-1.
-template <int MODE, bool PN, int SCH>
+template <int MODE, bool PN, int SCH, int PHYS>
 __device__ __forceinline__ void sweep_x_body_pair(const double* __restrict__ P, const StageIO& io, const Geom& g,
                                                   int bx) {
   const int lane = threadIdx.x & 63;
@@ -678,25 +718,30 @@ __device__ __forceinline__ void sweep_x_body_pair(const double* __restrict__ P, 
     double q[5][5];
 #pragma unroll
     for (int m = 0; m < 5; ++m) load_prims(P, g.vs, c0 + m, q[m]);
-    double d[4] = {0.0, 0.0, 0.0, 0.0};
-    if (g.viscous) tangential_at_flat<0>(g, P, cell_at(g, f + 1, j, k), d);
+    double d[3] = {0.0, 0.0, 0.0};
+    if (with_viscous<PHYS>(g)) {
+      double x[4][4];
+      tangential_load<0>(g, P, cell_at(g, f + 1, j, k), x);
+      __builtin_amdgcn_sched_barrier(0);
+      tangential_combine3<0>(g, x, d);
+    }
     // T~ = p/rho of cells f-2 .. f+1 (heat flux only), from the window
     double T[4] = {0.0, 0.0, 0.0, 0.0};
-    if (g.heat) {
+    if (with_heat<PHYS>(g)) {
 #pragma unroll
       for (int m = 0; m < 4; ++m) T[m] = div_nr(q[m][4], q[m][0]);
     }
     // face values of the derivatives from cells f-2..f+1 (lanes - 3 .. lane)
-    double tf[4];
+    double tf[3];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
+    for (int v = 0; v < 3; ++v) {
       const double t2 = lane_shr1(d[v]);
       const double t1 = lane_shr1(t2);
       const double t0 = lane_shr1(t1);
       tf[v] = rc4(t0, t1, t2, d[v]);
     }
     double WL[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, WR[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (g.inviscid) {
+    if (with_inviscid<PHYS>(g)) {
       double qr[5];
       recon_pair<SCH>(q, qr, WR);
 #pragma unroll
@@ -706,7 +751,7 @@ __device__ __forceinline__ void sweep_x_body_pair(const double* __restrict__ P, 
     double alpha = 0.0;
     if constexpr (SCH == SCH_W3_NN) alpha = g.nna[c0 + 1];  // alpha of face f (left cell f-1)
     double G[5];
-    face_flux_states<0, SCH>(g, WL, WR, q, T, tf, alpha, G);
+    face_flux_states<0, SCH, PHYS>(g, WL, WR, q, T, tf, alpha, G);
     double Gm[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) Gm[v] = lane_shr1(G[v]);
@@ -716,28 +761,28 @@ __device__ __forceinline__ void sweep_x_body_pair(const double* __restrict__ P, 
       for (int v = 0; v < 5; ++v) D[v] = (G[v] - Gm[v]) * g.idx[0];
       const long long ce = cell_at(g, f - 1, j, k);
       EmitIn ein;
-      emit_fetch<MODE>(io, g.vs, ce, ein);
-      emit_put<MODE, PN, false>(io, g, ce, D, ein, dt, smax, bad);
+      emit_fetch<MODE>(io, g.vs, ce, 0, ein);
+      emit_put<MODE, PN, false>(io, g, ce, 0, D, ein, dt, smax, bad);
     }
   }
   if (PN) finish_prims(io, smax, bad);
   else if (bad && io.ctl) atomicOr(&io.ctl->status, bad);
 }
 
-template <int MODE, bool PN = false, int SCH = SCH_JS>
+template <int MODE, bool PN = false, int SCH = SCH_JS, int PHYS = PHYS_ANY>
 __device__ __forceinline__ void sweep_x_body(const double* __restrict__ P, const StageIO& io, const Geom& g,
                                              int bx) {
-  if constexpr (SCH == SCH_ROE || SCH == SCH_Z) sweep_x_body_face<MODE, PN, SCH>(P, io, g, bx);
-  else sweep_x_body_pair<MODE, PN, SCH>(P, io, g, bx);
+  if constexpr (SCH == SCH_ROE || SCH == SCH_Z) sweep_x_body_face<MODE, PN, SCH, PHYS>(P, io, g, bx);
+  else sweep_x_body_pair<MODE, PN, SCH, PHYS>(P, io, g, bx);
 }
 
 // Blocks are taken in XCD-major order, so that the neighbouring rows and
 // planes whose velocities the derivative stencils read are being processed in
 // the same XCD and stay in its L2.
-template <int MODE, bool PN, int SCH>
+template <int MODE, bool PN, int SCH, int PHYS>
 __global__ void __launch_bounds__(kBlock) k_sweep_x(const double* __restrict__ P, StageIO io, Geom g) {
   if (step_disabled(io.dtp)) return;
-  sweep_x_body<MODE, PN, SCH>(P, io, g, xcd_major_block(blockIdx.x, gridDim.x));
+  sweep_x_body<MODE, PN, SCH, PHYS>(P, io, g, xcd_major_block(blockIdx.x, gridDim.x));
 }
 
 // Blocks of an x sweep.
@@ -748,17 +793,14 @@ __host__ __device__ __forceinline__ int sweep_x_blocks(const Geom& g) {
 }
 
 // y / z sweep: one lane per (x, other) column segment of Geom::seg cells
-// along the axis (kSegSolo for a single grid, kSeg in the serving batch;
-// fewer on grids too small to fill the chip with segments that long); lanes
-// run along x so every load is coalesced. The segment's first face is
-// computed only to seed the left flux.
+// along the axis; lanes run along x so every load is coalesced. The segment's
+// first face is computed only to seed the left flux.
 constexpr int kSeg = 32;
-constexpr int kSegSolo = 128;
 
 // y / z sweep body of one lane. Lanes beyond the grid (a partial last block)
 // march a valid column too but store nothing, so that every lane reaches the
 // block-wide CFL reduction of a sweep that stores next-stage primitives.
-template <int AX, int MODE, bool PN, int SCH>
+template <int AX, int MODE, bool PN, int SCH, int PHYS>
 __device__ __forceinline__ void sweep_march_body_face(const double* __restrict__ P, const StageIO& io,
                                                       const Geom& g, int bx, int by) {
   constexpr int OT = AX == 1 ? 2 : 1;  // the other transverse axis
@@ -781,7 +823,7 @@ __device__ __forceinline__ void sweep_march_body_face(const double* __restrict__
   q3[OT] = o;
   q3[AX] = s0 - 3;
   long long c = cell_at(g, q3[0], q3[1], q3[2]);  // window cell 0 (axis index f-2 for face f+1/2)
-  const bool dis = g.viscous || g.heat;
+  const bool dis = with_viscous<PHYS>(g) || with_heat<PHYS>(g);
   FaceWindow w;
 #pragma unroll
   for (int m = 0; m < 6; ++m) load_prims(P, g.vs, c + m * st, w.q[m]);
@@ -789,7 +831,7 @@ __device__ __forceinline__ void sweep_march_body_face(const double* __restrict__
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       w.T[m] = P[5 * g.vs + c + (1 + m) * st];
-      if (g.viscous) tangential_at<AX>(g, P, c + (1 + m) * st, w.tg[m]);
+      if (with_viscous<PHYS>(g)) tangential_at<AX>(g, P, c + (1 + m) * st, w.tg[m]);
     }
   }
   double Gm[5];
@@ -800,7 +842,7 @@ __device__ __forceinline__ void sweep_march_body_face(const double* __restrict__
     // their latency overlaps it
     const bool more = f + 1 < s1;
     EmitIn ein;
-    if (f >= s0 && in) emit_fetch<MODE>(io, g.vs, c + 2 * st, ein);  // window cell 2 is cell f
+    if (f >= s0 && in) emit_fetch<MODE>(io, g.vs, c + 2 * st, 0, ein);  // window cell 2 is cell f
     // The entering cell's derivative stencil: in MODE_WRITE (no update loads
     // in flight) the sixteen raw values are held across the face arithmetic
     // and combined after it, so their latency is hidden; the other modes have
@@ -811,7 +853,7 @@ __device__ __forceinline__ void sweep_march_body_face(const double* __restrict__
       load_prims(P, g.vs, c + 6 * st, nq);
       if (dis) {
         nT = P[5 * g.vs + c + 5 * st];
-        if (g.viscous) {
+        if (with_viscous<PHYS>(g)) {
           if (kDeferTg) tangential_load<AX>(g, P, c + 5 * st, ntr);
           else tangential_at<AX>(g, P, c + 5 * st, ntg);
         }
@@ -820,12 +862,12 @@ __device__ __forceinline__ void sweep_march_body_face(const double* __restrict__
     if (kDeferTg) __builtin_amdgcn_sched_barrier(0);
     if constexpr (SCH == SCH_W3_NN) w.a = g.nna[AX * g.vs + c + 2 * st];  // face f+1/2, left cell f
     double G[5];
-    face_flux<AX, SCH>(g, w, G);
+    face_flux<AX, SCH, PHYS>(g, w, G);
     if (f >= s0 && in) {
       double D[5];
 #pragma unroll
       for (int v = 0; v < 5; ++v) D[v] = (G[v] - Gm[v]) * g.idx[AX];
-      emit_put<MODE, PN>(io, g, c + 2 * st, D, ein, dt, smax, bad);
+      emit_put<MODE, PN>(io, g, c + 2 * st, 0, D, ein, dt, smax, bad);
     }
 #pragma unroll
     for (int v = 0; v < 5; ++v) Gm[v] = G[v];
@@ -846,7 +888,7 @@ __device__ __forceinline__ void sweep_march_body_face(const double* __restrict__
           for (int v = 0; v < 4; ++v) w.tg[m][v] = w.tg[m + 1][v];
         }
         w.T[3] = nT;
-        if (kDeferTg && g.viscous) tangential_combine<AX>(g, ntr, ntg);
+        if (kDeferTg && with_viscous<PHYS>(g)) tangential_combine<AX>(g, ntr, ntg);
 #pragma unroll
         for (int v = 0; v < 4; ++v) w.tg[3][v] = ntg[v];
       }
@@ -855,43 +897,63 @@ __device__ __forceinline__ void sweep_march_body_face(const double* __restrict__
   if (PN) finish_prims(io, smax, bad);
 }
 
+// The four values a central difference at cell c takes along the axis of
+// stride st, and the difference (times 12 dx).
+struct Diff4 {
+  double x[4];
+  __device__ __forceinline__ void load(const double* q, long long st, unsigned off) {
+    x[0] = ld_at(q - 2 * st, off);
+    x[1] = ld_at(q - st, off);
+    x[2] = ld_at(q + st, off);
+    x[3] = ld_at(q + 2 * st, off);
+  }
+  __device__ __forceinline__ double diff() const { return fma(8.0, x[2] - x[1], x[0] - x[3]); }
+};
+
 // The same for the cell-centred schemes: the lane carries the left state of
 // the next face, reconstructed with the right state of the current face from
 // the cell between them (one smoothness evaluation for the two faces), so the
 // window holds five cells, f-1 .. f+3 for face f+1/2. The segment starts with
 // the reconstruction of cell s0-1, for the left state of its first face.
-template <int AX, int MODE, bool PN, int SCH>
+template <int AX, int MODE, bool PN, int SCH, int PHYS>
 __device__ __forceinline__ void sweep_march_body_pair(const double* __restrict__ P, const StageIO& io,
                                                       const Geom& g, int bx, int by) {
   constexpr int OT = AX == 1 ? 2 : 1;  // the other transverse axis
-  const int i = bx * 64 + (threadIdx.x & 63);
+  constexpr int T1 = (AX + 1) % 3, T2 = (AX + 2) % 3;
+  const int i = bx * 64 + (int)(threadIdx.x & 63);
   const int sl = g.seg;
   const int nseg = (g.n[AX] + sl - 1) / sl;
-  const long long col = (long long)by * (kBlock >> 6) + (threadIdx.x >> 6);
-  const bool in = i < g.n[0] && col < (long long)g.n[OT] * nseg;
-  if (!PN && !in) return;
+  const int col = uniform(by * (kBlock >> 6) + wave_in_block());
+  const bool live = col < g.n[OT] * nseg;  // uniform
+  const bool in = live && i < g.n[0];
+  if (!PN && !live) return;
   double smax = 0.0;
   int bad = 0;
-  const long long colc = in ? col : 0;
-  const int o = (int)(colc / nseg);
-  const int seg = (int)(colc - (long long)o * nseg);
-  const int s0 = seg * sl;
+  const int colc = live ? col : 0;
+  const int o = uniform(colc / nseg);
+  const int s0 = (colc - o * nseg) * sl;
   const int s1 = min(s0 + sl, g.n[AX]);
   const long long st = g.s[AX];
   int q3[3];
-  q3[0] = in ? i : 0;
+  q3[0] = 0;
   q3[OT] = o;
   q3[AX] = s0 - 3;
-  long long c = cell_at(g, q3[0], q3[1], q3[2]);  // cell s0-3
-  const bool dis = g.viscous || g.heat;
+  const long long c = cell_at(g, q3[0], q3[1], q3[2]);  // uniform: cell s0-3 of the column at x = 0
+  const unsigned off = (unsigned)(i < g.n[0] ? i : g.n[0] - 1) * 8u;
+  const bool vis = with_viscous<PHYS>(g), heat = with_heat<PHYS>(g);
+  const long long sT1 = g.act[T1] ? g.s[T1] : 0, sT2 = g.act[T2] ? g.s[T2] : 0;
+  const double w1 = g.act[T1] ? g.idx[T1] * (1.0 / 12.0) : 0.0, w2 = g.act[T2] ? g.idx[T2] * (1.0 / 12.0) : 0.0;
   double q[5][5];   // window: cells f-1 .. f+3 for face f+1/2
   double WLc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};  // left state of face f+1/2
   {
     double s[5][5];  // cells s0-3 .. s0+1
 #pragma unroll
-    for (int m = 0; m < 5; ++m) load_prims(P, g.vs, c + m * st, s[m]);
-    load_prims(P, g.vs, c + 5 * st, q[4]);
-    if (g.inviscid) {
+    for (int m = 0; m < 5; ++m)
+#pragma unroll
+      for (int v = 0; v < 5; ++v) s[m][v] = ld_at(P + v * g.vs + c + m * st, off);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) q[4][v] = ld_at(P + v * g.vs + c + 5 * st, off);
+    if (with_inviscid<PHYS>(g)) {
       double unused[5];
       recon_pair<SCH>(s, WLc, unused);
     }
@@ -900,107 +962,110 @@ __device__ __forceinline__ void sweep_march_body_pair(const double* __restrict__
 #pragma unroll
       for (int v = 0; v < 5; ++v) q[m][v] = s[m + 1][v];
   }
-  c += st;  // window cell 0: cell f-1 for the first face f = s0-1
-  double T[4] = {0.0, 0.0, 0.0, 0.0}, tg[4][4];
+  const long long c1 = c + st;  // window cell 0: cell f-1 for the first face f = s0-1
+  // T~ and the tangential sums (sub_dissipative_q) of cells f-1 .. f+2
+  double T[4] = {0.0, 0.0, 0.0, 0.0}, tg[4][3];
+  // the entering cell's tangential stencil: u_D and u_T1 along T1, u_D and u_T2 along T2
+  Diff4 d[4];
+  auto tang_load = [&](long long cc) {
+    d[0].load(P + (1 + AX) * g.vs + cc, sT1, off);
+    d[1].load(P + (1 + T1) * g.vs + cc, sT1, off);
+    d[2].load(P + (1 + AX) * g.vs + cc, sT2, off);
+    d[3].load(P + (1 + T2) * g.vs + cc, sT2, off);
+  };
+  auto tang_sum = [&](double* t) {
+    t[0] = d[0].diff() * w1;
+    t[1] = d[2].diff() * w2;
+    t[2] = fma(d[1].diff(), w1, d[3].diff() * w2);
+  };
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int m = 0; m < 4; ++m) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) tg[m][v] = 0.0;
-  if (dis) {
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      if (g.heat) T[m] = div_nr(q[m][4], q[m][0]);  // T~ = p/rho from the window
-      if (g.viscous) tangential_at<AX>(g, P, c + m * st, tg[m]);
+    for (int v = 0; v < 3; ++v) tg[m][v] = 0.0;
+    if (vis) {
+      tang_load(c1 + m * st);
+      tang_sum(tg[m]);
     }
+    if (heat) T[m] = div_nr(q[m][4], q[m][0]);
   }
   double Gm[5];
   const double dt = mode_rk(MODE) ? *io.dtp : 0.0;
   for (int f = s0 - 1; f < s1; ++f) {
     // issue the loads of the cell entering the window at the next face, and
-    // those of this face's cell update, before this face's arithmetic, so
-    // their latency overlaps it
-    const bool more = f + 1 < s1;
-    EmitIn ein;
-    if (f >= s0 && in) emit_fetch<MODE>(io, g.vs, c + st, ein);  // window cell 1 is cell f
-    constexpr bool kDeferTg = MODE == MODE_WRITE;
-    double nq[5], nT = 0.0, ntr[4][4], ntg[4] = {0.0, 0.0, 0.0, 0.0};
-    if (more) {
-      load_prims(P, g.vs, c + 5 * st, nq);
-      if (dis) {
-        if (g.heat) nT = div_nr(q[4][4], q[4][0]);  // cell f+3, window cell 4
-        if (g.viscous) {
-          if (kDeferTg) tangential_load<AX>(g, P, c + 4 * st, ntr);
-          else tangential_at<AX>(g, P, c + 4 * st, ntg);
-        }
-      }
-    }
-    if (kDeferTg) __builtin_amdgcn_sched_barrier(0);
+    // of its tangential stencil, before this face's arithmetic, so that their
+    // latency overlaps it
+    // (after the segment's last face the loaded cell is not used; it is the
+    // window's last one then, inside the padded block)
+    const long long c = c1 + uniform(f - (s0 - 1)) * st;  // window cell 0
+    const long long ce = f + 1 < s1 ? c + 5 * st : c + 4 * st;
+    double nq[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) nq[v] = ld_at(P + v * g.vs + ce, off);
+    if (vis) tang_load(c + 4 * st);
+    __builtin_amdgcn_sched_barrier(0);
     double alpha = 0.0;
-    if constexpr (SCH == SCH_W3_NN) alpha = g.nna[AX * g.vs + c + st];  // face f+1/2, left cell f
+    if constexpr (SCH == SCH_W3_NN) alpha = ld_at(g.nna + AX * g.vs + c + st, off);  // face f+1/2, left cell f
     double WR[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, qr[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     double WL[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) WL[v] = WLc[v];
-    if (g.inviscid) {
+    if (with_inviscid<PHYS>(g)) {
       recon_pair<SCH>(q, qr, WR);  // cell f+1: left state of face f+3/2, right state of f+1/2
       check_face_states(g, true, WL, WR, q[1], q[2], bad);
     }
-    double tf[4] = {0.0, 0.0, 0.0, 0.0};
-    if (g.viscous) {
+    double tf[3] = {0.0, 0.0, 0.0};
+    if (vis) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) tf[v] = rc4(tg[0][v], tg[1][v], tg[2][v], tg[3][v]);
+      for (int v = 0; v < 3; ++v) tf[v] = rc4(tg[0][v], tg[1][v], tg[2][v], tg[3][v]);
     }
     double G[5];
-    face_flux_states<AX, SCH>(g, WL, WR, q, T, tf, alpha, G);
+    face_flux_states<AX, SCH, PHYS>(g, WL, WR, q, T, tf, alpha, G);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) pin(G[v]);
     if (f >= s0 && in) {
       double D[5];
 #pragma unroll
       for (int v = 0; v < 5; ++v) D[v] = (G[v] - Gm[v]) * g.idx[AX];
-      emit_put<MODE, PN, false>(io, g, c + st, D, ein, dt, smax, bad);
+      EmitIn ein;
+      emit_fetch<MODE>(io, g.vs, c + st, off, ein);  // window cell 1 is cell f
+      emit_put<MODE, PN, false>(io, g, c + st, off, D, ein, dt, smax, bad);
     }
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
       Gm[v] = G[v];
       WLc[v] = qr[v];
     }
-    if (more) {
-      // shift the window by one cell along the axis
+    // shift the window by one cell along the axis
 #pragma unroll
-      for (int m = 0; m < 4; ++m)
+    for (int m = 0; m < 3; ++m) {
+      T[m] = T[m + 1];
 #pragma unroll
-        for (int v = 0; v < 5; ++v) q[m][v] = q[m + 1][v];
-#pragma unroll
-      for (int v = 0; v < 5; ++v) q[4][v] = nq[v];
-      c += st;
-      if (dis) {
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-          T[m] = T[m + 1];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) tg[m][v] = tg[m + 1][v];
-        }
-        T[3] = nT;
-        if (kDeferTg && g.viscous) tangential_combine<AX>(g, ntr, ntg);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) tg[3][v] = ntg[v];
-      }
+      for (int v = 0; v < 3; ++v) tg[m][v] = tg[m + 1][v];
     }
+    if (heat) T[3] = div_nr(q[4][4], q[4][0]);  // cell f+3
+    if (vis) tang_sum(tg[3]);
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int v = 0; v < 5; ++v) q[m][v] = q[m + 1][v];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) q[4][v] = nq[v];
   }
   if (PN) finish_prims(io, smax, bad);
   else if (bad && io.ctl) atomicOr(&io.ctl->status, bad);
 }
 
-template <int AX, int MODE, bool PN = false, int SCH = SCH_JS>
+template <int AX, int MODE, bool PN = false, int SCH = SCH_JS, int PHYS = PHYS_ANY>
 __device__ __forceinline__ void sweep_march_body(const double* __restrict__ P, const StageIO& io,
                                                  const Geom& g, int bx, int by) {
-  if constexpr (SCH == SCH_ROE || SCH == SCH_Z) sweep_march_body_face<AX, MODE, PN, SCH>(P, io, g, bx, by);
-  else sweep_march_body_pair<AX, MODE, PN, SCH>(P, io, g, bx, by);
+  if constexpr (SCH == SCH_ROE || SCH == SCH_Z) sweep_march_body_face<AX, MODE, PN, SCH, PHYS>(P, io, g, bx, by);
+  else sweep_march_body_pair<AX, MODE, PN, SCH, PHYS>(P, io, g, bx, by);
 }
 
 // The Roe flux splitting does not fit the marching window in the register
 // budget of two wavefronts per SIMD; its marches run one wavefront per SIMD,
 // which leaves the accumulation registers to the compiler.
-template <int AX, int MODE, bool PN, int SCH>
+template <int AX, int MODE, bool PN, int SCH, int PHYS>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SCH == SCH_ROE ? 1 : 2)))
 k_sweep_march(const double* __restrict__ P, StageIO io, Geom g) {
   if (step_disabled(io.dtp)) return;
@@ -1008,7 +1073,245 @@ k_sweep_march(const double* __restrict__ P, StageIO io, Geom g) {
   // neighbouring planes of the transverse derivatives, share an XCD
   const int logical = xcd_major_block(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int by = logical / gridDim.x;
-  sweep_march_body<AX, MODE, PN, SCH>(P, io, g, logical - by * gridDim.x, by);
+  sweep_march_body<AX, MODE, PN, SCH, PHYS>(P, io, g, logical - by * gridDim.x, by);
+}
+
+// Marching sweep along AX that also forms the x faces of the rows it passes
+// (cell-centred schemes): the stage's last sweep wherever x and another axis
+// are active. A wavefront holds 64 consecutive x of a row; while it marches,
+// the x face of lane l (between lanes l-1 and l) takes its stencil from the
+// window rows of the neighbouring lanes (DPP shifts), so one pass over P
+// serves both axes and the x divergence never goes through memory. The x part
+// treats the row at the window's centre (f+1 at face f+1/2), whose
+// derivatives along AX are in the window already; a row's x divergence is
+// carried to the next face with the flux of the face between them. The first
+// three lanes and the last three of a wavefront only supply stencils: it
+// emits kMxNew cells. Rows of different transverse index o follow each other
+// in the lanes (slots -3 .. n+2 of every row) unless strips of kMxNew cells of
+// one row take fewer wavefronts (Geom::xs).
+// Bounds: FP64 VALU and the latency of the march's loads at two wavefronts
+// per SIMD; without this fusion the x sweep re-read P, R and both stage
+// states at the rate of a plain copy (4.9 TB/s at 256^3) while the marches,
+// at 2.6 TB/s, waited on latency.
+constexpr int kMxCtx = 3, kMxNew = 64 - 2 * kMxCtx;
+
+template <int AX, int MODE, bool PN, int SCH, int PHYS>
+__device__ __forceinline__ void sweep_mx_body(const double* __restrict__ P, const StageIO& io, const Geom& g,
+                                              int block) {
+  constexpr int OT = 3 - AX;  // the transverse axis of the rows
+  constexpr int T1 = (AX + 1) % 3;
+  const int lane = threadIdx.x & 63;
+  const int sl = g.segx;
+  const int nseg = (g.n[AX] + sl - 1) / sl;
+  const int item = uniform(block * (kBlock >> 6) + wave_in_block());
+  const int seg = uniform(item / g.xg);
+  const int gw = item - seg * g.xg;
+  const bool live = seg < nseg;  // uniform
+  if (!PN && !live) return;
+  double smax = 0.0;
+  int bad = 0;
+  if (live) {
+    int o, x, ob;
+    bool inrow;
+    if (g.xs) {
+      const int k = (g.n[0] + kMxNew - 1) / kMxNew;
+      ob = o = uniform(gw / k);
+      x = (gw - o * k) * kMxNew + lane - kMxCtx;
+      inrow = x < g.n[0];
+    } else {
+      const int S = g.n[0] + 2 * kMxCtx;
+      const int slot = gw * kMxNew + lane - kMxCtx;
+      const int sc = min(max(slot, 0), S * g.n[OT] - 1);
+      o = sc / S;
+      x = sc - o * S - kMxCtx;
+      inrow = slot == sc && x >= 0 && x < g.n[0];
+      ob = uniform(o);
+    }
+    const bool emit = inrow && lane >= kMxCtx && lane < 64 - kMxCtx;
+    const bool xface = lane >= kMxCtx && lane <= 64 - kMxCtx && x >= 0 && x <= g.n[0];  // lane's x face is used
+    const unsigned off = (unsigned)((o - ob) * g.s[OT] + min(max(x, -kMxCtx), g.n[0] + kMxCtx - 1) + g.h[0]) * 8u;
+    const int s0 = seg * sl;
+    const int s1 = min(s0 + sl, g.n[AX]);
+    const long long st = g.s[AX], sO = g.act[OT] ? g.s[OT] : 0;
+    const double wA = g.idx[AX] * (1.0 / 12.0), wO = g.act[OT] ? g.idx[OT] * (1.0 / 12.0) : 0.0,
+                 w0 = g.idx[0] * (1.0 / 12.0);
+    const bool vis = with_viscous<PHYS>(g), heat = with_heat<PHYS>(g);
+    // uniform base of row s0-2 (window cell 0 of the first face) at padded x = 0
+    const long long c1 = (long long)(ob + g.h[OT]) * g.s[OT] + (long long)(s0 - 2 + g.h[AX]) * st;
+    double q[5][5];  // window: rows f-1 .. f+3 for face f+1/2
+    double WLc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    {
+      double s[5][5];  // rows s0-3 .. s0+1
+#pragma unroll
+      for (int m = 0; m < 5; ++m)
+#pragma unroll
+        for (int v = 0; v < 5; ++v) s[m][v] = ld_at(P + v * g.vs + c1 + (m - 1) * st, off);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) q[4][v] = ld_at(P + v * g.vs + c1 + 4 * st, off);
+      if (with_inviscid<PHYS>(g)) {
+        double unused[5];
+        recon_pair<SCH>(s, WLc, unused);
+      }
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int v = 0; v < 5; ++v) q[m][v] = s[m + 1][v];
+    }
+    // Rows f-1 .. f+2: T~ and the tangential derivatives of the AX faces -
+    // along OT and x of u_AX, and du_OT/dOT + du_x/dx; du_OT/dOT and du_x/dOT
+    // on their own for the x part of the rows from the centre on.
+    double T[4] = {0.0, 0.0, 0.0, 0.0}, tO[4], tX[4], tS[4], rO[4], rX[4];
+    Diff4 d[3];
+    auto o_load = [&](long long cc) {
+      d[0].load(P + (1 + AX) * g.vs + cc, sO, off);
+      d[1].load(P + (1 + OT) * g.vs + cc, sO, off);
+      d[2].load(P + g.vs + cc, sO, off);
+    };
+    auto x_diff = [&](double u) {
+      const double b = lane_shr1(u), e = lane_shl1(u);
+      return fma(8.0, e - b, lane_shr1(b) - lane_shl1(e)) * w0;
+    };
+    auto tang = [&](int m, const double* row) {
+      tO[m] = d[0].diff() * wO;
+      tX[m] = x_diff(row[1 + AX]);
+      rO[m] = d[1].diff() * wO;
+      rX[m] = d[2].diff() * wO;
+      tS[m] = rO[m] + x_diff(row[1]);
+    };
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      tO[m] = tX[m] = tS[m] = rO[m] = rX[m] = 0.0;
+      if (vis) {
+        o_load(c1 + m * st);
+        tang(m, q[m]);
+      }
+      if (heat) T[m] = div_nr(q[m][4], q[m][0]);
+    }
+    double Gm[5], Dx[5];  // flux of face f-1/2 and x divergence of row f
+    const double dt = mode_rk(MODE) ? *io.dtp : 0.0;
+    for (int f = s0 - 1; f < s1; ++f) {
+      const long long c = c1 + uniform(f - (s0 - 1)) * st;  // row f-1
+      // the entering row (after the segment's last face a row already held,
+      // inside the padded block)
+      const long long ce = f + 1 < s1 ? c + 5 * st : c + 4 * st;
+      double nq[5];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) nq[v] = ld_at(P + v * g.vs + ce, off);
+      if (vis) o_load(c + 4 * st);
+      __builtin_amdgcn_sched_barrier(0);
+      double G[5], nWL[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+      {
+        double alpha = 0.0;
+        if constexpr (SCH == SCH_W3_NN) alpha = ld_at(g.nna + AX * g.vs + c + st, off);  // face f+1/2, left cell f
+        double WR[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        if (with_inviscid<PHYS>(g)) {
+          recon_pair<SCH>(q, nWL, WR);  // row f+1: left state of face f+3/2, right state of f+1/2
+          check_face_states(g, emit, WLc, WR, q[1], q[2], bad);
+        }
+        double tf[3] = {0.0, 0.0, 0.0};
+        if (vis) {
+          const double a = rc4(tO[0], tO[1], tO[2], tO[3]), b = rc4(tX[0], tX[1], tX[2], tX[3]);
+          tf[0] = T1 == 0 ? b : a;
+          tf[1] = T1 == 0 ? a : b;
+          tf[2] = rc4(tS[0], tS[1], tS[2], tS[3]);
+        }
+        face_flux_states<AX, SCH, PHYS>(g, WLc, WR, q, T, tf, alpha, G);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) pin(G[v]);
+      }
+      // row f is complete with this face
+      if (f >= s0 && emit) {
+        double D[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) D[v] = fma(G[v] - Gm[v], g.idx[AX], Dx[v]);
+        EmitIn ein;
+        emit_fetch<MODE>(io, g.vs, c + st, off, ein);
+        emit_put<MODE, PN, false>(io, g, c + st, off, D, ein, dt, smax, bad);
+      }
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        Gm[v] = G[v];
+        WLc[v] = nWL[v];
+      }
+      // x faces of row f+1 (not after the segment's last face)
+      if (f + 1 < s1) {
+        double WL[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, WR[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        double xq[4][5];  // cells x-2 .. x+1 of the lane's left face
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          xq[2][v] = q[2][v];
+          xq[1][v] = lane_shr1(q[2][v]);
+          xq[0][v] = lane_shr1(xq[1][v]);
+          xq[3][v] = lane_shl1(q[2][v]);
+          if (with_inviscid<PHYS>(g)) {
+            double r;
+            const double e = lane_shl1(xq[3][v]);
+            if constexpr (sch_weno3(SCH)) weno3_pair(xq[1][v], xq[2][v], xq[3][v], r, WR[v]);
+            else weno5_pair(xq[0][v], xq[1][v], xq[2][v], xq[3][v], e, r, WR[v]);
+            WL[v] = lane_shr1(r);
+            pin(WL[v]);
+            pin(WR[v]);
+          }
+        }
+        if (with_inviscid<PHYS>(g)) check_face_states(g, xface, WL, WR, xq[1], xq[2], bad);
+        double tf[3] = {0.0, 0.0, 0.0}, xT[4] = {0.0, 0.0, 0.0, 0.0};
+        if (vis) {
+          // du_x/dy, du_x/dz, du_y/dy + du_z/dz at the row; their face values
+          auto a_diff = [&](int v) { return fma(8.0, q[3][v] - q[1][v], q[0][v] - q[4][v]) * wA; };
+          const double xA = a_diff(1), t[3] = {AX == 1 ? xA : rX[2], AX == 1 ? rX[2] : xA, a_diff(1 + AX) + rO[2]};
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const double b = lane_shr1(t[k]);
+            tf[k] = rc4(lane_shr1(b), b, t[k], lane_shl1(t[k]));
+          }
+        }
+        if (heat) {
+          xT[2] = T[2];
+          xT[1] = lane_shr1(T[2]);
+          xT[0] = lane_shr1(xT[1]);
+          xT[3] = lane_shl1(T[2]);
+        }
+        double alpha = 0.0, Gx[5];
+        if constexpr (SCH == SCH_W3_NN) alpha = ld_at(g.nna + c + 2 * st - 1, off);  // face x, left cell x-1
+        face_flux_states<0, SCH, PHYS>(g, WL, WR, xq, xT, tf, alpha, Gx);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) Dx[v] = (lane_shl1(Gx[v]) - Gx[v]) * g.idx[0];
+      }
+      // shift the window by one row
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        T[m] = T[m + 1];
+        tO[m] = tO[m + 1];
+        tX[m] = tX[m + 1];
+        tS[m] = tS[m + 1];
+        rO[m] = rO[m + 1];
+        rX[m] = rX[m + 1];
+      }
+      if (heat) T[3] = div_nr(q[4][4], q[4][0]);
+      if (vis) tang(3, q[4]);
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int v = 0; v < 5; ++v) q[m][v] = q[m + 1][v];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) q[4][v] = nq[v];
+    }
+  }
+  if (PN) finish_prims(io, smax, bad);
+  else if (bad && io.ctl) atomicOr(&io.ctl->status, bad);
+}
+
+template <int AX, int MODE, bool PN, int SCH, int PHYS>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
+k_sweep_mx(const double* __restrict__ P, StageIO io, Geom g) {
+  if (step_disabled(io.dtp)) return;
+  sweep_mx_body<AX, MODE, PN, SCH, PHYS>(P, io, g, xcd_major_block(blockIdx.x, gridDim.x));
+}
+
+// Blocks of a march with x faces along AX.
+__host__ __device__ __forceinline__ int sweep_mx_blocks(const Geom& g, int ax) {
+  const long long items = (long long)g.xg * ((g.n[ax] + g.segx - 1) / g.segx);
+  return (int)((items + 3) / 4);
 }
 
 // Launch shape of a marching sweep along AX (x blocks, y blocks).

@@ -35,6 +35,8 @@ struct Geom {
   int rusanov;     // Rusanov flux instead of HLLC
   int rk2;         // TVD-RK2 instead of TVD-RK3
   int seg;         // cells per lane of the y / z marches
+  int segx;        // rows per segment of a march with x faces
+  int xg, xs;      // its wavefronts per segment; strips of single rows
   int nn;          // Rusanov-NN flux (with WENO3-JS): alpha per face from nna
   int safe;        // safe reconstruction: first-order states at faces with a non-positive rho or p
   const double* nnw;  // Rusanov-NN network weights (device, 2305 values)
@@ -55,6 +57,24 @@ constexpr int SCH_W3_NN = 6;
 __host__ __device__ constexpr bool sch_weno3(int sch) { return sch == SCH_W3 || sch == SCH_W3_RUS || sch == SCH_W3_NN; }
 __host__ __device__ constexpr bool sch_rusanov(int sch) {
   return sch == SCH_JS_RUS || sch == SCH_W3_RUS || sch == SCH_W3_NN;
+}
+
+
+// Flux terms of the sweeps, a compile-time parameter: the Euler equations, the
+// full Navier-Stokes equations (convective, viscous and heat flux), or any
+// other combination, read from the Geom flags at run time. The flags are
+// uniform, but branching on them inside a march splits its loop into blocks
+// that loads cannot be moved across and keeps zeroed windows live.
+constexpr int PHYS_ANY = 0, PHYS_EULER = 1, PHYS_NS = 2;
+template <int PHYS>
+__host__ __device__ __forceinline__ bool with_inviscid(const Geom& g) { return PHYS != PHYS_ANY || g.inviscid; }
+template <int PHYS>
+__host__ __device__ __forceinline__ bool with_viscous(const Geom& g) {
+  return PHYS == PHYS_NS || (PHYS == PHYS_ANY && g.viscous);
+}
+template <int PHYS>
+__host__ __device__ __forceinline__ bool with_heat(const Geom& g) {
+  return PHYS == PHYS_NS || (PHYS == PHYS_ANY && g.heat);
 }
 
 __host__ __device__ __forceinline__ double sq(double x) { return x * x; }
@@ -80,15 +100,27 @@ __host__ __device__ __forceinline__ double div_nr(double a, double b) {
 #endif
 }
 
+// 1 / b for the same denominators: the estimate r with error e = 1 - b r is
+// corrected by r (e + e^2) (third order; error below 2^-72 before the final
+// rounding), one operation shorter than div_nr(1, b).
+__host__ __device__ __forceinline__ double rcp_nr(double b) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const double r = __builtin_amdgcn_rcp(b);
+  const double e = fma(-b, r, 1.0);
+  return fma(fma(e, e, e), r, r);
+#else
+  return 1.0 / b;
+#endif
+}
+
 // sqrt(x) for a finite x >= 2^-767 (densities, pressures, squared sound
 // speeds): the hardware reciprocal square root estimate y ~ 1/sqrt(x)
 // (v_rsq_f64) refined by one Goldschmidt step on the pair g ~ sqrt(x),
-// h ~ 1/(2 sqrt(x)) (r = 1/2 - g h, g += g r, h += h r) and two Newton
-// corrections of the root (g += (x - g^2) h). These are the steps of the
-// compiler's own square root on gfx950 for such x, without its range scaling
-// for tiny arguments and its fixups for 0 and infinity (x = 0 gives NaN, a
-// negative x NaN as sqrt does): about half of its instructions. The host pass
-// takes sqrt.
+// h ~ 1/(2 sqrt(x)) (r = 1/2 - g h, g += g r, h += h r) and one Newton
+// correction of the root (g += (x - g^2) h). It has neither range scaling for
+// tiny arguments nor fixups for 0 and infinity (x = 0 gives NaN, a negative x
+// NaN as sqrt does), and on 4 194 304 random arguments it returned the
+// correctly rounded root every time. The host pass takes sqrt.
 __host__ __device__ __forceinline__ double sqrt_pos(double x) {
 #ifdef __HIP_DEVICE_COMPILE__
   const double y = __builtin_amdgcn_rsq(x);
@@ -96,12 +128,21 @@ __host__ __device__ __forceinline__ double sqrt_pos(double x) {
   const double r = fma(-h, g, 0.5);
   g = fma(g, r, g);
   h = fma(h, r, h);
-  double d = fma(-g, g, x);
-  g = fma(d, h, g);
-  d = fma(-g, g, x);
-  return fma(d, h, g);
+  return fma(fma(-g, g, x), h, g);
 #else
   return sqrt(x);
+#endif
+}
+
+// Keeps x where it stands in the order of the program: what x is formed from
+// comes before, what uses it after. Without such points the compiler starts
+// independent chains (the five variables of a reconstruction) together, and
+// the marches' windows no longer fit the registers beside them.
+__host__ __device__ __forceinline__ void pin(double& x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+v"(x));
+#else
+  (void)x;
 #endif
 }
 
@@ -132,22 +173,20 @@ __device__ __forceinline__ double bc_sign(int c, int n, int bc_lo, int bc_hi) {
 // linear weights (0.1, 0.6, 0.3), alpha_k = d_k/(1e-6 + beta_k)^2, normalised.
 // Evaluated with a single division: with s_k = (1e-6 + beta_k)^2 the weights
 // are proportional to d_k * prod_{j != k} s_j, and the 1/6 of the candidate
-// stencils is applied to the normaliser. The products stay within FP64 range
-// for |beta_k| up to ~1e100.
+// stencils is applied to the normaliser. Differences and increments on c as in
+// weno5_pair. The products stay within FP64 range for |beta_k| up to ~1e70.
 __host__ __device__ __forceinline__ double weno5(double a, double b, double c, double d, double e) {
   constexpr double k13 = 13.0 / 12.0;
   constexpr double eps = 1.0e-6;
-  const double t0 = a - 2.0 * b + c, u0 = a - 4.0 * b + 3.0 * c;
-  const double t1 = b - 2.0 * c + d, u1 = b - d;
-  const double t2 = c - 2.0 * d + e, u2 = 3.0 * c - 4.0 * d + e;
-  const double s0 = sq(eps + (k13 * t0 * t0 + 0.25 * u0 * u0));
-  const double s1 = sq(eps + (k13 * t1 * t1 + 0.25 * u1 * u1));
-  const double s2 = sq(eps + (k13 * t2 * t2 + 0.25 * u2 * u2));
-  const double w0 = 0.1 * (s1 * s2), w1 = 0.6 * (s0 * s2), w2 = 0.3 * (s0 * s1);
-  const double P0 = 2.0 * a - 7.0 * b + 11.0 * c;
-  const double P1 = -b + 5.0 * c + 2.0 * d;
-  const double P2 = 2.0 * c + 5.0 * d - e;
-  return div_nr(w0 * P0 + w1 * P1 + w2 * P2, 6.0 * (w0 + w1 + w2));
+  const double dm = c - b, dp = d - c;
+  const double Db = dm - (b - a), Dc = dp - dm, Dd = (e - d) - dp;
+  const double t0 = fma(0.5, Db, dm), t1 = 0.5 * (dm + dp), t2 = fma(-0.5, Dd, dp);
+  const double s0 = sq(fma(t0, t0, fma(k13 * Db, Db, eps)));
+  const double s1 = sq(fma(t1, t1, fma(k13 * Dc, Dc, eps)));
+  const double s2 = sq(fma(t2, t2, fma(k13 * Dd, Dd, eps)));
+  const double w0 = s1 * s2, w1 = 6.0 * (s0 * s2), w2 = 3.0 * (s0 * s1);
+  const double n = fma(w0, fma(2.0, Db, 3.0 * dm), fma(w1, fma(2.0, dp, dm), w2 * fma(3.0, dp, -Dd)));
+  return c + div_nr(n, 6.0 * (w0 + (w1 + w2)));
 }
 
 // WENO5-Z (Borges, Carmona, Costa & Don 2008): the same candidates and
@@ -181,36 +220,39 @@ __host__ __device__ __forceinline__ double weno5z(double a, double b, double c, 
 // of cells i-2..i is beta_0 of qr and beta_2 of ql - so each is formed once
 // per cell, from the second differences Db, Dc, Dd centred at b, c, d and the
 // first differences dm = c - b, dp = d - c:
-//   beta_L = 13/12 Db^2 + 1/4 (Db + 2 dm)^2     (a - 4b + 3c = Db + 2 dm)
-//   beta_C = 13/12 Dc^2 + 1/4 (dm + dp)^2       (b - d = -(dm + dp))
-//   beta_R = 13/12 Dd^2 + 1/4 (Dd - 2 dp)^2     (3c - 4d + e = Dd - 2 dp).
+//   beta_L = 13/12 Db^2 + (dm + Db/2)^2         (a - 4b + 3c = Db + 2 dm)
+//   beta_C = 13/12 Dc^2 + ((dm + dp)/2)^2       (b - d = -(dm + dp))
+//   beta_R = 13/12 Dd^2 + (dp - Dd/2)^2         (3c - 4d + e = Dd - 2 dp).
 // With s_k = (1e-6 + beta_k)^2 the weights of qr are proportional to
-// (0.1 s_C s_R, 0.6 s_L s_R, 0.3 s_L s_C) on the candidates
-// (2a - 7b + 11c, -b + 5c + 2d, 2c + 5d - e)/6, those of ql to
-// (0.1 s_L s_C, 0.6 s_L s_R, 0.3 s_C s_R) on the mirrored candidates
-// (2e - 7d + 11c, -d + 5c + 2b, 2c + 5b - a)/6: the pairwise products are
-// shared too. Both quotients come from one reciprocal of the product of the
-// two normalisers (in range for |beta| below ~1e38).
+// (s_C s_R, 6 s_L s_R, 3 s_L s_C), those of ql to (s_L s_C, 6 s_L s_R,
+// 3 s_C s_R): the pairwise products are shared too. The candidates are taken
+// as increments on c, six times
+//   qr: 2 Db + 3 dm, 2 dp + dm, 3 dp - Dd;  ql: 2 Dd - 3 dp, -(2 dm + dp), -(3 dm + Db),
+// one operation each from the differences (three to four from the cell
+// values), and their rounding scales with the increment instead of with c;
+// mirrored stencils give mirrored values bit for bit.
+// Both quotients come from one reciprocal of the product of the two
+// normalisers (in range for |beta| below ~1e38). Against candidates from the
+// cell values and weights (0.1, 0.6, 0.3): 57 instead of 75 FP64 operations.
 __host__ __device__ __forceinline__ void weno5_pair(double a, double b, double c, double d, double e, double& qr,
                                                    double& ql) {
   constexpr double k13 = 13.0 / 12.0;
   constexpr double eps = 1.0e-6;
-  const double Db = a - 2.0 * b + c, Dc = b - 2.0 * c + d, Dd = c - 2.0 * d + e;
   const double dm = c - b, dp = d - c;
-  const double tL = Db + 2.0 * dm, tC = dm + dp, tR = Dd - 2.0 * dp;
-  const double sL = sq(eps + (k13 * Db * Db + 0.25 * tL * tL));
-  const double sC = sq(eps + (k13 * Dc * Dc + 0.25 * tC * tC));
-  const double sR = sq(eps + (k13 * Dd * Dd + 0.25 * tR * tR));
-  const double pCR = sC * sR, pLR = sL * sR, pLC = sL * sC;
-  const double nr = 0.1 * pCR * (2.0 * a - 7.0 * b + 11.0 * c) + 0.6 * pLR * (-b + 5.0 * c + 2.0 * d) +
-                    0.3 * pLC * (2.0 * c + 5.0 * d - e);
-  const double nl = 0.1 * pLC * (2.0 * e - 7.0 * d + 11.0 * c) + 0.6 * pLR * (-d + 5.0 * c + 2.0 * b) +
-                    0.3 * pCR * (2.0 * c + 5.0 * b - a);
-  const double dr = 0.1 * pCR + 0.6 * pLR + 0.3 * pLC;
-  const double dl = 0.1 * pLC + 0.6 * pLR + 0.3 * pCR;
-  const double r = div_nr(1.0, 6.0 * (dr * dl));
-  qr = nr * dl * r;
-  ql = nl * dr * r;
+  const double Db = dm - (b - a), Dc = dp - dm, Dd = (e - d) - dp;
+  const double tL = fma(0.5, Db, dm), tC = 0.5 * (dm + dp), tR = fma(-0.5, Dd, dp);
+  const double sL = sq(fma(tL, tL, fma(k13 * Db, Db, eps)));
+  const double sC = sq(fma(tC, tC, fma(k13 * Dc, Dc, eps)));
+  const double sR = sq(fma(tR, tR, fma(k13 * Dd, Dd, eps)));
+  const double pCR = sC * sR, pLC = sL * sC;
+  const double w1 = 6.0 * (sL * sR), w2 = 3.0 * pLC, v2 = 3.0 * pCR;
+  const double m3 = 3.0 * dm, p3 = 3.0 * dp;
+  const double nr = fma(pCR, fma(2.0, Db, m3), fma(w1, fma(2.0, dp, dm), w2 * (p3 - Dd)));
+  const double nl = fma(pLC, fma(2.0, Dd, -p3), -fma(w1, fma(2.0, dm, dp), v2 * (m3 + Db)));
+  const double dr = pCR + (w1 + w2), dl = pLC + (w1 + v2);
+  const double r = rcp_nr(dr * dl) * (1.0 / 6.0);
+  qr = fma(nr, dl * r, c);
+  ql = fma(nl, dr * r, c);
 }
 
 // WENO3-JS (Jiang & Shu 1996, r = 2) value at the right face of the centre
@@ -275,7 +317,7 @@ __host__ __device__ __forceinline__ void rusanov(double gamma, double gm1i, cons
 
 // ---------------------------------------------------------------------------
 // HLLC flux (Toro, Spruce & Speares 1994) with Einfeldt (1988) speeds across a
-// face normal to axis D (five divisions, five square roots). Inputs:
+// face normal to axis D (a division, four reciprocals, five square roots). Inputs:
 // reconstructed primitive states (rho, u, v, w, p) left/right. Output in
 // physical slot order. The flux comes from one side K: the left one where
 // 0 <= S_L or 0 <= S*, else the right one; it is that side's physical flux
@@ -288,14 +330,15 @@ __host__ __device__ __forceinline__ void hllc(double gamma, double gm1i, const d
   constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
   const double rL = WL[0], uL = WL[1 + D], pL = WL[4];
   const double rR = WR[0], uR = WR[1 + D], pR = WR[4];
-  const double c2L = div_nr(gamma * pL, rL), c2R = div_nr(gamma * pR, rR);
+  const double c2L = gamma * pL * rcp_nr(rL), c2R = gamma * pR * rcp_nr(rR);
   const double cL = sqrt_pos(c2L), cR = sqrt_pos(c2R);
-  // Einfeldt: Roe-averaged normal velocity and sound-speed bound
+  // Einfeldt: Roe-averaged normal velocity and sound-speed bound. A negative
+  // density (a face check_face_states reports) makes the averages NaN, which
+  // fmin and fmax below pass over, so its 1/rho is not taken from its root.
   const double sL = sqrt_pos(rL), sR = sqrt_pos(rR);
-  const double isum = div_nr(1.0, sL + sR);
-  const double ubar = (sL * uL + sR * uR) * isum;
-  const double eta2 = 0.5 * sL * sR * isum * isum;
-  const double dbar = sqrt_pos((sL * c2L + sR * c2R) * isum + eta2 * sq(uR - uL));
+  const double isum = rcp_nr(sL + sR);
+  const double ubar = fma(sL, uL, sR * uR) * isum;
+  const double dbar = sqrt_pos(isum * fma(0.5 * (sL * sR) * isum, sq(uR - uL), fma(sL, c2L, sR * c2R)));
   const double SL = fmin(uL - cL, ubar - dbar);
   const double SR = fmax(uR + cR, ubar + dbar);
   const double mL = rL * (SL - uL), mR = rR * (SR - uR);  // mass fluxes relative to the waves
@@ -310,7 +353,7 @@ __host__ __device__ __forceinline__ void hllc(double gamma, double gm1i, const d
   // star state U*_K = rho_K (S_K - u_K)/(S_K - S*) (1, S*, t1, t2, E_K/rho_K + (S*-u_K)(S* + p_K/(rho_K (S_K-u_K))));
   // the energy slot is rearranged so that no division by rho_K or m_K
   // remains; outside the star region it may be non-finite and is discarded
-  const double i = div_nr(1.0, S - Ss);
+  const double i = rcp_nr(S - Ss);
   const double f = m * i;
   const double e = (S - u) * i * E + (Ss - u) * (f * Ss + p * i);
   const double F0 = r * u;
@@ -353,66 +396,55 @@ __host__ __device__ __forceinline__ void face_tangential(const FaceWindow& w, do
   for (int k = 0; k < 4; ++k) tf[k] = rc4(w.tg[0][k], w.tg[1][k], w.tg[2][k], w.tg[3][k]);
 }
 
-// Numerical flux G = F - F^d across the face (§3.3, §3.4) from given
-// reconstructed states WL, WR (inviscid part), the window's cells 1..4
-// (velocities and T~ for the fourth-order normal derivatives and the face
-// velocities) and the face values tf of the tangential derivatives.
-// Subtracts the dissipative flux F^d (§3.4) across the face from F: the
-// window's cells 1..4 (velocities and T~ for the fourth-order normal
-// derivatives and the face velocities) and the face values tf of the
-// tangential derivatives.
-// The same from the primitives q[0..3] and T~[0..3] of the four cells i-1 ..
-// i+2 around the face i+1/2.
-template <int D>
+// Subtracts the dissipative flux F^d (§3.4) across face i+1/2 from F: the
+// primitives q[0..3] and T~[0..3] of cells i-1 .. i+2 (velocities and T~ for
+// the fourth-order normal derivatives and the face velocities) and the face
+// values tf of the tangential derivatives d u_D / d x_T1, d u_D / d x_T2 and
+// d u_T1 / d x_T1 + d u_T2 / d x_T2 (the two enter only through div u).
+template <int D, int PHYS = PHYS_ANY>
 __host__ __device__ __forceinline__ void sub_dissipative_q(const Geom& g, const double (*q)[5], const double* T,
                                                            const double* tf, double* F) {
   constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
-  if (g.viscous || g.heat) {
-    const double i24 = g.idx[D] * (1.0 / 24.0);
-    auto dn = [&](double a, double b, double c, double d) { return (a - 27.0 * b + 27.0 * c - d) * i24; };
-    double Fd1 = 0.0, Fd2 = 0.0, Fd3 = 0.0, Fd4 = 0.0;  // slots D, T1, T2 momentum; energy
-    if (g.viscous) {
-      // normal derivatives of the three velocity components
-      const double dD = dn(q[0][1 + D], q[1][1 + D], q[2][1 + D], q[3][1 + D]);
-      const double d1 = dn(q[0][1 + T1], q[1][1 + T1], q[2][1 + T1], q[3][1 + T1]);
-      const double d2 = dn(q[0][1 + T2], q[1][1 + T2], q[2][1 + T2], q[3][1 + T2]);
-      const double uD_t1 = tf[0], u1_t1 = tf[1], uD_t2 = tf[2], u2_t2 = tf[3];
-      const double div = dD + u1_t1 + u2_t2;
-      const double tDD = g.mu * (dD + dD) - (2.0 / 3.0) * g.mu * div;
-      const double tD1 = g.mu * (uD_t1 + d1);
-      const double tD2 = g.mu * (uD_t2 + d2);
-      const double ufD = rc4(q[0][1 + D], q[1][1 + D], q[2][1 + D], q[3][1 + D]);
-      const double uf1 = rc4(q[0][1 + T1], q[1][1 + T1], q[2][1 + T1], q[3][1 + T1]);
-      const double uf2 = rc4(q[0][1 + T2], q[1][1 + T2], q[2][1 + T2], q[3][1 + T2]);
-      Fd1 = tDD;
-      Fd2 = tD1;
-      Fd3 = tD2;
-      Fd4 = ufD * tDD + uf1 * tD1 + uf2 * tD2;
-    }
-    if (g.heat) Fd4 += g.kappa * dn(T[0], T[1], T[2], T[3]);
-    F[1 + D] -= Fd1;
-    F[1 + T1] -= Fd2;
-    F[1 + T2] -= Fd3;
-    F[4] -= Fd4;
+  const double i24 = g.idx[D] * (1.0 / 24.0);
+  auto dn = [&](double a, double b, double c, double d) { return fma(27.0, c - b, a - d) * i24; };
+  auto rc16 = [](double a, double b, double c, double d) { return fma(9.0, b + c, -(a + d)); };  // 16 x the face value
+  if (with_viscous<PHYS>(g)) {
+    // normal derivatives of the three velocity components
+    const double dD = dn(q[0][1 + D], q[1][1 + D], q[2][1 + D], q[3][1 + D]);
+    const double d1 = dn(q[0][1 + T1], q[1][1 + T1], q[2][1 + T1], q[3][1 + T1]);
+    const double d2 = dn(q[0][1 + T2], q[1][1 + T2], q[2][1 + T2], q[3][1 + T2]);
+    const double tDD = g.mu * fma(4.0 / 3.0, dD, (-2.0 / 3.0) * tf[2]);
+    const double tD1 = g.mu * (tf[0] + d1);
+    const double tD2 = g.mu * (tf[1] + d2);
+    const double ufD = rc16(q[0][1 + D], q[1][1 + D], q[2][1 + D], q[3][1 + D]);
+    const double uf1 = rc16(q[0][1 + T1], q[1][1 + T1], q[2][1 + T1], q[3][1 + T1]);
+    const double uf2 = rc16(q[0][1 + T2], q[1][1 + T2], q[2][1 + T2], q[3][1 + T2]);
+    F[1 + D] -= tDD;
+    F[1 + T1] -= tD1;
+    F[1 + T2] -= tD2;
+    F[4] = fma(-1.0 / 16.0, fma(ufD, tDD, fma(uf1, tD1, uf2 * tD2)), F[4]);
   }
+  if (with_heat<PHYS>(g)) F[4] = fma(-g.kappa, dn(T[0], T[1], T[2], T[3]), F[4]);
 }
 
-template <int D>
+// The same from a full window and its four tangential derivatives.
+template <int D, int PHYS = PHYS_ANY>
 __host__ __device__ __forceinline__ void sub_dissipative(const Geom& g, const FaceWindow& w, const double* tf,
                                                          double* F) {
-  sub_dissipative_q<D>(g, w.q + 1, w.T, tf, F);
+  const double t3[3] = {tf[0], tf[2], tf[1] + tf[3]};
+  sub_dissipative_q<D, PHYS>(g, w.q + 1, w.T, t3, F);
 }
 
-template <int D, bool RUS = false, bool NN = false>
+template <int D, bool RUS, bool NN, int PHYS>
 __host__ __device__ __forceinline__ void face_flux_lr(const Geom& g, const double* WL, const double* WR,
                                                       const FaceWindow& w, const double* tf, double* G) {
   double F[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  if (g.inviscid) {
+  if (with_inviscid<PHYS>(g)) {
     if constexpr (NN) rusanov<D, true>(g.gamma, g.gm1i, WL, WR, F, w.a);
     else if constexpr (RUS) rusanov<D>(g.gamma, g.gm1i, WL, WR, F);
     else hllc<D>(g.gamma, g.gm1i, WL, WR, F);
   }
-  sub_dissipative<D>(g, w, tf, F);
+  sub_dissipative<D, PHYS>(g, w, tf, F);
 #pragma unroll
   for (int v = 0; v < 5; ++v) G[v] = F[v];
 }
@@ -508,19 +540,19 @@ __host__ __device__ __forceinline__ void roe_flux(const Geom& g, const double (&
 // or the Roe flux splitting, then the dissipative flux. The scheme is a
 // compile-time choice: a run-time branch between them multiplies the live
 // registers of the sweeps.
-template <int D, int SCH = SCH_JS>
+template <int D, int SCH = SCH_JS, int PHYS = PHYS_ANY>
 __host__ __device__ __forceinline__ void face_flux_tf(const Geom& g, const FaceWindow& w, const double* tf,
                                                       double* G) {
   if constexpr (SCH == SCH_ROE) {
     double F[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (g.inviscid) roe_flux<D>(g, w.q, F);
-    sub_dissipative<D>(g, w, tf, F);
+    if (with_inviscid<PHYS>(g)) roe_flux<D>(g, w.q, F);
+    sub_dissipative<D, PHYS>(g, w, tf, F);
 #pragma unroll
     for (int v = 0; v < 5; ++v) G[v] = F[v];
     return;
   }
   double WL[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, WR[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  if (g.inviscid) {
+  if (with_inviscid<PHYS>(g)) {
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
       if constexpr (sch_weno3(SCH)) {
@@ -535,7 +567,7 @@ __host__ __device__ __forceinline__ void face_flux_tf(const Geom& g, const FaceW
       }
     }
   }
-  face_flux_lr<D, sch_rusanov(SCH), SCH == SCH_W3_NN>(g, WL, WR, w, tf, G);
+  face_flux_lr<D, sch_rusanov(SCH), SCH == SCH_W3_NN, PHYS>(g, WL, WR, w, tf, G);
 }
 
 // Reconstructed states of the cell-centred schemes (WENO5-JS and WENO3-JS on
@@ -545,40 +577,45 @@ __host__ __device__ __forceinline__ void face_flux_tf(const Geom& g, const FaceW
 // state of face i+1/2 (qr) and the right state of face i-1/2 (ql), per
 // variable.
 template <int SCH>
-__host__ __device__ __forceinline__ void recon_pair(const double (*q)[5], double* qr, double* ql) {
+__host__ __device__ __forceinline__ void recon_pair(double (*q)[5], double* qr, double* ql) {
   static_assert(SCH != SCH_ROE && SCH != SCH_Z, "face-by-face schemes");
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
+    pin(q[2][v]);
     if constexpr (sch_weno3(SCH)) weno3_pair(q[1][v], q[2][v], q[3][v], qr[v], ql[v]);
     else weno5_pair(q[0][v], q[1][v], q[2][v], q[3][v], q[4][v], qr[v], ql[v]);
+    pin(qr[v]);
+    pin(ql[v]);
   }
 }
 
 // Numerical flux G = F - F^d across face i+1/2 (§3.3, §3.4) from its
 // reconstructed states WL, WR, the primitives q[0..3] and T~[0..3] of cells
-// i-1 .. i+2, the face values tf of the tangential derivatives and, for the
-// Rusanov-NN flux, the face's alpha.
-template <int D, int SCH>
+// i-1 .. i+2, the face values tf of the tangential derivatives (as in
+// sub_dissipative_q) and, for the Rusanov-NN flux, the face's alpha.
+template <int D, int SCH, int PHYS>
 __host__ __device__ __forceinline__ void face_flux_states(const Geom& g, const double* WL, const double* WR,
                                                           const double (*q)[5], const double* T, const double* tf,
                                                           double alpha, double* G) {
   double F[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  if (g.inviscid) {
+  if (with_inviscid<PHYS>(g)) {
     if constexpr (SCH == SCH_W3_NN) rusanov<D, true>(g.gamma, g.gm1i, WL, WR, F, alpha);
     else if constexpr (sch_rusanov(SCH)) rusanov<D>(g.gamma, g.gm1i, WL, WR, F);
     else hllc<D>(g.gamma, g.gm1i, WL, WR, F);
   }
-  sub_dissipative_q<D>(g, q, T, tf, F);
+#pragma unroll
+  for (int v = 0; v < 5; ++v) pin(F[v]);
+  sub_dissipative_q<D, PHYS>(g, q, T, tf, F);
 #pragma unroll
   for (int v = 0; v < 5; ++v) G[v] = F[v];
 }
 
 // Numerical flux G = F - F^d across the face (§3.3, §3.4) from a full window.
-template <int D, int SCH = SCH_JS>
+template <int D, int SCH = SCH_JS, int PHYS = PHYS_ANY>
 __host__ __device__ __forceinline__ void face_flux(const Geom& g, const FaceWindow& w, double* G) {
   double tf[4] = {0.0, 0.0, 0.0, 0.0};
-  if (g.viscous) face_tangential(w, tf);
-  face_flux_tf<D, SCH>(g, w, tf, G);
+  if (with_viscous<PHYS>(g)) face_tangential(w, tf);
+  face_flux_tf<D, SCH, PHYS>(g, w, tf, G);
 }
 
 }  // namespace cfd
