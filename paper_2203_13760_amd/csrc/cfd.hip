@@ -86,6 +86,7 @@ struct cfd_solver {
   double* nnbar = nullptr;    // caller's weight-gradient accumulator (may be NULL)
   NNTape tape{};
   int npart = 0;
+  bool images = false;        // the sweeps store the halo images of the next primitives
   DevCtl* ctl = nullptr;
   hipStream_t cap = nullptr;
   hipStream_t side = nullptr;  // the dissipative face reverses run here, beside the inviscid ones
@@ -345,44 +346,52 @@ static void launch_march(int mode, const double* P, const StageIO& io, const Geo
 }
 
 template <int SCH, int PHYS>
-static void launch_x(int mode, const double* P, const StageIO& io, const Geom& g, hipStream_t st) {
+static void launch_x(int mode, bool img, const double* P, const StageIO& io, const Geom& g, hipStream_t st) {
   const dim3 grid((unsigned)sweep_x_blocks(g)), blk(kBlock);
-  switch (mode) {
-    case MODE_WRITE: hipLaunchKernelGGL((k_sweep_x<MODE_WRITE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g); break;
-    case MODE_WRITE_RK: hipLaunchKernelGGL((k_sweep_x<MODE_WRITE_RK, true, SCH, PHYS>), grid, blk, 0, st, P, io, g); break;
-    default:
-      if constexpr (SCH == SCH_ROE || SCH == SCH_Z) {
-        if (mode == MODE_ACC) hipLaunchKernelGGL((k_sweep_x<MODE_ACC, false, SCH, PHYS>), grid, blk, 0, st, P, io, g);
-        else if (mode == MODE_ACC_RK) hipLaunchKernelGGL((k_sweep_x<MODE_ACC_RK, true, SCH, PHYS>), grid, blk, 0, st, P, io, g);
-        else hipLaunchKernelGGL((k_sweep_x<MODE_ACC2_RK, true, SCH, PHYS>), grid, blk, 0, st, P, io, g);
-      }
+  constexpr bool face = SCH == SCH_ROE || SCH == SCH_Z;
+  if (mode == MODE_WRITE) {
+    hipLaunchKernelGGL((k_sweep_x<MODE_WRITE, false, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
+  } else if (mode == MODE_WRITE_RK) {
+    if (!face && img) hipLaunchKernelGGL((k_sweep_x<MODE_WRITE_RK, true, SCH, PHYS, !face>), grid, blk, 0, st, P, io, g);
+    else hipLaunchKernelGGL((k_sweep_x<MODE_WRITE_RK, true, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
+  } else if constexpr (face) {
+    if (mode == MODE_ACC) hipLaunchKernelGGL((k_sweep_x<MODE_ACC, false, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
+    else if (mode == MODE_ACC_RK) hipLaunchKernelGGL((k_sweep_x<MODE_ACC_RK, true, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
+    else hipLaunchKernelGGL((k_sweep_x<MODE_ACC2_RK, true, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
   }
+}
+
+template <int AX, int MODE, int SCH, int PHYS>
+static void launch_mx_mode(bool img, const double* P, const StageIO& io, const Geom& g, hipStream_t st) {
+  const dim3 grid((unsigned)sweep_mx_blocks(g, AX)), blk(kBlock);
+  constexpr bool rk = mode_rk(MODE);
+  if (rk && img) hipLaunchKernelGGL((k_sweep_mx<AX, MODE, rk, SCH, PHYS, rk>), grid, blk, 0, st, P, io, g);
+  else hipLaunchKernelGGL((k_sweep_mx<AX, MODE, rk, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
 }
 
 template <int SCH, int PHYS>
-static void launch_mx(int ax, int mode, const double* P, const StageIO& io, const Geom& g, hipStream_t st) {
+static void launch_mx(int ax, int mode, bool img, const double* P, const StageIO& io, const Geom& g, hipStream_t st) {
   if constexpr (SCH != SCH_ROE && SCH != SCH_Z) {
-    const dim3 grid((unsigned)sweep_mx_blocks(g, ax)), blk(kBlock);
     if (ax == 2) {
-      if (mode == MODE_WRITE) hipLaunchKernelGGL((k_sweep_mx<2, MODE_WRITE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g);
-      else hipLaunchKernelGGL((k_sweep_mx<2, MODE_WRITE_RK, true, SCH, PHYS>), grid, blk, 0, st, P, io, g);
+      if (mode == MODE_WRITE) launch_mx_mode<2, MODE_WRITE, SCH, PHYS>(img, P, io, g, st);
+      else launch_mx_mode<2, MODE_WRITE_RK, SCH, PHYS>(img, P, io, g, st);
       return;
     }
     switch (mode) {
-      case MODE_WRITE: hipLaunchKernelGGL((k_sweep_mx<1, MODE_WRITE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g); break;
-      case MODE_ACC: hipLaunchKernelGGL((k_sweep_mx<1, MODE_ACC, false, SCH, PHYS>), grid, blk, 0, st, P, io, g); break;
-      case MODE_WRITE_RK: hipLaunchKernelGGL((k_sweep_mx<1, MODE_WRITE_RK, true, SCH, PHYS>), grid, blk, 0, st, P, io, g); break;
-      default: hipLaunchKernelGGL((k_sweep_mx<1, MODE_ADD_RK, true, SCH, PHYS>), grid, blk, 0, st, P, io, g);
+      case MODE_WRITE: return launch_mx_mode<1, MODE_WRITE, SCH, PHYS>(img, P, io, g, st);
+      case MODE_ACC: return launch_mx_mode<1, MODE_ACC, SCH, PHYS>(img, P, io, g, st);
+      case MODE_WRITE_RK: return launch_mx_mode<1, MODE_WRITE_RK, SCH, PHYS>(img, P, io, g, st);
+      default: launch_mx_mode<1, MODE_ADD_RK, SCH, PHYS>(img, P, io, g, st);
     }
   }
 }
 
-static void launch_sweep(const Geom& g, const Sweep& sw, const double* P, StageIO io, hipStream_t st) {
+static void launch_sweep(const Geom& g, const Sweep& sw, bool img, const double* P, StageIO io, hipStream_t st) {
   if (sw.r2) io.R = const_cast<double*>(io.R2);
   with_scheme(g, [&](auto sch, auto phys) {
     constexpr int SCH = decltype(sch)::value, PHYS = decltype(phys)::value;
-    if (sw.kind == Sweep::MARCH_X) launch_mx<SCH, PHYS>(sw.ax, sw.mode, P, io, g, st);
-    else if (sw.kind == Sweep::X) launch_x<SCH, PHYS>(sw.mode, P, io, g, st);
+    if (sw.kind == Sweep::MARCH_X) launch_mx<SCH, PHYS>(sw.ax, sw.mode, img, P, io, g, st);
+    else if (sw.kind == Sweep::X) launch_x<SCH, PHYS>(sw.mode, img, P, io, g, st);
     else if (sw.ax == 1) launch_march<1, SCH, PHYS>(sw.mode, P, io, g, st);
     else launch_march<2, SCH, PHYS>(sw.mode, P, io, g, st);
   });
@@ -420,10 +429,20 @@ static cfd_status enqueue_nn_alpha(cfd_solver* s, const double* P, hipStream_t s
   return CFD_OK;
 }
 
+// Whether the last sweep of a stage stores the halo images of the primitives it
+// writes (cell-centred schemes with an x axis, up to kImagesMaxCells padded
+// cells; else a pass of its own copies them). The pass is a launch of 4 to 5 us per
+// stage, the images cost the sweep registers and scattered stores: without ->
+// with them the implosion at 128^2 500 -> 412 us (20 steps), KH 331^2 583 ->
+// 528 us, a TGV step at 32^3 95 -> 87 us, but at 64^3 171 -> 180 us, KH 600^2
+// 556 -> 579 us and HIT 256^3 11.2 -> 11.6 ms.
+constexpr long long kImagesMaxCells = 1LL << 18;
+static bool stores_images(const Geom& g) { return !face_by_face(g) && g.act[0] && g.vs <= kImagesMaxCells; }
+
 // Enqueue the sweeps over primitives P. With rk set, the last one applies the
 // stage update into io.Uout and stores the primitives of the updated interior
-// cells into io.Pn, whose halo is then refreshed; otherwise io.R receives the
-// full right-hand side.
+// cells into io.Pn with its halo (itself or in a pass of its own, see
+// stores_images); otherwise io.R receives the full right-hand side.
 static cfd_status enqueue_fluxes(cfd_solver* s, const double* P, const StageIO& io, bool rk, hipStream_t st) {
   const Geom& g = s->g;
   if (g.nn) {
@@ -433,66 +452,75 @@ static cfd_status enqueue_fluxes(cfd_solver* s, const double* P, const StageIO& 
   Sweep plan[3];
   const int n = plan_sweeps(g, rk, plan);
   for (int i = 0; i < n; ++i) {
-    launch_sweep(g, plan[i], P, io, st);
+    launch_sweep(g, plan[i], s->images, P, io, st);
     CFD_LAUNCHED();
   }
-  if (rk) {
+  if (rk && !s->images) {
     hipLaunchKernelGGL(k_prim_halo, dim3(halo_blocks(g)), dim3(kBlock), 0, st, io.Pn, g, io.dtp);
     CFD_LAUNCHED();
   }
   return CFD_OK;
 }
 
-// Clear the CFL slots before a fresh accumulation: the last step of a run
-// leaves the maxima of its final state there, consumed by nobody.
-static cfd_status enqueue_clear_slots(cfd_solver* s, hipStream_t st) {
-  hipLaunchKernelGGL(k_zero, dim3(1), dim3(kBlock), 0, st, s->partial, (long long)s->npart);
+// Start of a run of steps: the primitives of U into Pb[0] with the health bits
+// and, for CFL steps, the size of the first step from the CFL rate maxima of U
+// (clipped against *t_dev and t_end when t_dev is given). The CFL slots are
+// clear before and after: whoever reads them clears them. dt_out (nullable)
+// receives the step.
+static cfd_status enqueue_step_prologue(cfd_solver* s, const double* U, double fixed_dt, double t_end,
+                                        const double* t_dev, double* dt_out, hipStream_t st) {
+  const bool cfl = !(fixed_dt > 0.0);
+  cfd_status rc = enqueue_prim(s, U, PRIM_HEALTH | (cfl ? PRIM_CFL : 0), nullptr, st);
+  if (rc || !(cfl || dt_out)) return rc;
+  hipLaunchKernelGGL(k_dt, dim3(1), dim3(kBlock), 0, st, s->ctl, s->g.cfl, fixed_dt, t_end, t_dev, dt_out, s->partial,
+                     s->npart);
   CFD_LAUNCHED();
   return CFD_OK;
 }
 
-// Step prologue: the primitives of U into Pb[0] with the health bits and,
-// for a CFL step, the CFL rate maxima of U.
-static cfd_status enqueue_step_prologue(cfd_solver* s, const double* U, bool cfl, hipStream_t st) {
-  if (cfl) {
-    cfd_status rc = enqueue_clear_slots(s, st);
-    if (rc) return rc;
-  }
-  return enqueue_prim(s, U, PRIM_HEALTH | (cfl ? PRIM_CFL : 0), nullptr, st);
+static StageIO stage_io(cfd_solver* s, double fixed_dt) {
+  StageIO io{};
+  io.R = s->Racc;
+  io.R2 = s->Racc2;
+  io.dtp = fixed_dt > 0.0 ? nullptr : &s->ctl->dt;
+  io.dt = fixed_dt;
+  io.partial = s->partial;
+  io.ctl = s->ctl;
+  return io;
 }
 
 // Enqueue one TVD-RK3 step on U in place; Pb[0] must hold the primitives of U
-// and, for a CFL step, the CFL slots its rate maxima (the prologue, or the
-// previous step, leaves both). fixed_dt > 0 fixes the step; otherwise the
-// CFL step of Un, clipped against *t_dev and t_end when t_dev is given.
-// dt_out (nullable) receives the step. Each stage's last sweep stores the
-// primitives of its output for the next stage (Pb[0] -> Pb[1] -> Pb[2] ->
-// Pb[0]); the third also the health bits of U^{n+1} and, for CFL steps, its
-// CFL rate maxima, so consecutive steps need no separate primitive pass.
+// and, for a CFL step, the control block the step's size (the prologue, or the
+// previous step, leaves both). fixed_dt > 0 fixes the step. Each stage's last
+// sweep stores the primitives of its output for the next stage (Pb[0] ->
+// Pb[1] -> Pb[2] -> Pb[0]); the third also the health bits of U^{n+1} and,
+// with `more` set on CFL steps, the size of the next step, advancing *t_dev by
+// this one's, so consecutive steps need neither a primitive pass nor a
+// step-size launch between them.
 // Pst (nullable): the primitives of the three stage inputs are read from and
 // written to Pst[0] (which must hold those of Un), Pst[1] and Pst[2] instead
 // of the solver's ring; the third stage still writes Pb[0].
-static cfd_status enqueue_step(cfd_solver* s, double* U, double fixed_dt, double t_end, double* t_dev,
-                               double* dt_out, hipStream_t st, double* U1 = nullptr, double* U2 = nullptr,
+static cfd_status enqueue_step(cfd_solver* s, double* U, double fixed_dt, bool more, double t_end, double* t_dev,
+                               hipStream_t st, double* U1 = nullptr, double* U2 = nullptr,
                                double* const* Pst = nullptr) {
   if (!U1) U1 = s->U1;
   if (!U2) U2 = s->U2;
   double* const P0 = Pst ? Pst[0] : s->Pb[0];
   double* const P1 = Pst ? Pst[1] : s->Pb[1];
   double* const P2 = Pst ? Pst[2] : s->Pb[2];
-  const double* dtp = &s->ctl->dt;
-  const bool cfl = !(fixed_dt > 0.0);
-  hipLaunchKernelGGL(k_dt, dim3(1), dim3(kBlock), 0, st, s->ctl, s->g.cfl, fixed_dt, t_end, t_dev, dt_out,
-                     s->partial, s->npart);
-  CFD_LAUNCHED();
-  StageIO io{};
-  io.R = s->Racc;
-  io.R2 = s->Racc2;
+  const bool next = more && !(fixed_dt > 0.0);
+  StageIO io = stage_io(s, fixed_dt);
   io.Un = U;
-  io.dtp = dtp;
-  io.partial = s->partial;
-  io.ctl = s->ctl;
   cfd_status rc;
+  auto last_stage = [&]() {
+    io.Uout = U;
+    io.Pn = s->Pb[0];
+    io.what = PRIM_HEALTH | (next ? PRIM_CFL : 0);
+    io.next = next;
+    io.cfl = s->g.cfl;
+    io.t_end = t_end;
+    io.t = t_dev;
+  };
   // stage 1: U1 = Un + dt R(Un)
   io.Uk = U;
   io.Uout = U1;
@@ -504,11 +532,9 @@ static cfd_status enqueue_step(cfd_solver* s, double* U, double fixed_dt, double
   if (s->g.rk2) {
     // TVD-RK2, second stage: Un+1 = 1/2 Un + 1/2 (U1 + dt R(U1)), in place on U
     io.Uk = U1;
-    io.Uout = U;
     io.a = 0.5;
     io.b = 0.5;
-    io.Pn = s->Pb[0];
-    io.what = PRIM_HEALTH | (cfl ? PRIM_CFL : 0);
+    last_stage();
     return enqueue_fluxes(s, P1, io, true, st);
   }
   // stage 2: U2 = 3/4 Un + 1/4 (U1 + dt R(U1))
@@ -520,16 +546,14 @@ static cfd_status enqueue_step(cfd_solver* s, double* U, double fixed_dt, double
   if ((rc = enqueue_fluxes(s, P1, io, true, st))) return rc;
   // stage 3: Un+1 = 1/3 Un + 2/3 (U2 + dt R(U2)), in place on U
   io.Uk = U2;
-  io.Uout = U;
   io.a = 1.0 / 3.0;
   io.b = 2.0 / 3.0;
-  io.Pn = s->Pb[0];
-  io.what = PRIM_HEALTH | (cfl ? PRIM_CFL : 0);
+  last_stage();
   return enqueue_fluxes(s, P2, io, true, st);
 }
 
 static cfd_status enqueue_fill_halo(cfd_solver* s, double* U, hipStream_t st) {
-  hipLaunchKernelGGL(k_fill_halo, plane_grid(s->g), dim3(kBlock), 0, st, U, s->g);
+  hipLaunchKernelGGL(k_fill_halo, dim3(halo_blocks(s->g)), dim3(kBlock), 0, st, U, s->g);
   CFD_LAUNCHED();
   return CFD_OK;
 }
@@ -548,7 +572,7 @@ static cfd_status run_graph(cfd_solver* s, double* U, int mode, double fixed_dt,
     }
     hipGraph_t graph;
     CFD_HIP(hipStreamBeginCapture(s->cap, hipStreamCaptureModeThreadLocal));
-    cfd_status rc = enqueue_step(s, U, fixed_dt, t_end, t_dev, nullptr, s->cap);
+    cfd_status rc = enqueue_step(s, U, fixed_dt, true, t_end, t_dev, s->cap);
     hipError_t ec = hipStreamEndCapture(s->cap, &graph);
     if (rc) return rc;
     if (ec != hipSuccess) return fail(CFD_EHIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(ec));
@@ -564,7 +588,7 @@ static cfd_status run_graph(cfd_solver* s, double* U, int mode, double fixed_dt,
     gc.kd[0] = fixed_dt;
     gc.kd[1] = t_end;
   }
-  cfd_status rc = enqueue_step_prologue(s, U, !(fixed_dt > 0.0), st);
+  cfd_status rc = enqueue_step_prologue(s, U, fixed_dt, t_end, t_dev, nullptr, st);
   if (rc) return rc;
   for (int i = 0; i < n; ++i) CFD_HIP(hipGraphLaunch(gc.exec, st));
   return CFD_OK;
@@ -796,6 +820,7 @@ cfd_status cfd_create(const cfd_config* cfg, cfd_solver** out) {
   make_geom(*cfg, s->g);
   choose_segment(s->g);
   s->ncell = s->g.vs;
+  s->images = stores_images(s->g);
   s->nint = (long long)cfg->n[0] * cfg->n[1] * cfg->n[2];
   const size_t st = sizeof(double) * 5 * (size_t)s->ncell;
   bool ok = hipMalloc(&s->U1, st) == hipSuccess && hipMalloc(&s->U2, st) == hipSuccess &&
@@ -891,11 +916,9 @@ cfd_status cfd_rhs(cfd_solver* s, double* U, double* R, void* stream) {
 cfd_status cfd_compute_dt(cfd_solver* s, const double* U, double* dt_dev, void* stream) {
   if (!s || !U || !dt_dev) return fail(CFD_EINVAL, "NULL argument");
   hipStream_t st = (hipStream_t)stream;
-  cfd_status rc = enqueue_clear_slots(s, st);
-  if (rc) return rc;
   hipLaunchKernelGGL(k_cfl, plane_grid(s->g), dim3(kBlock), 0, st, U, s->g, s->partial);
   CFD_LAUNCHED();
-  hipLaunchKernelGGL(k_dt, dim3(1), dim3(kBlock), 0, st, s->ctl, s->g.cfl, 0.0, 0.0, (double*)nullptr, dt_dev,
+  hipLaunchKernelGGL(k_dt, dim3(1), dim3(kBlock), 0, st, s->ctl, s->g.cfl, 0.0, 0.0, (const double*)nullptr, dt_dev,
                      s->partial, s->npart);
   CFD_LAUNCHED();
   return CFD_OK;
@@ -905,9 +928,10 @@ cfd_status cfd_rk3_step(cfd_solver* s, double* U, double dt, double* dt_used_dev
   if (!s || !U) return fail(CFD_EINVAL, "NULL argument");
   if (!std::isfinite(dt)) return fail(CFD_EINVAL, "dt must be finite");
   hipStream_t st = (hipStream_t)stream;
-  cfd_status rc = enqueue_step_prologue(s, U, !(dt > 0.0), st);
+  const double fixed = dt > 0.0 ? dt : 0.0;
+  cfd_status rc = enqueue_step_prologue(s, U, fixed, 0.0, nullptr, dt_used_dev, st);
   if (rc) return rc;
-  if ((rc = enqueue_step(s, U, dt > 0.0 ? dt : 0.0, 0.0, nullptr, dt_used_dev, st))) return rc;
+  if ((rc = enqueue_step(s, U, fixed, false, 0.0, nullptr, st))) return rc;
   return enqueue_fill_halo(s, U, st);
 }
 
@@ -947,10 +971,6 @@ cfd_status cfd_profile_stage(cfd_solver* s, const double* U, int32_t reps, doubl
   if (!s || !U || !ms_out || reps < 1 || reps > 4096) return fail(CFD_EINVAL, "bad argument");
   hipStream_t st = (hipStream_t)stream;
   const Geom& g = s->g;
-  // a fixed nonzero step so that the stage kernels do their work
-  hipLaunchKernelGGL(k_dt, dim3(1), dim3(kBlock), 0, st, s->ctl, g.cfl, 1e-12, 0.0, (double*)nullptr,
-                     (double*)nullptr, s->partial, s->npart);
-  CFD_LAUNCHED();
   Sweep plan[3];
   const int nplan = plan_sweeps(g, true, plan);
   // slots of ms_out: prim pass, x, y, z sweeps, halo refresh of the next
@@ -970,18 +990,13 @@ cfd_status cfd_profile_stage(cfd_solver* s, const double* U, int32_t reps, doubl
     }
   for (int r = 0; r < reps && rc == CFD_OK; ++r) {
     const int stage = r % 3;
-    StageIO io{};
-    io.R = s->Racc;
-    io.R2 = s->Racc2;
+    StageIO io = stage_io(s, 1e-12);  // a nonzero step, so that the stage kernels do their work
     io.Un = U;
     io.Uk = U;
     io.Uout = s->U2;
     io.a = stage == 0 ? 0.0 : (stage == 1 ? 0.75 : 1.0 / 3.0);
     io.b = stage == 0 ? 1.0 : (stage == 1 ? 0.25 : 2.0 / 3.0);
-    io.dtp = &s->ctl->dt;
     io.Pn = s->Pb[1];
-    io.partial = s->partial;
-    io.ctl = s->ctl;
     io.what = stage == 2 ? (PRIM_HEALTH | PRIM_CFL) : 0;
     hipEvent_t* e = ev.data() + (size_t)r * (K + 1);
     int* sl = slot.data() + (size_t)r * (K + 1);
@@ -991,7 +1006,7 @@ cfd_status cfd_profile_stage(cfd_solver* s, const double* U, int32_t reps, doubl
     sl[n] = 0;
     (void)hipEventRecord(e[++n], st);
     for (int i = 0; i < nplan; ++i) {
-      launch_sweep(g, plan[i], s->P, io, st);
+      launch_sweep(g, plan[i], false, s->P, io, st);
       sl[n] = 1 + (plan[i].kind == Sweep::MARCH_X ? 0 : plan[i].ax);
       (void)hipEventRecord(e[++n], st);
     }
@@ -1012,7 +1027,10 @@ cfd_status cfd_profile_stage(cfd_solver* s, const double* U, int32_t reps, doubl
     }
   for (size_t e = 0; e < made; ++e) (void)hipEventDestroy(ev[e]);
   // the CFL maxima of the third stages are nobody's: clear them
-  if (rc == CFD_OK) rc = enqueue_clear_slots(s, st);
+  if (rc == CFD_OK) {
+    hipLaunchKernelGGL(k_zero, dim3(1), dim3(kBlock), 0, st, s->partial, (long long)s->npart);
+    if (hipGetLastError() != hipSuccess) rc = fail(CFD_EHIP, "profiled stage failed");
+  }
   for (int k = 0; k < K; ++k) ms_out[k] = acc[k] / reps;
   return rc;
 }
@@ -1041,24 +1059,15 @@ cfd_status cfd_rk3_step_adjoint(cfd_solver* s, const double* Un, double dt, cons
   // forward recompute of the stage states U1, U2 with the fixed step; the
   // stage updates leave the primitives of Un, U1, U2 in Pb[0], Pb[1], Pb[2]
   // (rho, u, v, w, p with halos: all the face reverses and the fold read)
-  hipLaunchKernelGGL(k_dt, dim3(1), dim3(kBlock), 0, st, s->ctl, g.cfl, dt, 0.0, (double*)nullptr,
-                     (double*)nullptr, s->partial, s->npart);
-  CFD_LAUNCHED();
-  const double* dtp = &s->ctl->dt;
-  StageIO io{};
-  io.R = s->Racc;
-  io.R2 = s->Racc2;
+  StageIO io = stage_io(s, dt);
   io.Un = Un;
-  io.dtp = dtp;
-  io.partial = s->partial;
-  io.ctl = s->ctl;
   io.what = 0;
   io.Uk = Un;
   io.Uout = s->U1;
   io.a = 0.0;
   io.b = 1.0;
   io.Pn = s->Pb[1];
-  if ((rc = enqueue_prim(s, Un, 0, dtp, st))) return rc;
+  if ((rc = enqueue_prim(s, Un, 0, nullptr, st))) return rc;
   if ((rc = enqueue_fluxes(s, s->Pb[0], io, true, st))) return rc;
   if (g.rk2) {
     const double* const Pk[2] = {s->Pb[0], s->Pb[1]};
@@ -1094,9 +1103,9 @@ cfd_status cfd_rk3_step_stages(cfd_solver* s, double* U, double dt, double* U1_o
   if (U1_out == U || U2_out == U || U1_out == U2_out) return fail(CFD_EINVAL, "the stage buffers must be distinct");
   if (s->g.rk2) return fail(CFD_EUNSUPPORTED, "the stages kept are those of TVD-RK3");
   hipStream_t st = (hipStream_t)stream;
-  cfd_status rc = enqueue_step_prologue(s, U, false, st);
+  cfd_status rc = enqueue_step_prologue(s, U, dt, 0.0, nullptr, nullptr, st);
   if (rc) return rc;
-  if ((rc = enqueue_step(s, U, dt, 0.0, nullptr, nullptr, st, U1_out, U2_out))) return rc;
+  if ((rc = enqueue_step(s, U, dt, false, 0.0, nullptr, st, U1_out, U2_out))) return rc;
   return enqueue_fill_halo(s, U, st);
 }
 
@@ -1134,7 +1143,7 @@ cfd_status cfd_rk3_step_prims(cfd_solver* s, double* U, double dt, double* P_out
   hipLaunchKernelGGL(k_prim, plane_grid(s->g), dim3(kBlock), 0, st, (const double*)U, Pst[0], s->g, s->ctl,
                      PRIM_HEALTH, (const double*)nullptr, s->partial);
   CFD_LAUNCHED();
-  cfd_status rc = enqueue_step(s, U, dt, 0.0, nullptr, nullptr, st, nullptr, nullptr, Pst);
+  cfd_status rc = enqueue_step(s, U, dt, false, 0.0, nullptr, st, nullptr, nullptr, Pst);
   if (rc) return rc;
   return enqueue_fill_halo(s, U, st);
 }
@@ -1208,6 +1217,7 @@ cfd_status cfd_rk3_step_noalloc(const cfd_config* cfg, double* U, double dt, dou
   make_geom(*cfg, s.g);
   choose_segment(s.g);
   s.ncell = s.g.vs;
+  s.images = stores_images(s.g);
   s.nint = (long long)cfg->n[0] * cfg->n[1] * cfg->n[2];
   if (s.ncell > noalloc_max_cells())
     return fail(CFD_EINVAL, "grid too large for the allocation-free step: " + std::to_string(s.ncell) +
@@ -1226,12 +1236,13 @@ cfd_status cfd_rk3_step_noalloc(const cfd_config* cfg, double* U, double dt, dou
   for (int k = 0; k < 3; ++k) s.Pb[k] = b + (20 + 6 * k) * nc;
   s.P = s.Pb[0];
   hipStream_t st = (hipStream_t)stream;
-  // the control block (step size, health bits) starts clear on every call;
-  // the CFL slots are cleared by the prologue of a CFL step
+  // the control block (step size, health bits) starts clear on every call; the
+  // CFL slots are clear between calls
   hipLaunchKernelGGL(k_zero, dim3(1), dim3(kBlock), 0, st, base + kCflSlots, 32LL);
   CFD_LAUNCHED();
-  if ((rc = enqueue_step_prologue(&s, U, !(dt > 0.0), st))) return rc;
-  if ((rc = enqueue_step(&s, U, dt > 0.0 ? dt : 0.0, 0.0, nullptr, dt_used_dev, st))) return rc;
+  const double fixed = dt > 0.0 ? dt : 0.0;
+  if ((rc = enqueue_step_prologue(&s, U, fixed, 0.0, nullptr, dt_used_dev, st))) return rc;
+  if ((rc = enqueue_step(&s, U, fixed, false, 0.0, nullptr, st))) return rc;
   return enqueue_fill_halo(&s, U, st);
 }
 

@@ -108,7 +108,7 @@ __device__ __forceinline__ void batch_item(const BatchTable* __restrict__ tab, i
     const int local = b - prefix[k];
     const GridWork& w = tab->grid[k];
     const Geom& g = w.g;
-    StageIO io;
+    StageIO io{};
     io.R = w.R;
     io.R2 = w.R2;
     io.Un = w.U;

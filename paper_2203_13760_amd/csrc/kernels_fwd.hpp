@@ -24,7 +24,7 @@ namespace cfd {
 struct DevCtl {
   double dt;   // step of the current step (0: step disabled, t_end reached)
   int status;  // health bits, see cfd_check
-  int pad;
+  unsigned done;  // blocks of a step's last sweep that have published their CFL rate (0 between sweeps)
 };
 
 constexpr int kBlock = 256;
@@ -50,13 +50,18 @@ struct StageIO {
   const double* Uk;  // stage input state
   double* Uout;      // stage output state (may alias Un in the last stage)
   double a, b;       // Uout = a Un + b (Uk + dt R)
-  const double* dtp; // step size; nullptr for a plain right-hand side
+  const double* dtp; // step size on the device; nullptr: the fixed step dt
+  double dt;
   double* Pn;        // primitives of Uout, interior cells (sweeps with PN set)
   double* partial;   // CFL rate slots (PN sweeps with PRIM_CFL in `what`)
   DevCtl* ctl;       // health bits (PN sweeps with PRIM_HEALTH in `what`)
   int what;
+  int next;          // the sweep ends a step and forms the next one's size (dt_next)
+  double cfl, t_end;
+  double* t;
 };
 
+__device__ __forceinline__ double stage_dt(const StageIO& io) { return io.dtp ? *io.dtp : io.dt; }
 __device__ __forceinline__ bool step_disabled(const double* dtp) { return dtp != nullptr && *dtp == 0.0; }
 
 // Kernels over the padded grid use a plane-indexed launch: blockIdx.y is the
@@ -110,24 +115,6 @@ __host__ __device__ __forceinline__ int plane_blocks_x(const Geom& g) {
 }
 
 // ----------------------------------------------------------------------------
-// Halo refresh of a padded field of NC components (in place): halo cells copy
-// their interior source cell, interior cells do nothing.
-template <int NC = 5>
-__device__ __forceinline__ void fill_halo_body(double* U, const Geom& g, const PlaneIdx& p) {
-  if (!p.in) return;
-  const int si = bc_source(p.i, g.n[0], g.bc[0], g.bc[1]);
-  const int sj = bc_source(p.j, g.n[1], g.bc[2], g.bc[3]);
-  const int sk = bc_source(p.k, g.n[2], g.bc[4], g.bc[5]);
-  if (si == p.i && sj == p.j && sk == p.k) return;
-  const long long s = cell_at(g, si, sj, sk);
-  const double sg[3] = {bc_sign(p.i, g.n[0], g.bc[0], g.bc[1]), bc_sign(p.j, g.n[1], g.bc[2], g.bc[3]),
-                        bc_sign(p.k, g.n[2], g.bc[4], g.bc[5])};
-#pragma unroll
-  for (int v = 0; v < NC; ++v) U[v * g.vs + p.c] = (v >= 1 && v <= 3 ? sg[v - 1] : 1.0) * U[v * g.vs + s];
-}
-
-__global__ void __launch_bounds__(kBlock) k_fill_halo(double* U, Geom g) { fill_halo_body<5>(U, g, plane_index(g)); }
-
 // Halo refresh of the primitives P (6 components) after a sweep stored the
 // interior ones, one thread per halo cell; skipped with the step. Halo cells
 // are numbered slab by slab: the z halo planes (whole padded planes), then
@@ -195,6 +182,20 @@ __device__ __forceinline__ void prim_halo_body(double* P, const Geom& g, long lo
 __global__ void __launch_bounds__(kBlock) k_prim_halo(double* P, Geom g, const double* dtp) {
   if (step_disabled(dtp)) return;
   prim_halo_body(P, g, (long long)blockIdx.x * kBlock + threadIdx.x);
+}
+
+// Halo refresh of a state U in place from its interior, one thread per halo cell.
+__global__ void __launch_bounds__(kBlock) k_fill_halo(double* U, Geom g) {
+  int i, j, k;
+  if (!halo_cell(g, (long long)blockIdx.x * kBlock + threadIdx.x, i, j, k)) return;
+  const int si = bc_source(i, g.n[0], g.bc[0], g.bc[1]);
+  const int sj = bc_source(j, g.n[1], g.bc[2], g.bc[3]);
+  const int sk = bc_source(k, g.n[2], g.bc[4], g.bc[5]);
+  const long long c = cell_at(g, i, j, k), s = cell_at(g, si, sj, sk);
+  const double sg[3] = {bc_sign(i, g.n[0], g.bc[0], g.bc[1]), bc_sign(j, g.n[1], g.bc[2], g.bc[3]),
+                        bc_sign(k, g.n[2], g.bc[4], g.bc[5])};
+#pragma unroll
+  for (int v = 0; v < 5; ++v) U[v * g.vs + c] = (v >= 1 && v <= 3 ? sg[v - 1] : 1.0) * U[v * g.vs + s];
 }
 
 // Conservative interior state from primitive point values W (5 x interior, no halo).
@@ -358,31 +359,36 @@ __global__ void __launch_bounds__(kBlock) k_cfl(const double* __restrict__ U, Ge
   publish_rate(partial, blockIdx.y * gridDim.x + blockIdx.x, smax);
 }
 
-// Step size of the current step: fixed, or cfl / (max of the npart CFL rate
-// partials); clipped to t_end (> 0) and zero once t_end is reached. Advances
-// *t. One block of kBlock threads.
-__device__ __forceinline__ void dt_body(DevCtl* ctl, double cfl, double fixed_dt, double t_end, double* t,
-                                        double* dt_out, double* __restrict__ partial, int npart) {
-  double dt = fixed_dt;
-  if (!(fixed_dt > 0.0)) {
-    double m = 0.0;
-    for (int i = threadIdx.x; i < npart; i += blockDim.x) m = fmax(m, partial[i]);
-    m = block_max(m);  // every slot has been read once this returns
-    for (int i = threadIdx.x; i < npart; i += blockDim.x) partial[i] = 0.0;
-    dt = cfl / m;
-  }
-  if (threadIdx.x != 0) return;
+// Step size from the CFL rate maximum m (or the fixed one), clipped to end at
+// t_end (> 0) and zero once t has reached it.
+__device__ __forceinline__ double step_size(double cfl, double m, double fixed_dt, const double* t, double t_end) {
+  double dt = fixed_dt > 0.0 ? fixed_dt : cfl / m;
   if (t != nullptr && t_end > 0.0) {
     const double rem = t_end - *t;
     dt = rem > 0.0 ? fmin(dt, rem) : 0.0;
   }
+  return dt;
+}
+
+// Size of the next step: fixed, or cfl / (max of the npart CFL rate slots,
+// which are cleared); clipped to t_end (> 0) and zero once t has reached it.
+// One block of kBlock threads.
+__device__ __forceinline__ void dt_body(DevCtl* ctl, double cfl, double fixed_dt, double t_end, const double* t,
+                                        double* dt_out, double* __restrict__ partial, int npart) {
+  double m = 0.0;
+  if (!(fixed_dt > 0.0)) {
+    for (int i = threadIdx.x; i < npart; i += blockDim.x) m = fmax(m, partial[i]);
+    m = block_max(m);  // every slot has been read once this returns
+    for (int i = threadIdx.x; i < npart; i += blockDim.x) partial[i] = 0.0;
+  }
+  if (threadIdx.x != 0) return;
+  const double dt = step_size(cfl, m, fixed_dt, t, t_end);
   ctl->dt = dt;
-  if (t != nullptr) *t = *t + dt;
   if (dt_out != nullptr) *dt_out = dt;
 }
 
 __global__ void __launch_bounds__(kBlock) k_dt(DevCtl* ctl, double cfl, double fixed_dt, double t_end,
-                                               double* t, double* dt_out, double* __restrict__ partial,
+                                               const double* t, double* dt_out, double* __restrict__ partial,
                                                int npart) {
   dt_body(ctl, cfl, fixed_dt, t_end, t, dt_out, partial, npart);
 }
@@ -505,6 +511,46 @@ __device__ __forceinline__ void tangential_at_flat(const Geom& g, const double* 
   tangential_combine<D>(g, x, tg);
 }
 
+// Halo images of one axis of an interior coordinate c: the low halo cells
+// [lo, lo + nlo) and the high ones [hi, hi + nhi) whose boundary source is c.
+struct AxisImages {
+  int lo, nlo, hi, nhi;
+  __device__ __forceinline__ AxisImages(int c, int n, int h, int bc_lo, int bc_hi) {
+    const bool first = c < h, last = c >= n - h;
+    nlo = bc_lo == 0 ? last : (bc_lo == 2 ? first : (c == 0 ? h : 0));
+    lo = bc_lo == 0 ? c - n : (bc_lo == 2 ? -1 - c : -h);
+    nhi = bc_hi == 0 ? first : (bc_hi == 2 ? last : (c == n - 1 ? h : 0));
+    hi = bc_hi == 0 ? c + n : (bc_hi == 2 ? 2 * n - 1 - c : n);
+  }
+  __device__ __forceinline__ int count() const { return 1 + nlo + nhi; }
+  __device__ __forceinline__ int at(int c, int m) const { return m == 0 ? c : (m <= nlo ? lo + m - 1 : hi + m - 1 - nlo); }
+};
+
+// Stores the primitives w of interior cell (i, j, k) at its halo images: what
+// the halo pass copies, without its launch. Worth it on grids whose sweeps
+// take a few microseconds; on large ones the scattered stores cost the sweep
+// what the pass costs.
+__device__ __forceinline__ void store_images(double* P, const Geom& g, int i, int j, int k, const double* w) {
+  const bool edge = (g.act[0] && (i < g.h[0] || i >= g.n[0] - g.h[0])) ||
+                    (g.act[1] && (j < g.h[1] || j >= g.n[1] - g.h[1])) ||
+                    (g.act[2] && (k < g.h[2] || k >= g.n[2] - g.h[2]));
+  if (!edge) return;
+  const AxisImages X(i, g.n[0], g.h[0], g.bc[0], g.bc[1]), Y(j, g.n[1], g.h[1], g.bc[2], g.bc[3]),
+      Z(k, g.n[2], g.h[2], g.bc[4], g.bc[5]);
+  const int nx = g.act[0] ? X.count() : 1, ny = g.act[1] ? Y.count() : 1, nz = g.act[2] ? Z.count() : 1;
+  for (int c = 0; c < nz; ++c)
+    for (int b = 0; b < ny; ++b)
+      for (int a = c + b == 0 ? 1 : 0; a < nx; ++a) {
+        const int x = X.at(i, a), y = Y.at(j, b), z = Z.at(k, c);
+        const long long e = cell_at(g, x, y, z);
+        P[e] = w[0];
+        P[g.vs + e] = bc_sign(x, g.n[0], g.bc[0], g.bc[1]) * w[1];
+        P[2 * g.vs + e] = bc_sign(y, g.n[1], g.bc[2], g.bc[3]) * w[2];
+        P[3 * g.vs + e] = bc_sign(z, g.n[2], g.bc[4], g.bc[5]) * w[3];
+        P[4 * g.vs + e] = w[4];
+      }
+}
+
 // Writing the divergence contribution D = (G+ - G-)/dx of one cell, in two
 // halves so that a marching sweep can issue the loads of the cell's update
 // (accumulated R, stage states) before the face arithmetic and store after
@@ -532,11 +578,13 @@ __device__ __forceinline__ void emit_fetch(const StageIO& io, long long vs, long
   }
 }
 
+// (i, j, k): the cell's coordinates, for its halo images.
+// IMG: also store the primitives' halo images.
 // STORE_T: also store T~ = p/rho with the next primitives (the face-by-face
 // sweeps read it from P; the cell-centred ones form it from rho and p).
-template <int MODE, bool PN = false, bool STORE_T = true>
+template <int MODE, bool PN = false, bool STORE_T = true, bool IMG = false>
 __device__ __forceinline__ void emit_put(const StageIO& io, const Geom& g, long long c, unsigned off, const double* D,
-                                         const EmitIn& in, double dt, double& smax, int& bad) {
+                                         const EmitIn& in, double dt, double& smax, int& bad, int i, int j, int k) {
   double uo[5];
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
@@ -557,6 +605,7 @@ __device__ __forceinline__ void emit_put(const StageIO& io, const Geom& g, long 
     const double ir = cons_to_prim(g, uo, w);
 #pragma unroll
     for (int v = 0; v < (STORE_T ? 6 : 5); ++v) st_at(io.Pn + v * g.vs + c, off, w[v]);
+    if constexpr (IMG) store_images(io.Pn, g, i, j, k, w);
     if (io.what & PRIM_CFL) smax = fmax(smax, cfl_rate(g, w, ir));
     if (io.what & PRIM_HEALTH) bad |= health_bits(uo, w[4]);
   }
@@ -564,10 +613,40 @@ __device__ __forceinline__ void emit_put(const StageIO& io, const Geom& g, long 
 
 // End of a sweep that stored next-stage primitives: the block's CFL rate
 // maximum into its slot, the health bits into the control block. Every thread
-// of the block calls it.
+// of the block calls it. With io.next set the sweep ends a step: the last
+// block to publish its maximum advances t by the step just taken, forms the
+// next step's size and clears the slots, so that a run of steps needs no
+// launch between them. The slots and the block counter are touched by atomics
+// only, each block's counter increment after its maximum has returned, so the
+// last block sees every maximum without a cache write-back per block.
 __device__ __forceinline__ void finish_prims(const StageIO& io, double smax, int bad) {
-  if (io.what & PRIM_CFL) publish_rate(io.partial, blockIdx.y * gridDim.x + blockIdx.x, smax);
   if (bad) atomicOr(&io.ctl->status, bad);
+  if (!(io.what & PRIM_CFL)) return;
+  const unsigned block = blockIdx.y * gridDim.x + blockIdx.x;
+  smax = block_max(smax);
+  __shared__ int last;
+  if (threadIdx.x == 0) {
+    unsigned long long old = 0;
+    if (smax > 0.0)
+      old = atomicMax(reinterpret_cast<unsigned long long*>(io.partial) + (block & (kCflSlots - 1)),
+                      (unsigned long long)__double_as_longlong(smax));
+    if (io.next) {
+      asm volatile("s_waitcnt vmcnt(0)" : "+v"(old) : : "memory");
+      last = atomicAdd(&io.ctl->done, 1u) == gridDim.x * gridDim.y - 1;
+    }
+  }
+  if (!io.next) return;
+  __syncthreads();
+  if (!last) return;
+  double m = 0.0;
+  for (int i = threadIdx.x; i < kCflSlots; i += blockDim.x)
+    m = fmax(m, __longlong_as_double((long long)atomicExch(reinterpret_cast<unsigned long long*>(io.partial) + i, 0ull)));
+  m = block_max(m);
+  if (threadIdx.x == 0) {
+    if (io.t != nullptr) *io.t = *io.t + io.ctl->dt;
+    io.ctl->dt = step_size(io.cfl, m, 0.0, io.t, io.t_end);
+    atomicExch(&io.ctl->done, 0u);
+  }
 }
 
 // Value of x in the lane below (lane - 1) across the whole wavefront, by one
@@ -633,7 +712,7 @@ __device__ __forceinline__ void sweep_x_body_face(const double* __restrict__ P, 
   double smax = 0.0;
   int bad = 0;
   if (first < total) {  // uniform per wavefront
-    const double dt = mode_rk(MODE) ? *io.dtp : 0.0;
+    const double dt = mode_rk(MODE) ? stage_dt(io) : 0.0;
     const int gs = first - (kXCtx + 1) + lane;
     const bool inrange = gs >= 0 && gs < total;
     int f = 0, j = 0, k = 0;
@@ -678,7 +757,7 @@ __device__ __forceinline__ void sweep_x_body_face(const double* __restrict__ P, 
       const long long ce = cell_at(g, f - 1, j, k);
       EmitIn ein;
       emit_fetch<MODE>(io, g.vs, ce, 0, ein);
-      emit_put<MODE, PN>(io, g, ce, 0, D, ein, dt, smax, bad);
+      emit_put<MODE, PN>(io, g, ce, 0, D, ein, dt, smax, bad, f - 1, j, k);
     }
   }
   if (PN) finish_prims(io, smax, bad);
@@ -688,7 +767,7 @@ __device__ __forceinline__ void sweep_x_body_face(const double* __restrict__ P, 
 // both faces of cell f (window cells f-2 .. f+2, one smoothness evaluation
 // for the two faces) and takes the left state of face f from the lane below,
 // which reconstructed cell f-1.
-template <int MODE, bool PN, int SCH, int PHYS>
+template <int MODE, bool PN, int SCH, int PHYS, bool IMG>
 __device__ __forceinline__ void sweep_x_body_pair(const double* __restrict__ P, const StageIO& io, const Geom& g,
                                                   int bx) {
   const int lane = threadIdx.x & 63;
@@ -699,7 +778,7 @@ __device__ __forceinline__ void sweep_x_body_pair(const double* __restrict__ P, 
   double smax = 0.0;
   int bad = 0;
   if (first < total) {  // uniform per wavefront
-    const double dt = mode_rk(MODE) ? *io.dtp : 0.0;
+    const double dt = mode_rk(MODE) ? stage_dt(io) : 0.0;
     const int gs = first - (kXCtx + 1) + lane;
     const bool inrange = gs >= 0 && gs < total;
     int f = 0, j = 0, k = 0;
@@ -762,27 +841,27 @@ __device__ __forceinline__ void sweep_x_body_pair(const double* __restrict__ P, 
       const long long ce = cell_at(g, f - 1, j, k);
       EmitIn ein;
       emit_fetch<MODE>(io, g.vs, ce, 0, ein);
-      emit_put<MODE, PN, false>(io, g, ce, 0, D, ein, dt, smax, bad);
+      emit_put<MODE, PN, false, IMG>(io, g, ce, 0, D, ein, dt, smax, bad, f - 1, j, k);
     }
   }
   if (PN) finish_prims(io, smax, bad);
   else if (bad && io.ctl) atomicOr(&io.ctl->status, bad);
 }
 
-template <int MODE, bool PN = false, int SCH = SCH_JS, int PHYS = PHYS_ANY>
+template <int MODE, bool PN = false, int SCH = SCH_JS, int PHYS = PHYS_ANY, bool IMG = false>
 __device__ __forceinline__ void sweep_x_body(const double* __restrict__ P, const StageIO& io, const Geom& g,
                                              int bx) {
   if constexpr (SCH == SCH_ROE || SCH == SCH_Z) sweep_x_body_face<MODE, PN, SCH, PHYS>(P, io, g, bx);
-  else sweep_x_body_pair<MODE, PN, SCH, PHYS>(P, io, g, bx);
+  else sweep_x_body_pair<MODE, PN, SCH, PHYS, IMG>(P, io, g, bx);
 }
 
 // Blocks are taken in XCD-major order, so that the neighbouring rows and
 // planes whose velocities the derivative stencils read are being processed in
 // the same XCD and stay in its L2.
-template <int MODE, bool PN, int SCH, int PHYS>
+template <int MODE, bool PN, int SCH, int PHYS, bool IMG>
 __global__ void __launch_bounds__(kBlock) k_sweep_x(const double* __restrict__ P, StageIO io, Geom g) {
   if (step_disabled(io.dtp)) return;
-  sweep_x_body<MODE, PN, SCH, PHYS>(P, io, g, xcd_major_block(blockIdx.x, gridDim.x));
+  sweep_x_body<MODE, PN, SCH, PHYS, IMG>(P, io, g, xcd_major_block(blockIdx.x, gridDim.x));
 }
 
 // Blocks of an x sweep.
@@ -835,7 +914,7 @@ __device__ __forceinline__ void sweep_march_body_face(const double* __restrict__
     }
   }
   double Gm[5];
-  const double dt = mode_rk(MODE) ? *io.dtp : 0.0;
+  const double dt = mode_rk(MODE) ? stage_dt(io) : 0.0;
   for (int f = s0 - 1; f < s1; ++f) {
     // issue the loads of the cell entering the window at the next face, and
     // those of this face's cell update, before this face's arithmetic, so
@@ -867,7 +946,7 @@ __device__ __forceinline__ void sweep_march_body_face(const double* __restrict__
       double D[5];
 #pragma unroll
       for (int v = 0; v < 5; ++v) D[v] = (G[v] - Gm[v]) * g.idx[AX];
-      emit_put<MODE, PN>(io, g, c + 2 * st, 0, D, ein, dt, smax, bad);
+      emit_put<MODE, PN>(io, g, c + 2 * st, 0, D, ein, dt, smax, bad, i, AX == 1 ? f : o, AX == 1 ? o : f);
     }
 #pragma unroll
     for (int v = 0; v < 5; ++v) Gm[v] = G[v];
@@ -989,7 +1068,7 @@ __device__ __forceinline__ void sweep_march_body_pair(const double* __restrict__
     if (heat) T[m] = div_nr(q[m][4], q[m][0]);
   }
   double Gm[5];
-  const double dt = mode_rk(MODE) ? *io.dtp : 0.0;
+  const double dt = mode_rk(MODE) ? stage_dt(io) : 0.0;
   for (int f = s0 - 1; f < s1; ++f) {
     // issue the loads of the cell entering the window at the next face, and
     // of its tangential stencil, before this face's arithmetic, so that their
@@ -1028,7 +1107,7 @@ __device__ __forceinline__ void sweep_march_body_pair(const double* __restrict__
       for (int v = 0; v < 5; ++v) D[v] = (G[v] - Gm[v]) * g.idx[AX];
       EmitIn ein;
       emit_fetch<MODE>(io, g.vs, c + st, off, ein);  // window cell 1 is cell f
-      emit_put<MODE, PN, false>(io, g, c + st, off, D, ein, dt, smax, bad);
+      emit_put<MODE, PN, false>(io, g, c + st, off, D, ein, dt, smax, bad, i, AX == 1 ? f : o, AX == 1 ? o : f);
     }
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
@@ -1095,7 +1174,7 @@ k_sweep_march(const double* __restrict__ P, StageIO io, Geom g) {
 // at 2.6 TB/s, waited on latency.
 constexpr int kMxCtx = 3, kMxNew = 64 - 2 * kMxCtx;
 
-template <int AX, int MODE, bool PN, int SCH, int PHYS>
+template <int AX, int MODE, bool PN, int SCH, int PHYS, bool IMG = false>
 __device__ __forceinline__ void sweep_mx_body(const double* __restrict__ P, const StageIO& io, const Geom& g,
                                               int block) {
   constexpr int OT = 3 - AX;  // the transverse axis of the rows
@@ -1188,7 +1267,7 @@ __device__ __forceinline__ void sweep_mx_body(const double* __restrict__ P, cons
       if (heat) T[m] = div_nr(q[m][4], q[m][0]);
     }
     double Gm[5], Dx[5];  // flux of face f-1/2 and x divergence of row f
-    const double dt = mode_rk(MODE) ? *io.dtp : 0.0;
+    const double dt = mode_rk(MODE) ? stage_dt(io) : 0.0;
     for (int f = s0 - 1; f < s1; ++f) {
       const long long c = c1 + uniform(f - (s0 - 1)) * st;  // row f-1
       // the entering row (after the segment's last face a row already held,
@@ -1226,7 +1305,7 @@ __device__ __forceinline__ void sweep_mx_body(const double* __restrict__ P, cons
         for (int v = 0; v < 5; ++v) D[v] = fma(G[v] - Gm[v], g.idx[AX], Dx[v]);
         EmitIn ein;
         emit_fetch<MODE>(io, g.vs, c + st, off, ein);
-        emit_put<MODE, PN, false>(io, g, c + st, off, D, ein, dt, smax, bad);
+        emit_put<MODE, PN, false, IMG>(io, g, c + st, off, D, ein, dt, smax, bad, x, AX == 1 ? f : o, AX == 1 ? o : f);
       }
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
@@ -1301,11 +1380,11 @@ __device__ __forceinline__ void sweep_mx_body(const double* __restrict__ P, cons
   else if (bad && io.ctl) atomicOr(&io.ctl->status, bad);
 }
 
-template <int AX, int MODE, bool PN, int SCH, int PHYS>
+template <int AX, int MODE, bool PN, int SCH, int PHYS, bool IMG>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
 k_sweep_mx(const double* __restrict__ P, StageIO io, Geom g) {
   if (step_disabled(io.dtp)) return;
-  sweep_mx_body<AX, MODE, PN, SCH, PHYS>(P, io, g, xcd_major_block(blockIdx.x, gridDim.x));
+  sweep_mx_body<AX, MODE, PN, SCH, PHYS, IMG>(P, io, g, xcd_major_block(blockIdx.x, gridDim.x));
 }
 
 // Blocks of a march with x faces along AX.
