@@ -70,7 +70,6 @@ struct cfd_solver {
   double* P = nullptr;    // 6 x padded (= Pb[0])
   double* Pb[3] = {nullptr, nullptr, nullptr};  // primitives of the stage inputs of a step
   double* Racc = nullptr; // 5 x padded
-  double* Racc2 = nullptr; // 5 x padded: the second march's accumulator (grids with three active axes)
   double* A1 = nullptr;   // adjoint scratch (allocated on the first adjoint call)
   double* A2 = nullptr;
   double* A3 = nullptr;
@@ -228,7 +227,7 @@ static int best_segment(int n, double groups, double face, double seed, int res)
 // own (batch_segment): it fills the chip with many grids.
 static void choose_segment(Geom& g) {
   const bool euler = g.inviscid && !g.viscous && !g.heat;
-  const int res = g.roe ? 1 : (euler ? 4 : 2);
+  const int res = euler && !g.roe ? 4 : 2;
   int seg = 0;
   for (int ax = 1; ax < 3; ++ax) {
     if (!g.act[ax]) continue;
@@ -278,49 +277,39 @@ static void with_scheme(const Geom& g, F&& f) {
   else with_phys<SCH_JS>(g, f);
 }
 
-// WENO5-Z and the Roe splitting reconstruct face by face; the others per cell.
-static bool face_by_face(const Geom& g) { return g.roe || g.wenoz; }
-
-// Face-by-face schemes on three axes: the y and z marches write R and R2, the
-// x sweep reads both (MODE_ACC2_RK).
-static bool split_accumulator(const Geom& g) { return face_by_face(g) && g.act[0] && g.act[1] && g.act[2]; }
+// The Roe splitting projects face by face; the others reconstruct per cell.
+static bool face_by_face(const Geom& g) { return g.roe; }
 
 // The sweeps of a stage, in order. Cell-centred schemes with x and another
 // axis active: on three axes the z march, then the y march with the x faces;
 // on two axes the march along the other axis with the x faces alone. With one
-// active axis its sweep alone; without x (and for the face-by-face schemes)
-// one sweep per active axis in the order y, z, x. The last sweep applies the
-// stage update and stores the next primitives.
+// active axis its sweep alone; without x (and for the Roe splitting) one sweep
+// per active axis in the order y, z, x. The last sweep applies the stage update
+// and stores the next primitives.
 struct Sweep {
   enum Kind { X, MARCH, MARCH_X } kind;
   int ax;    // marching axis (0: x sweep)
   int mode;
-  bool r2;   // writes the second accumulator
 };
 
 static int plan_sweeps(const Geom& g, bool rk, Sweep* out) {
   int act = 0, n = 0;
   for (int d = 0; d < 3; ++d) act += g.act[d];
   if (!face_by_face(g) && g.act[0] && act > 1) {
-    if (act == 3) out[n++] = {Sweep::MARCH, 2, rk ? MODE_STAGE : MODE_WRITE, false};
+    if (act == 3) out[n++] = {Sweep::MARCH, 2, rk ? MODE_STAGE : MODE_WRITE};
     out[n++] = {Sweep::MARCH_X, g.act[1] ? 1 : 2,
-                act == 3 ? (rk ? MODE_ADD_RK : MODE_ACC) : (rk ? MODE_WRITE_RK : MODE_WRITE), false};
+                act == 3 ? (rk ? MODE_ADD_RK : MODE_ACC) : (rk ? MODE_WRITE_RK : MODE_WRITE)};
     return n;
   }
   for (int d : kSweepAxes) {
     if (!g.act[d]) continue;
     const bool first = n == 0, last = n == act - 1;
     int mode;
-    bool r2 = false;
-    if (rk && last) {
-      mode = first ? MODE_WRITE_RK : (act == 3 ? MODE_ACC2_RK : MODE_ACC_RK);
-    } else if (rk && act == 3) {
-      mode = MODE_WRITE;  // the marches before the x sweep each write their own accumulator
-      r2 = !first;
-    } else {
-      mode = first ? MODE_WRITE : MODE_ACC;
-    }
-    out[n++] = {d == 0 ? Sweep::X : Sweep::MARCH, d, mode, r2};
+    if (!rk) mode = first ? MODE_WRITE : MODE_ACC;
+    else if (!g.act[0]) mode = !last ? MODE_WRITE : (first ? MODE_WRITE_RK : MODE_ACC_RK);
+    else if (last) mode = first ? MODE_WRITE_RK : MODE_ADD_RK;
+    else mode = first ? MODE_STAGE : MODE_ADD_STAGE;
+    out[n++] = {d == 0 ? Sweep::X : Sweep::MARCH, d, mode};
   }
   return n;
 }
@@ -330,7 +319,7 @@ static void launch_march(int mode, const double* P, const StageIO& io, const Geo
   int gx, gy;
   sweep_march_blocks<AX>(g, gx, gy);
   const dim3 grid(gx, gy), blk(kBlock);
-  constexpr bool face = SCH == SCH_ROE || SCH == SCH_Z;
+  constexpr bool face = SCH == SCH_ROE;
   // sweeps that a cell-centred scheme runs only on grids without x take the
   // run-time flux terms
   constexpr int PA = face ? PHYS : PHYS_ANY;
@@ -339,16 +328,20 @@ static void launch_march(int mode, const double* P, const StageIO& io, const Geo
     case MODE_ACC: hipLaunchKernelGGL((k_sweep_march<AX, MODE_ACC, false, SCH, PA>), grid, blk, 0, st, P, io, g); break;
     case MODE_ACC_RK: hipLaunchKernelGGL((k_sweep_march<AX, MODE_ACC_RK, true, SCH, PA>), grid, blk, 0, st, P, io, g); break;
     case MODE_WRITE_RK: hipLaunchKernelGGL((k_sweep_march<AX, MODE_WRITE_RK, true, SCH, PA>), grid, blk, 0, st, P, io, g); break;
-    default:
-      if constexpr (!face && AX == 2)
+    case MODE_STAGE:
+      if constexpr (face || AX == 2)
         hipLaunchKernelGGL((k_sweep_march<AX, MODE_STAGE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g);
+      break;
+    default:
+      if constexpr (face && AX == 2)
+        hipLaunchKernelGGL((k_sweep_march<AX, MODE_ADD_STAGE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g);
   }
 }
 
 template <int SCH, int PHYS>
 static void launch_x(int mode, bool img, const double* P, const StageIO& io, const Geom& g, hipStream_t st) {
   const dim3 grid((unsigned)sweep_x_blocks(g)), blk(kBlock);
-  constexpr bool face = SCH == SCH_ROE || SCH == SCH_Z;
+  constexpr bool face = SCH == SCH_ROE;
   if (mode == MODE_WRITE) {
     hipLaunchKernelGGL((k_sweep_x<MODE_WRITE, false, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
   } else if (mode == MODE_WRITE_RK) {
@@ -356,22 +349,21 @@ static void launch_x(int mode, bool img, const double* P, const StageIO& io, con
     else hipLaunchKernelGGL((k_sweep_x<MODE_WRITE_RK, true, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
   } else if constexpr (face) {
     if (mode == MODE_ACC) hipLaunchKernelGGL((k_sweep_x<MODE_ACC, false, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
-    else if (mode == MODE_ACC_RK) hipLaunchKernelGGL((k_sweep_x<MODE_ACC_RK, true, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
-    else hipLaunchKernelGGL((k_sweep_x<MODE_ACC2_RK, true, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
+    else hipLaunchKernelGGL((k_sweep_x<MODE_ADD_RK, true, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
   }
 }
 
 template <int AX, int MODE, int SCH, int PHYS>
 static void launch_mx_mode(bool img, const double* P, const StageIO& io, const Geom& g, hipStream_t st) {
   const dim3 grid((unsigned)sweep_mx_blocks(g, AX)), blk(kBlock);
-  constexpr bool rk = mode_rk(MODE);
+  constexpr bool rk = mode_last(MODE);
   if (rk && img) hipLaunchKernelGGL((k_sweep_mx<AX, MODE, rk, SCH, PHYS, rk>), grid, blk, 0, st, P, io, g);
   else hipLaunchKernelGGL((k_sweep_mx<AX, MODE, rk, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
 }
 
 template <int SCH, int PHYS>
 static void launch_mx(int ax, int mode, bool img, const double* P, const StageIO& io, const Geom& g, hipStream_t st) {
-  if constexpr (SCH != SCH_ROE && SCH != SCH_Z) {
+  if constexpr (SCH != SCH_ROE) {
     if (ax == 2) {
       if (mode == MODE_WRITE) launch_mx_mode<2, MODE_WRITE, SCH, PHYS>(img, P, io, g, st);
       else launch_mx_mode<2, MODE_WRITE_RK, SCH, PHYS>(img, P, io, g, st);
@@ -386,8 +378,7 @@ static void launch_mx(int ax, int mode, bool img, const double* P, const StageIO
   }
 }
 
-static void launch_sweep(const Geom& g, const Sweep& sw, bool img, const double* P, StageIO io, hipStream_t st) {
-  if (sw.r2) io.R = const_cast<double*>(io.R2);
+static void launch_sweep(const Geom& g, const Sweep& sw, bool img, const double* P, const StageIO& io, hipStream_t st) {
   with_scheme(g, [&](auto sch, auto phys) {
     constexpr int SCH = decltype(sch)::value, PHYS = decltype(phys)::value;
     if (sw.kind == Sweep::MARCH_X) launch_mx<SCH, PHYS>(sw.ax, sw.mode, img, P, io, g, st);
@@ -481,7 +472,6 @@ static cfd_status enqueue_step_prologue(cfd_solver* s, const double* U, double f
 static StageIO stage_io(cfd_solver* s, double fixed_dt) {
   StageIO io{};
   io.R = s->Racc;
-  io.R2 = s->Racc2;
   io.dtp = fixed_dt > 0.0 ? nullptr : &s->ctl->dt;
   io.dt = fixed_dt;
   io.partial = s->partial;
@@ -825,7 +815,6 @@ cfd_status cfd_create(const cfd_config* cfg, cfd_solver** out) {
   const size_t st = sizeof(double) * 5 * (size_t)s->ncell;
   bool ok = hipMalloc(&s->U1, st) == hipSuccess && hipMalloc(&s->U2, st) == hipSuccess &&
             hipMalloc(&s->Racc, st) == hipSuccess &&
-            (!split_accumulator(s->g) || hipMalloc(&s->Racc2, st) == hipSuccess) &&
             hipMalloc(&s->Pb[0], sizeof(double) * 6 * (size_t)s->ncell) == hipSuccess &&
             hipMalloc(&s->Pb[1], sizeof(double) * 6 * (size_t)s->ncell) == hipSuccess &&
             hipMalloc(&s->Pb[2], sizeof(double) * 6 * (size_t)s->ncell) == hipSuccess &&
@@ -865,7 +854,7 @@ void cfd_destroy(cfd_solver* s) {
   if (s->side) (void)hipStreamDestroy(s->side);
   if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);
   if (s->ev_join) (void)hipEventDestroy(s->ev_join);
-  double* bufs[] = {s->U1, s->U2,   s->Pb[0], s->Pb[1], s->Pb[2], s->Racc,    s->Racc2, s->A1,
+  double* bufs[] = {s->U1, s->U2,   s->Pb[0], s->Pb[1], s->Pb[2], s->Racc,    s->A1,
                     s->A2, s->A3,   s->Wbar,  s->Dbar,  s->Wbar2, s->Dbar2, s->partial, s->nna, s->nntape};
   for (double* b : bufs)
     if (b) (void)hipFree(b);
@@ -1141,7 +1130,7 @@ cfd_status cfd_rk3_step_prims(cfd_solver* s, double* U, double dt, double* P_out
   const size_t ps = kPrimComps * (size_t)s->ncell;
   double* const Pst[3] = {P_out, P_out + ps, P_out + 2 * ps};
   hipLaunchKernelGGL(k_prim, plane_grid(s->g), dim3(kBlock), 0, st, (const double*)U, Pst[0], s->g, s->ctl,
-                     PRIM_HEALTH, (const double*)nullptr, s->partial);
+                     PRIM_HEALTH | PRIM_T, (const double*)nullptr, s->partial);
   CFD_LAUNCHED();
   cfd_status rc = enqueue_step(s, U, dt, false, 0.0, nullptr, st, nullptr, nullptr, Pst);
   if (rc) return rc;
@@ -1181,9 +1170,9 @@ static __device__ __align__(256) double scratch[kNoAllocDoubles];
 static std::mutex g_noalloc_mu;
 static double* g_noalloc_ptr[kNoAllocMaxDevices] = {};
 
-// Padded cells of cfg that fit the scratch array: 38 doubles per padded cell
-// (U1, U2 and the two accumulators: 5 each; three primitive buffers: 6 each)
-// after the head.
+// Padded cells of cfg that fit the scratch array, at 38 doubles per padded cell
+// after the head (a step uses 33: U1, U2 and the accumulator, 5 each, and three
+// primitive buffers, 6 each).
 static constexpr long long noalloc_max_cells() { return (kNoAllocDoubles - kNoAllocHead) / 38; }
 static_assert(noalloc_max_cells() == CFD_NOALLOC_MAX_PADDED_CELLS, "header limit out of date");
 
@@ -1232,8 +1221,7 @@ cfd_status cfd_rk3_step_noalloc(const cfd_config* cfg, double* U, double dt, dou
   s.U1 = b;
   s.U2 = b + 5 * nc;
   s.Racc = b + 10 * nc;
-  s.Racc2 = b + 15 * nc;
-  for (int k = 0; k < 3; ++k) s.Pb[k] = b + (20 + 6 * k) * nc;
+  for (int k = 0; k < 3; ++k) s.Pb[k] = b + (15 + 6 * k) * nc;
   s.P = s.Pb[0];
   hipStream_t st = (hipStream_t)stream;
   // the control block (step size, health bits) starts clear on every call; the

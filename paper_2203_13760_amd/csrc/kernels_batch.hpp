@@ -39,7 +39,6 @@ struct GridWork {
   double* U2;
   double* Pb[3];   // primitives (6 x padded) of the stage inputs: stage s reads Pb[s-1]
   double* R;       // 5 x padded
-  double* R2;      // 5 x padded: the second march's accumulator (grids with three active axes)
   double* partial; // CFL rate slots
   DevCtl* ctl;
   int npart;
@@ -110,7 +109,6 @@ __device__ __forceinline__ void batch_item(const BatchTable* __restrict__ tab, i
     const Geom& g = w.g;
     StageIO io{};
     io.R = w.R;
-    io.R2 = w.R2;
     io.Un = w.U;
     io.dtp = &w.ctl->dt;
     io.Uk = STAGE == 1 ? w.U : (STAGE == 2 ? w.U1 : w.U2);

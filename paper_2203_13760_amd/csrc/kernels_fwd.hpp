@@ -31,21 +31,21 @@ constexpr int kBlock = 256;
 constexpr int kGradComps = 9;  // adjoint of d u_a / d x_b accumulated at component a*3+b
 
 // What a sweep does with the divergence D of its axis: MODE_WRITE stores
-// R = -D, MODE_ACC R -= D; the RK modes apply the stage update with
-// R = -D (MODE_WRITE_RK), R - D (MODE_ACC_RK) or R + R2 - D (MODE_ACC2_RK:
-// the two marches before it each wrote their own accumulator, which spares
-// the second one a read-modify-write of R).
-// MODE_STAGE / MODE_ADD_RK split the update of a stage between two sweeps:
-// the first stores V = a Un + b (Uk - dt D1) in R, the second the new state
-// V - b dt D2.
+// R = -D, MODE_ACC R -= D; the RK modes apply the stage update with R = -D
+// (MODE_WRITE_RK) or R - D (MODE_ACC_RK). MODE_STAGE, MODE_ADD_STAGE and
+// MODE_ADD_RK split the update of a stage between sweeps: the first stores
+// V = a Un + b (Uk - dt D) in R, one in between V -= b dt D, and the last the
+// new state V - b dt D, so that the last one, which also writes the next
+// primitives, reads one array instead of three or four.
 enum SweepMode {
-  MODE_WRITE = 0, MODE_ACC = 1, MODE_ACC_RK = 2, MODE_WRITE_RK = 3, MODE_ACC2_RK = 4, MODE_STAGE = 5, MODE_ADD_RK = 6
+  MODE_WRITE = 0, MODE_ACC = 1, MODE_ACC_RK = 2, MODE_WRITE_RK = 3, MODE_STAGE = 4, MODE_ADD_STAGE = 5, MODE_ADD_RK = 6
 };
 __host__ __device__ constexpr bool mode_rk(int m) { return m >= MODE_ACC_RK; }
+// modes that store a new state (and its primitives)
+__host__ __device__ constexpr bool mode_last(int m) { return m == MODE_ACC_RK || m == MODE_WRITE_RK || m == MODE_ADD_RK; }
 
 struct StageIO {
   double* R;         // right-hand-side accumulator (padded layout)
-  const double* R2;  // second accumulator (MODE_ACC2_RK)
   const double* Un;  // state at the start of the step
   const double* Uk;  // stage input state
   double* Uout;      // stage output state (may alias Un in the last stage)
@@ -115,7 +115,7 @@ __host__ __device__ __forceinline__ int plane_blocks_x(const Geom& g) {
 }
 
 // ----------------------------------------------------------------------------
-// Halo refresh of the primitives P (6 components) after a sweep stored the
+// Halo refresh of the primitives P after a sweep stored the
 // interior ones, one thread per halo cell; skipped with the step. Halo cells
 // are numbered slab by slab: the z halo planes (whole padded planes), then
 // for interior z the y halo rows (whole padded rows), then for interior z and
@@ -171,12 +171,8 @@ __device__ __forceinline__ void prim_halo_body(double* P, const Geom& g, long lo
   const long long c = cell_at(g, i, j, k), s = cell_at(g, si, sj, sk);
   const double sg[3] = {bc_sign(i, g.n[0], g.bc[0], g.bc[1]), bc_sign(j, g.n[1], g.bc[2], g.bc[3]),
                         bc_sign(k, g.n[2], g.bc[4], g.bc[5])};
-  // T~ = p/rho (slot 5) only for the face-by-face schemes, which read it from
-  // P; the cell-centred ones form it from the window and do not store it
-  const bool with_t = g.roe || g.wenoz;
 #pragma unroll
-  for (int v = 0; v < 6; ++v)
-    if (v < 5 || with_t) P[v * g.vs + c] = (v >= 1 && v <= 3 ? sg[v - 1] : 1.0) * P[v * g.vs + s];
+  for (int v = 0; v < 5; ++v) P[v * g.vs + c] = (v >= 1 && v <= 3 ? sg[v - 1] : 1.0) * P[v * g.vs + s];
 }
 
 __global__ void __launch_bounds__(kBlock) k_prim_halo(double* P, Geom g, const double* dtp) {
@@ -305,7 +301,9 @@ __device__ __forceinline__ int health_bits(const double* q, double p) {
 // Primitive variables on the padded grid, gathered through the boundary map.
 // Over interior cells, `what` bit 0 adds the CFL rate (block maxima written
 // to partial[], one per block) and bit 1 the health bits.
-constexpr int PRIM_CFL = 1, PRIM_HEALTH = 2;
+// Bit 2 also stores T~ = p/rho (component 5), which no kernel reads: the
+// sweeps form it from their windows.
+constexpr int PRIM_CFL = 1, PRIM_HEALTH = 2, PRIM_T = 4;
 
 __device__ __forceinline__ void prim_body(const double* __restrict__ U, double* __restrict__ P, const Geom& g,
                                           DevCtl* ctl, int what, double* __restrict__ partial, const PlaneIdx& q,
@@ -325,7 +323,8 @@ __device__ __forceinline__ void prim_body(const double* __restrict__ U, double* 
     u[3] *= bc_sign(q.k, g.n[2], g.bc[4], g.bc[5]);
     const double ir = cons_to_prim(g, u, w);
 #pragma unroll
-    for (int v = 0; v < 6; ++v) P[v * g.vs + c] = w[v];
+    for (int v = 0; v < 5; ++v) P[v * g.vs + c] = w[v];
+    if (what & PRIM_T) P[5 * g.vs + c] = w[5];
     if (what && s == c) {
       if (what & PRIM_CFL) smax = cfl_rate(g, w, ir);
       if (what & PRIM_HEALTH) {
@@ -569,9 +568,9 @@ __device__ __forceinline__ void emit_fetch(const StageIO& io, long long vs, long
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     const long long e = v * vs + c;
-    if (MODE == MODE_ACC || MODE == MODE_ACC_RK || MODE == MODE_ADD_RK) in.r[v] = ld_at(io.R + e, off);
-    if (MODE == MODE_ACC2_RK) in.r[v] = ld_at(io.R + e, off) + ld_at(io.R2 + e, off);
-    if (mode_rk(MODE) && MODE != MODE_ADD_RK) {
+    constexpr bool add = MODE == MODE_ADD_RK || MODE == MODE_ADD_STAGE;
+    if (MODE == MODE_ACC || MODE == MODE_ACC_RK || add) in.r[v] = ld_at(io.R + e, off);
+    if (mode_rk(MODE) && !add) {
       in.un[v] = with_un ? ld_at(io.Un + e, off) : 0.0;
       in.uk[v] = ld_at(io.Uk + e, off);
     }
@@ -580,9 +579,7 @@ __device__ __forceinline__ void emit_fetch(const StageIO& io, long long vs, long
 
 // (i, j, k): the cell's coordinates, for its halo images.
 // IMG: also store the primitives' halo images.
-// STORE_T: also store T~ = p/rho with the next primitives (the face-by-face
-// sweeps read it from P; the cell-centred ones form it from rho and p).
-template <int MODE, bool PN = false, bool STORE_T = true, bool IMG = false>
+template <int MODE, bool PN = false, bool IMG = false>
 __device__ __forceinline__ void emit_put(const StageIO& io, const Geom& g, long long c, unsigned off, const double* D,
                                          const EmitIn& in, double dt, double& smax, int& bad, int i, int j, int k) {
   double uo[5];
@@ -591,9 +588,9 @@ __device__ __forceinline__ void emit_put(const StageIO& io, const Geom& g, long 
     const long long e = v * g.vs + c;
     if (MODE == MODE_WRITE || MODE == MODE_ACC) {
       st_at(io.R + e, off, MODE == MODE_WRITE ? -D[v] : in.r[v] - D[v]);
-    } else if (MODE == MODE_ADD_RK) {
+    } else if (MODE == MODE_ADD_RK || MODE == MODE_ADD_STAGE) {
       uo[v] = fma(-(io.b * dt), D[v], in.r[v]);
-      st_at(io.Uout + e, off, uo[v]);
+      st_at((MODE == MODE_ADD_STAGE ? io.R : io.Uout) + e, off, uo[v]);
     } else {
       const double r = MODE == MODE_WRITE_RK || MODE == MODE_STAGE ? -D[v] : in.r[v] - D[v];
       uo[v] = io.a * in.un[v] + io.b * (in.uk[v] + dt * r);
@@ -604,7 +601,7 @@ __device__ __forceinline__ void emit_put(const StageIO& io, const Geom& g, long 
     double w[6];
     const double ir = cons_to_prim(g, uo, w);
 #pragma unroll
-    for (int v = 0; v < (STORE_T ? 6 : 5); ++v) st_at(io.Pn + v * g.vs + c, off, w[v]);
+    for (int v = 0; v < 5; ++v) st_at(io.Pn + v * g.vs + c, off, w[v]);
     if constexpr (IMG) store_images(io.Pn, g, i, j, k, w);
     if (io.what & PRIM_CFL) smax = fmax(smax, cfl_rate(g, w, ir));
     if (io.what & PRIM_HEALTH) bad |= health_bits(uo, w[4]);
@@ -700,9 +697,9 @@ __device__ __forceinline__ void x_row(const Geom& g, int row, int& j, int& k) {
   j = band * kXBand + (r - k * h);
 }
 
-template <int MODE, bool PN, int SCH, int PHYS>
+template <int MODE, bool PN, int PHYS>
 __device__ __forceinline__ void sweep_x_body_face(const double* __restrict__ P, const StageIO& io, const Geom& g,
-                                                  int bx) {
+                                              int bx) {
   // slot numbering fits in 32 bits (checked when the solver is created)
   const int lane = threadIdx.x & 63;
   const int wave = (bx * kBlock + (int)threadIdx.x) >> 6;
@@ -728,25 +725,36 @@ __device__ __forceinline__ void sweep_x_body_face(const double* __restrict__ P, 
     // are in flight together.
     const int fl = f < 0 ? 0 : f;
     const long long c0 = cell_at(g, fl - 3, j, k);
-    FaceWindow w;
+    double q[6][5];
 #pragma unroll
-    for (int m = 0; m < 6; ++m) load_prims(P, g.vs, c0 + m, w.q[m]);
-#pragma unroll
-    for (int m = 0; m < 4; ++m) w.T[m] = P[5 * g.vs + c0 + 1 + m];  // unused without heat flux
-    double d[4] = {0.0, 0.0, 0.0, 0.0};
-    if (with_viscous<PHYS>(g)) tangential_at_flat<0>(g, P, cell_at(g, f + 1, j, k), d);
+    for (int m = 0; m < 6; ++m) load_prims(P, g.vs, c0 + m, q[m]);
+    double d[4] = {0.0, 0.0, 0.0, 0.0};  // tangential sums and T~ of cell f+1
+    const long long c1 = cell_at(g, f + 1, j, k);
+    if (with_viscous<PHYS>(g)) {
+      double x[4][4];
+      tangential_load<0>(g, P, c1, x);
+      __builtin_amdgcn_sched_barrier(0);
+      tangential_combine3<0>(g, x, d);
+    }
+    if (with_heat<PHYS>(g)) d[3] = div_nr(P[4 * g.vs + c1], P[c1]);
     // face values of the derivatives from cells f-2..f+1 (lanes - 3 .. lane)
-    double tf[4];
+    double tf[3], T[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const double t2 = lane_shr1(d[v]);
       const double t1 = lane_shr1(t2);
       const double t0 = lane_shr1(t1);
-      tf[v] = rc4(t0, t1, t2, d[v]);
+      if (v < 3) {
+        tf[v] = rc4(t0, t1, t2, d[v]);
+      } else {
+        T[0] = t0;
+        T[1] = t1;
+        T[2] = t2;
+        T[3] = d[v];
+      }
     }
-    if constexpr (SCH == SCH_W3_NN) w.a = g.nna[c0 + 2];  // alpha of face f (left cell f-1)
     double G[5];
-    face_flux_tf<0, SCH, PHYS>(g, w, tf, G);
+    roe_face_flux<0, PHYS>(g, q, T, tf, G);
     double Gm[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) Gm[v] = lane_shr1(G[v]);
@@ -841,7 +849,7 @@ __device__ __forceinline__ void sweep_x_body_pair(const double* __restrict__ P, 
       const long long ce = cell_at(g, f - 1, j, k);
       EmitIn ein;
       emit_fetch<MODE>(io, g.vs, ce, 0, ein);
-      emit_put<MODE, PN, false, IMG>(io, g, ce, 0, D, ein, dt, smax, bad, f - 1, j, k);
+      emit_put<MODE, PN, IMG>(io, g, ce, 0, D, ein, dt, smax, bad, f - 1, j, k);
     }
   }
   if (PN) finish_prims(io, smax, bad);
@@ -851,7 +859,7 @@ __device__ __forceinline__ void sweep_x_body_pair(const double* __restrict__ P, 
 template <int MODE, bool PN = false, int SCH = SCH_JS, int PHYS = PHYS_ANY, bool IMG = false>
 __device__ __forceinline__ void sweep_x_body(const double* __restrict__ P, const StageIO& io, const Geom& g,
                                              int bx) {
-  if constexpr (SCH == SCH_ROE || SCH == SCH_Z) sweep_x_body_face<MODE, PN, SCH, PHYS>(P, io, g, bx);
+  if constexpr (SCH == SCH_ROE) sweep_x_body_face<MODE, PN, PHYS>(P, io, g, bx);
   else sweep_x_body_pair<MODE, PN, SCH, PHYS, IMG>(P, io, g, bx);
 }
 
@@ -859,7 +867,7 @@ __device__ __forceinline__ void sweep_x_body(const double* __restrict__ P, const
 // planes whose velocities the derivative stencils read are being processed in
 // the same XCD and stay in its L2.
 template <int MODE, bool PN, int SCH, int PHYS, bool IMG>
-__global__ void __launch_bounds__(kBlock) k_sweep_x(const double* __restrict__ P, StageIO io, Geom g) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) k_sweep_x(const double* __restrict__ P, StageIO io, Geom g) {
   if (step_disabled(io.dtp)) return;
   sweep_x_body<MODE, PN, SCH, PHYS, IMG>(P, io, g, xcd_major_block(blockIdx.x, gridDim.x));
 }
@@ -876,106 +884,6 @@ __host__ __device__ __forceinline__ int sweep_x_blocks(const Geom& g) {
 // first face is computed only to seed the left flux.
 constexpr int kSeg = 32;
 
-// y / z sweep body of one lane. Lanes beyond the grid (a partial last block)
-// march a valid column too but store nothing, so that every lane reaches the
-// block-wide CFL reduction of a sweep that stores next-stage primitives.
-template <int AX, int MODE, bool PN, int SCH, int PHYS>
-__device__ __forceinline__ void sweep_march_body_face(const double* __restrict__ P, const StageIO& io,
-                                                      const Geom& g, int bx, int by) {
-  constexpr int OT = AX == 1 ? 2 : 1;  // the other transverse axis
-  const int i = bx * 64 + (threadIdx.x & 63);
-  const int sl = g.seg;
-  const int nseg = (g.n[AX] + sl - 1) / sl;
-  const long long col = (long long)by * (kBlock >> 6) + (threadIdx.x >> 6);
-  const bool in = i < g.n[0] && col < (long long)g.n[OT] * nseg;
-  if (!PN && !in) return;
-  double smax = 0.0;
-  int bad = 0;
-  const long long colc = in ? col : 0;
-  const int o = (int)(colc / nseg);
-  const int seg = (int)(colc - (long long)o * nseg);
-  const int s0 = seg * sl;
-  const int s1 = min(s0 + sl, g.n[AX]);
-  const long long st = g.s[AX];
-  int q3[3];
-  q3[0] = in ? i : 0;
-  q3[OT] = o;
-  q3[AX] = s0 - 3;
-  long long c = cell_at(g, q3[0], q3[1], q3[2]);  // window cell 0 (axis index f-2 for face f+1/2)
-  const bool dis = with_viscous<PHYS>(g) || with_heat<PHYS>(g);
-  FaceWindow w;
-#pragma unroll
-  for (int m = 0; m < 6; ++m) load_prims(P, g.vs, c + m * st, w.q[m]);
-  if (dis) {
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      w.T[m] = P[5 * g.vs + c + (1 + m) * st];
-      if (with_viscous<PHYS>(g)) tangential_at<AX>(g, P, c + (1 + m) * st, w.tg[m]);
-    }
-  }
-  double Gm[5];
-  const double dt = mode_rk(MODE) ? stage_dt(io) : 0.0;
-  for (int f = s0 - 1; f < s1; ++f) {
-    // issue the loads of the cell entering the window at the next face, and
-    // those of this face's cell update, before this face's arithmetic, so
-    // their latency overlaps it
-    const bool more = f + 1 < s1;
-    EmitIn ein;
-    if (f >= s0 && in) emit_fetch<MODE>(io, g.vs, c + 2 * st, 0, ein);  // window cell 2 is cell f
-    // The entering cell's derivative stencil: in MODE_WRITE (no update loads
-    // in flight) the sixteen raw values are held across the face arithmetic
-    // and combined after it, so their latency is hidden; the other modes have
-    // no registers to spare for that and combine them at once.
-    constexpr bool kDeferTg = MODE == MODE_WRITE;
-    double nq[5], nT = 0.0, ntr[4][4], ntg[4] = {0.0, 0.0, 0.0, 0.0};
-    if (more) {
-      load_prims(P, g.vs, c + 6 * st, nq);
-      if (dis) {
-        nT = P[5 * g.vs + c + 5 * st];
-        if (with_viscous<PHYS>(g)) {
-          if (kDeferTg) tangential_load<AX>(g, P, c + 5 * st, ntr);
-          else tangential_at<AX>(g, P, c + 5 * st, ntg);
-        }
-      }
-    }
-    if (kDeferTg) __builtin_amdgcn_sched_barrier(0);
-    if constexpr (SCH == SCH_W3_NN) w.a = g.nna[AX * g.vs + c + 2 * st];  // face f+1/2, left cell f
-    double G[5];
-    face_flux<AX, SCH, PHYS>(g, w, G);
-    if (f >= s0 && in) {
-      double D[5];
-#pragma unroll
-      for (int v = 0; v < 5; ++v) D[v] = (G[v] - Gm[v]) * g.idx[AX];
-      emit_put<MODE, PN>(io, g, c + 2 * st, 0, D, ein, dt, smax, bad, i, AX == 1 ? f : o, AX == 1 ? o : f);
-    }
-#pragma unroll
-    for (int v = 0; v < 5; ++v) Gm[v] = G[v];
-    if (more) {
-      // shift the window by one cell along the axis
-#pragma unroll
-      for (int m = 0; m < 5; ++m)
-#pragma unroll
-        for (int v = 0; v < 5; ++v) w.q[m][v] = w.q[m + 1][v];
-#pragma unroll
-      for (int v = 0; v < 5; ++v) w.q[5][v] = nq[v];
-      c += st;
-      if (dis) {
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-          w.T[m] = w.T[m + 1];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) w.tg[m][v] = w.tg[m + 1][v];
-        }
-        w.T[3] = nT;
-        if (kDeferTg && with_viscous<PHYS>(g)) tangential_combine<AX>(g, ntr, ntg);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) w.tg[3][v] = ntg[v];
-      }
-    }
-  }
-  if (PN) finish_prims(io, smax, bad);
-}
-
 // The four values a central difference at cell c takes along the axis of
 // stride st, and the difference (times 12 dx).
 struct Diff4 {
@@ -989,13 +897,17 @@ struct Diff4 {
   __device__ __forceinline__ double diff() const { return fma(8.0, x[2] - x[1], x[0] - x[3]); }
 };
 
-// The same for the cell-centred schemes: the lane carries the left state of
-// the next face, reconstructed with the right state of the current face from
-// the cell between them (one smoothness evaluation for the two faces), so the
-// window holds five cells, f-1 .. f+3 for face f+1/2. The segment starts with
-// the reconstruction of cell s0-1, for the left state of its first face.
-template <int AX, int MODE, bool PN, int SCH, int PHYS>
-__device__ __forceinline__ void sweep_march_body_pair(const double* __restrict__ P, const StageIO& io,
+// y / z sweep body of one lane. Lanes beyond the grid (a partial last block)
+// march a valid column too but store nothing, so that every lane reaches the
+// block-wide CFL reduction of a sweep that stores next-stage primitives.
+// Cell-centred schemes carry the left state of the next face, reconstructed
+// with the right state of the current face from the cell between them (one
+// smoothness evaluation for the two faces), so their window holds five cells,
+// f-1 .. f+3 for face f+1/2, and the segment starts with the reconstruction of
+// cell s0-1, for the left state of its first face. The Roe splitting's face
+// takes the six cells f-2 .. f+3 (qm is cell f-2).
+template <int AX, int MODE, bool PN = false, int SCH = SCH_JS, int PHYS = PHYS_ANY>
+__device__ __forceinline__ void sweep_march_body(const double* __restrict__ P, const StageIO& io,
                                                       const Geom& g, int bx, int by) {
   constexpr int OT = AX == 1 ? 2 : 1;  // the other transverse axis
   constexpr int T1 = (AX + 1) % 3, T2 = (AX + 2) % 3;
@@ -1022,7 +934,9 @@ __device__ __forceinline__ void sweep_march_body_pair(const double* __restrict__
   const bool vis = with_viscous<PHYS>(g), heat = with_heat<PHYS>(g);
   const long long sT1 = g.act[T1] ? g.s[T1] : 0, sT2 = g.act[T2] ? g.s[T2] : 0;
   const double w1 = g.act[T1] ? g.idx[T1] * (1.0 / 12.0) : 0.0, w2 = g.act[T2] ? g.idx[T2] * (1.0 / 12.0) : 0.0;
+  constexpr bool kRoe = SCH == SCH_ROE;
   double q[5][5];   // window: cells f-1 .. f+3 for face f+1/2
+  double qm[5];     // Roe splitting: cell f-2
   double WLc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};  // left state of face f+1/2
   {
     double s[5][5];  // cells s0-3 .. s0+1
@@ -1032,7 +946,10 @@ __device__ __forceinline__ void sweep_march_body_pair(const double* __restrict__
       for (int v = 0; v < 5; ++v) s[m][v] = ld_at(P + v * g.vs + c + m * st, off);
 #pragma unroll
     for (int v = 0; v < 5; ++v) q[4][v] = ld_at(P + v * g.vs + c + 5 * st, off);
-    if (with_inviscid<PHYS>(g)) {
+    if constexpr (kRoe) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) qm[v] = s[0][v];
+    } else if (with_inviscid<PHYS>(g)) {
       double unused[5];
       recon_pair<SCH>(s, WLc, unused);
     }
@@ -1080,17 +997,18 @@ __device__ __forceinline__ void sweep_march_body_pair(const double* __restrict__
     double nq[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) nq[v] = ld_at(P + v * g.vs + ce, off);
-    if (vis) tang_load(c + 4 * st);
+    // the Roe splitting has no registers to hold the stencil across its face
+    if constexpr (!kRoe)
+      if (vis) tang_load(c + 4 * st);
     __builtin_amdgcn_sched_barrier(0);
     double alpha = 0.0;
     if constexpr (SCH == SCH_W3_NN) alpha = ld_at(g.nna + AX * g.vs + c + st, off);  // face f+1/2, left cell f
     double WR[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, qr[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    double WL[5];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) WL[v] = WLc[v];
-    if (with_inviscid<PHYS>(g)) {
-      recon_pair<SCH>(q, qr, WR);  // cell f+1: left state of face f+3/2, right state of f+1/2
-      check_face_states(g, true, WL, WR, q[1], q[2], bad);
+    if constexpr (!kRoe) {
+      if (with_inviscid<PHYS>(g)) {
+        recon_pair<SCH>(q, qr, WR);  // cell f+1: left state of face f+3/2, right state of f+1/2
+        check_face_states(g, true, WLc, WR, q[1], q[2], bad);
+      }
     }
     double tf[3] = {0.0, 0.0, 0.0};
     if (vis) {
@@ -1098,7 +1016,18 @@ __device__ __forceinline__ void sweep_march_body_pair(const double* __restrict__
       for (int v = 0; v < 3; ++v) tf[v] = rc4(tg[0][v], tg[1][v], tg[2][v], tg[3][v]);
     }
     double G[5];
-    face_flux_states<AX, SCH, PHYS>(g, WL, WR, q, T, tf, alpha, G);
+    if constexpr (kRoe) {
+      double q6[6][5];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        q6[0][v] = qm[v];
+#pragma unroll
+        for (int m = 0; m < 5; ++m) q6[1 + m][v] = q[m][v];
+      }
+      roe_face_flux<AX, PHYS>(g, q6, T, tf, G);
+    } else {
+      face_flux_states<AX, SCH, PHYS>(g, WLc, WR, q, T, tf, alpha, G);
+    }
 #pragma unroll
     for (int v = 0; v < 5; ++v) pin(G[v]);
     if (f >= s0 && in) {
@@ -1107,13 +1036,15 @@ __device__ __forceinline__ void sweep_march_body_pair(const double* __restrict__
       for (int v = 0; v < 5; ++v) D[v] = (G[v] - Gm[v]) * g.idx[AX];
       EmitIn ein;
       emit_fetch<MODE>(io, g.vs, c + st, off, ein);  // window cell 1 is cell f
-      emit_put<MODE, PN, false>(io, g, c + st, off, D, ein, dt, smax, bad, i, AX == 1 ? f : o, AX == 1 ? o : f);
+      emit_put<MODE, PN>(io, g, c + st, off, D, ein, dt, smax, bad, i, AX == 1 ? f : o, AX == 1 ? o : f);
     }
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
       Gm[v] = G[v];
       WLc[v] = qr[v];
     }
+    if constexpr (kRoe)
+      if (vis) tang_load(c + 4 * st);
     // shift the window by one cell along the axis
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
@@ -1123,6 +1054,10 @@ __device__ __forceinline__ void sweep_march_body_pair(const double* __restrict__
     }
     if (heat) T[3] = div_nr(q[4][4], q[4][0]);  // cell f+3
     if (vis) tang_sum(tg[3]);
+    if constexpr (kRoe) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) qm[v] = q[0][v];
+    }
 #pragma unroll
     for (int m = 0; m < 4; ++m)
 #pragma unroll
@@ -1134,18 +1069,8 @@ __device__ __forceinline__ void sweep_march_body_pair(const double* __restrict__
   else if (bad && io.ctl) atomicOr(&io.ctl->status, bad);
 }
 
-template <int AX, int MODE, bool PN = false, int SCH = SCH_JS, int PHYS = PHYS_ANY>
-__device__ __forceinline__ void sweep_march_body(const double* __restrict__ P, const StageIO& io,
-                                                 const Geom& g, int bx, int by) {
-  if constexpr (SCH == SCH_ROE || SCH == SCH_Z) sweep_march_body_face<AX, MODE, PN, SCH, PHYS>(P, io, g, bx, by);
-  else sweep_march_body_pair<AX, MODE, PN, SCH, PHYS>(P, io, g, bx, by);
-}
-
-// The Roe flux splitting does not fit the marching window in the register
-// budget of two wavefronts per SIMD; its marches run one wavefront per SIMD,
-// which leaves the accumulation registers to the compiler.
 template <int AX, int MODE, bool PN, int SCH, int PHYS>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SCH == SCH_ROE ? 1 : 2)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
 k_sweep_march(const double* __restrict__ P, StageIO io, Geom g) {
   if (step_disabled(io.dtp)) return;
   // XCD-major block order (see k_sweep_x): consecutive column groups, hence
@@ -1305,7 +1230,7 @@ __device__ __forceinline__ void sweep_mx_body(const double* __restrict__ P, cons
         for (int v = 0; v < 5; ++v) D[v] = fma(G[v] - Gm[v], g.idx[AX], Dx[v]);
         EmitIn ein;
         emit_fetch<MODE>(io, g.vs, c + st, off, ein);
-        emit_put<MODE, PN, false, IMG>(io, g, c + st, off, D, ein, dt, smax, bad, x, AX == 1 ? f : o, AX == 1 ? o : f);
+        emit_put<MODE, PN, IMG>(io, g, c + st, off, D, ein, dt, smax, bad, x, AX == 1 ? f : o, AX == 1 ? o : f);
       }
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
@@ -1326,6 +1251,7 @@ __device__ __forceinline__ void sweep_mx_body(const double* __restrict__ P, cons
             double r;
             const double e = lane_shl1(xq[3][v]);
             if constexpr (sch_weno3(SCH)) weno3_pair(xq[1][v], xq[2][v], xq[3][v], r, WR[v]);
+            else if constexpr (SCH == SCH_Z) weno5z_pair(xq[0][v], xq[1][v], xq[2][v], xq[3][v], e, r, WR[v]);
             else weno5_pair(xq[0][v], xq[1][v], xq[2][v], xq[3][v], e, r, WR[v]);
             WL[v] = lane_shr1(r);
             pin(WL[v]);

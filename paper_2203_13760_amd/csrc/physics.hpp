@@ -189,30 +189,6 @@ __host__ __device__ __forceinline__ double weno5(double a, double b, double c, d
   return c + div_nr(n, 6.0 * (w0 + (w1 + w2)));
 }
 
-// WENO5-Z (Borges, Carmona, Costa & Don 2008): the same candidates and
-// smoothness indicators, global indicator tau5 = |beta0 - beta2|, weights
-// alpha_k = d_k (1 + tau5 / e_k) with e_k = beta_k + 1e-40, normalised.
-// Single division as in weno5: with alpha_k = d_k (e_k + tau5) / e_k the
-// weights are proportional to d_k (e_k + tau5) prod_{j != k} e_j.
-__host__ __device__ __forceinline__ double weno5z(double a, double b, double c, double d, double e) {
-  constexpr double k13 = 13.0 / 12.0;
-  constexpr double eps = 1.0e-40;
-  const double t0 = a - 2.0 * b + c, u0 = a - 4.0 * b + 3.0 * c;
-  const double t1 = b - 2.0 * c + d, u1 = b - d;
-  const double t2 = c - 2.0 * d + e, u2 = 3.0 * c - 4.0 * d + e;
-  const double b0 = k13 * t0 * t0 + 0.25 * u0 * u0;
-  const double b1 = k13 * t1 * t1 + 0.25 * u1 * u1;
-  const double b2 = k13 * t2 * t2 + 0.25 * u2 * u2;
-  const double tau = fabs(b0 - b2);
-  const double e0 = b0 + eps, e1 = b1 + eps, e2 = b2 + eps;
-  const double w0 = 0.1 * (e0 + tau) * (e1 * e2), w1 = 0.6 * (e1 + tau) * (e0 * e2),
-               w2 = 0.3 * (e2 + tau) * (e0 * e1);
-  const double P0 = 2.0 * a - 7.0 * b + 11.0 * c;
-  const double P1 = -b + 5.0 * c + 2.0 * d;
-  const double P2 = 2.0 * c + 5.0 * d - e;
-  return (w0 * P0 + w1 * P1 + w2 * P2) / (6.0 * (w0 + w1 + w2));
-}
-
 // WENO5-JS at both faces of the centre cell c of the stencil (a, b, c, d, e) =
 // q_{i-2} .. q_{i+2}: qr at the right face i+1/2 (the left state there) and
 // ql at the left face i-1/2 (the right state there). The two reconstructions
@@ -253,6 +229,33 @@ __host__ __device__ __forceinline__ void weno5_pair(double a, double b, double c
   const double r = rcp_nr(dr * dl) * (1.0 / 6.0);
   qr = fma(nr, dl * r, c);
   ql = fma(nl, dr * r, c);
+}
+
+// WENO5-Z (Borges, Carmona, Costa & Don 2008) at both faces of the centre cell,
+// as weno5_pair: the same candidates and smoothness indicators, global
+// indicator tau5 = |beta_L - beta_R|, weights alpha_k = d_k (1 + tau5 / e_k)
+// with e_k = beta_k + 1e-40. With alpha_k = d_k (e_k + tau5) / e_k the weights
+// are proportional to d_k (e_k + tau5) prod_{j != k} e_j, of which the two
+// faces share all three products. A reciprocal per face keeps the range of
+// |beta| (up to ~1e100).
+__host__ __device__ __forceinline__ void weno5z_pair(double a, double b, double c, double d, double e, double& qr,
+                                                    double& ql) {
+  constexpr double k13 = 13.0 / 12.0;
+  constexpr double eps = 1.0e-40;
+  const double dm = c - b, dp = d - c;
+  const double Db = dm - (b - a), Dc = dp - dm, Dd = (e - d) - dp;
+  const double tL = fma(0.5, Db, dm), tC = 0.5 * (dm + dp), tR = fma(-0.5, Dd, dp);
+  const double eL = fma(tL, tL, fma(k13 * Db, Db, eps));
+  const double eC = fma(tC, tC, fma(k13 * Dc, Dc, eps));
+  const double eR = fma(tR, tR, fma(k13 * Dd, Dd, eps));
+  const double tau = fabs(eL - eR);
+  const double a0 = (eL + tau) * (eC * eR), a2 = (eR + tau) * (eL * eC), w1 = 6.0 * ((eC + tau) * (eL * eR));
+  const double w2 = 3.0 * a2, v2 = 3.0 * a0;
+  const double m3 = 3.0 * dm, p3 = 3.0 * dp;
+  const double nr = fma(a0, fma(2.0, Db, m3), fma(w1, fma(2.0, dp, dm), w2 * (p3 - Dd)));
+  const double nl = fma(a2, fma(2.0, Dd, -p3), -fma(w1, fma(2.0, dm, dp), v2 * (m3 + Db)));
+  qr = c + div_nr(nr, 6.0 * (a0 + (w1 + w2)));
+  ql = c + div_nr(nl, 6.0 * (a2 + (w1 + v2)));
 }
 
 // WENO3-JS (Jiang & Shu 1996, r = 2) value at the right face of the centre
@@ -389,13 +392,6 @@ __host__ __device__ __forceinline__ double rc4(double a, double b, double c, dou
   return (-a + 9.0 * b + 9.0 * c - d) / 16.0;
 }
 
-// Face values of the four tangential derivatives of a window (same order as
-// FaceWindow::tg), interpolated along the normal from cells 1..4.
-__host__ __device__ __forceinline__ void face_tangential(const FaceWindow& w, double* tf) {
-#pragma unroll
-  for (int k = 0; k < 4; ++k) tf[k] = rc4(w.tg[0][k], w.tg[1][k], w.tg[2][k], w.tg[3][k]);
-}
-
 // Subtracts the dissipative flux F^d (§3.4) across face i+1/2 from F: the
 // primitives q[0..3] and T~[0..3] of cells i-1 .. i+2 (velocities and T~ for
 // the fourth-order normal derivatives and the face velocities) and the face
@@ -427,28 +423,6 @@ __host__ __device__ __forceinline__ void sub_dissipative_q(const Geom& g, const 
   if (with_heat<PHYS>(g)) F[4] = fma(-g.kappa, dn(T[0], T[1], T[2], T[3]), F[4]);
 }
 
-// The same from a full window and its four tangential derivatives.
-template <int D, int PHYS = PHYS_ANY>
-__host__ __device__ __forceinline__ void sub_dissipative(const Geom& g, const FaceWindow& w, const double* tf,
-                                                         double* F) {
-  const double t3[3] = {tf[0], tf[2], tf[1] + tf[3]};
-  sub_dissipative_q<D, PHYS>(g, w.q + 1, w.T, t3, F);
-}
-
-template <int D, bool RUS, bool NN, int PHYS>
-__host__ __device__ __forceinline__ void face_flux_lr(const Geom& g, const double* WL, const double* WR,
-                                                      const FaceWindow& w, const double* tf, double* G) {
-  double F[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  if (with_inviscid<PHYS>(g)) {
-    if constexpr (NN) rusanov<D, true>(g.gamma, g.gm1i, WL, WR, F, w.a);
-    else if constexpr (RUS) rusanov<D>(g.gamma, g.gm1i, WL, WR, F);
-    else hllc<D>(g.gamma, g.gm1i, WL, WR, F);
-  }
-  sub_dissipative<D, PHYS>(g, w, tf, F);
-#pragma unroll
-  for (int v = 0; v < 5; ++v) G[v] = F[v];
-}
-
 // ---------------------------------------------------------------------------
 // Flux-splitting approach of §3.3 with the ROE setup of §5: convective flux
 // across the face between window cells 2 and 3 (primitives q[0..5] = cells
@@ -473,7 +447,7 @@ __host__ __device__ __forceinline__ void roe_flux(const Geom& g, const double (&
   constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
   const double gm1 = g.gamma - 1.0;
   const double sl = sqrt_pos(q[2][0]), sr = sqrt_pos(q[3][0]);
-  const double isum = 1.0 / (sl + sr);
+  const double isum = rcp_nr(sl + sr);
   const double al = sl * isum, ar = sr * isum;
   const double uD = al * q[2][1 + D] + ar * q[3][1 + D];
   const double u1 = al * q[2][1 + T1] + ar * q[3][1 + T1];
@@ -481,24 +455,27 @@ __host__ __device__ __forceinline__ void roe_flux(const Geom& g, const double (&
   const double kl = 0.5 * (q[2][1] * q[2][1] + q[2][2] * q[2][2] + q[2][3] * q[2][3]);
   const double kr = 0.5 * (q[3][1] * q[3][1] + q[3][2] * q[3][2] + q[3][3] * q[3][3]);
   const double hp = g.gamma * g.gm1i;  // gamma/(gamma-1): H = hp p/rho + |v|^2/2
-  const double H = al * (hp * q[2][4] / q[2][0] + kl) + ar * (hp * q[3][4] / q[3][0] + kr);
+  const double H = al * (hp * div_nr(q[2][4], q[2][0]) + kl) + ar * (hp * div_nr(q[3][4], q[3][0]) + kr);
   const double q2 = uD * uD + u1 * u1 + u2 * u2;
   const double c2 = gm1 * (H - 0.5 * q2);
   const double c = sqrt_pos(c2);
-  const double ic = 1.0 / c;
+  const double ic = rcp_nr(c);
   const double b = gm1 * ic * ic;
   const double lam[5] = {fabs(uD - c), fabs(uD), fabs(uD), fabs(uD), fabs(uD + c)};
-  // per cell: A, S and the pressure terms of the projected fluxes; the fields
-  // are then split and reconstructed one at a time (fewer live registers)
-  double A[6], S[6], pb[6], pc[6];
+  // per cell: A and the pressure term of the projected fluxes; the fields are
+  // then split and reconstructed one at a time, and S = rho (u_D - v_D) / c is
+  // formed where it is used (fewer live registers: the marches hold two
+  // wavefronts per SIMD)
+  double A[6], pb[6];
+  const double hic = 0.5 * ic;
 #pragma unroll
   for (int j = 0; j < 6; ++j) {
     const double rho = q[j][0], p = q[j][4];
     const double dD = q[j][1 + D] - uD, d1 = q[j][1 + T1] - u1, d2 = q[j][1 + T2] - u2;
-    A[j] = b * (0.5 * rho * (dD * dD + d1 * d1 + d2 * d2) + p * g.gm1i);
-    S[j] = -rho * dD * ic;
+    A[j] = 0.5 * b * fma(0.5 * rho, fma(dD, dD, fma(d1, d1, d2 * d2)), p * g.gm1i);  // A / 2
     pb[j] = 0.5 * p * b * dD;
-    pc[j] = 0.5 * p * ic;
+    pin(A[j]);
+    pin(pb[j]);
   }
   double Gf[5];
 #pragma unroll
@@ -509,14 +486,14 @@ __host__ __device__ __forceinline__ void roe_flux(const Geom& g, const double (&
       const double rho = q[j][0], vD = q[j][1 + D];
       double V, G;
       if (k == 0) {
-        V = 0.5 * (A[j] + S[j]);
-        G = vD * V + (pb[j] - pc[j]);
+        V = fma(hic * rho, uD - vD, A[j]);
+        G = fma(vD, V, fma(-hic, q[j][4], pb[j]));
       } else if (k == 1) {
-        V = rho - A[j];
-        G = vD * V - 2.0 * pb[j];
+        V = fma(-2.0, A[j], rho);
+        G = fma(vD, V, -2.0 * pb[j]);
       } else if (k == 4) {
-        V = 0.5 * (A[j] - S[j]);
-        G = vD * V + (pb[j] + pc[j]);
+        V = fma(hic * rho, vD - uD, A[j]);
+        G = fma(vD, V, fma(hic, q[j][4], pb[j]));
       } else {
         V = rho * (k == 2 ? q[j][1 + T1] - u1 : q[j][1 + T2] - u2);
         G = vD * V;
@@ -524,7 +501,10 @@ __host__ __device__ __forceinline__ void roe_flux(const Geom& g, const double (&
       Gp[j] = 0.5 * (G + lam[k] * V);
       Gm[j] = 0.5 * (G - lam[k] * V);
     }
-    Gf[k] = weno5(Gp[0], Gp[1], Gp[2], Gp[3], Gp[4]) + weno5(Gm[5], Gm[4], Gm[3], Gm[2], Gm[1]);
+    Gf[k] = weno5(Gp[0], Gp[1], Gp[2], Gp[3], Gp[4]);
+    pin(Gf[k]);
+    Gf[k] += weno5(Gm[5], Gm[4], Gm[3], Gm[2], Gm[1]);
+    pin(Gf[k]);
   }
   const double sac = Gf[0] + Gf[4], dac = Gf[4] - Gf[0];
   const double s3 = sac + Gf[1];
@@ -535,54 +515,35 @@ __host__ __device__ __forceinline__ void roe_flux(const Geom& g, const double (&
   F[4] = H * sac + uD * c * dac + 0.5 * q2 * Gf[1] + u1 * Gf[2] + u2 * Gf[3];
 }
 
-// Numerical flux from the window's primitives and given face tangential
-// derivatives tf: WENO5-JS (or WENO5-Z) left and right of the face and HLLC,
-// or the Roe flux splitting, then the dissipative flux. The scheme is a
-// compile-time choice: a run-time branch between them multiplies the live
-// registers of the sweeps.
-template <int D, int SCH = SCH_JS, int PHYS = PHYS_ANY>
-__host__ __device__ __forceinline__ void face_flux_tf(const Geom& g, const FaceWindow& w, const double* tf,
-                                                      double* G) {
-  if constexpr (SCH == SCH_ROE) {
-    double F[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (with_inviscid<PHYS>(g)) roe_flux<D>(g, w.q, F);
-    sub_dissipative<D, PHYS>(g, w, tf, F);
+// Numerical flux from the window's primitives q[0..5] (cells i-2 .. i+3 around
+// face i+1/2) with the Roe flux splitting, T~ of cells i-1 .. i+2 and the face
+// values tf of the tangential derivatives (as in sub_dissipative_q). The
+// scheme is a compile-time choice: a run-time branch between schemes
+// multiplies the live registers of the sweeps.
+template <int D, int PHYS>
+__host__ __device__ __forceinline__ void roe_face_flux(const Geom& g, const double (&q)[6][5], const double* T,
+                                                       const double* tf, double* G) {
+  double F[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  if (with_inviscid<PHYS>(g)) roe_flux<D>(g, q, F);
 #pragma unroll
-    for (int v = 0; v < 5; ++v) G[v] = F[v];
-    return;
-  }
-  double WL[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, WR[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  if (with_inviscid<PHYS>(g)) {
+  for (int v = 0; v < 5; ++v) pin(F[v]);
+  sub_dissipative_q<D, PHYS>(g, q + 1, T, tf, F);
 #pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      if constexpr (sch_weno3(SCH)) {
-        WL[v] = weno3(w.q[1][v], w.q[2][v], w.q[3][v]);
-        WR[v] = weno3(w.q[4][v], w.q[3][v], w.q[2][v]);
-      } else if constexpr (SCH == SCH_Z) {
-        WL[v] = weno5z(w.q[0][v], w.q[1][v], w.q[2][v], w.q[3][v], w.q[4][v]);
-        WR[v] = weno5z(w.q[5][v], w.q[4][v], w.q[3][v], w.q[2][v], w.q[1][v]);
-      } else {
-        WL[v] = weno5(w.q[0][v], w.q[1][v], w.q[2][v], w.q[3][v], w.q[4][v]);
-        WR[v] = weno5(w.q[5][v], w.q[4][v], w.q[3][v], w.q[2][v], w.q[1][v]);
-      }
-    }
-  }
-  face_flux_lr<D, sch_rusanov(SCH), SCH == SCH_W3_NN, PHYS>(g, WL, WR, w, tf, G);
+  for (int v = 0; v < 5; ++v) G[v] = F[v];
 }
 
-// Reconstructed states of the cell-centred schemes (WENO5-JS and WENO3-JS on
-// the primitives; the Roe flux splitting projects per face, and WENO5-Z's
-// per-cell form needs more registers than the marches hold, so both stay
-// face by face): from the primitives q[0..4] of cells i-2 .. i+2, the left
-// state of face i+1/2 (qr) and the right state of face i-1/2 (ql), per
-// variable.
+// Reconstructed states of the cell-centred schemes (all but the Roe flux
+// splitting, which projects per face): from the primitives q[0..4] of cells
+// i-2 .. i+2, the left state of face i+1/2 (qr) and the right state of face
+// i-1/2 (ql), per variable.
 template <int SCH>
 __host__ __device__ __forceinline__ void recon_pair(double (*q)[5], double* qr, double* ql) {
-  static_assert(SCH != SCH_ROE && SCH != SCH_Z, "face-by-face schemes");
+  static_assert(SCH != SCH_ROE, "a face-by-face scheme");
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     pin(q[2][v]);
     if constexpr (sch_weno3(SCH)) weno3_pair(q[1][v], q[2][v], q[3][v], qr[v], ql[v]);
+    else if constexpr (SCH == SCH_Z) weno5z_pair(q[0][v], q[1][v], q[2][v], q[3][v], q[4][v], qr[v], ql[v]);
     else weno5_pair(q[0][v], q[1][v], q[2][v], q[3][v], q[4][v], qr[v], ql[v]);
     pin(qr[v]);
     pin(ql[v]);
@@ -610,12 +571,28 @@ __host__ __device__ __forceinline__ void face_flux_states(const Geom& g, const d
   for (int v = 0; v < 5; ++v) G[v] = F[v];
 }
 
-// Numerical flux G = F - F^d across the face (§3.3, §3.4) from a full window.
-template <int D, int SCH = SCH_JS, int PHYS = PHYS_ANY>
+// Numerical flux G = F - F^d across the face (§3.3, §3.4) of a full window with
+// the default scheme, each reconstruction on its own: what face_flux_rev
+// reverses (used by its host check).
+template <int D>
 __host__ __device__ __forceinline__ void face_flux(const Geom& g, const FaceWindow& w, double* G) {
-  double tf[4] = {0.0, 0.0, 0.0, 0.0};
-  if (with_viscous<PHYS>(g)) face_tangential(w, tf);
-  face_flux_tf<D, SCH, PHYS>(g, w, tf, G);
+  double F[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, tf[3] = {0.0, 0.0, 0.0};
+  if (g.inviscid) {
+    double WL[5], WR[5];
+    for (int v = 0; v < 5; ++v) {
+      WL[v] = weno5(w.q[0][v], w.q[1][v], w.q[2][v], w.q[3][v], w.q[4][v]);
+      WR[v] = weno5(w.q[5][v], w.q[4][v], w.q[3][v], w.q[2][v], w.q[1][v]);
+    }
+    hllc<D>(g.gamma, g.gm1i, WL, WR, F);
+  }
+  if (g.viscous) {
+    auto face = [&](int k) { return rc4(w.tg[0][k], w.tg[1][k], w.tg[2][k], w.tg[3][k]); };
+    tf[0] = face(0);
+    tf[1] = face(2);
+    tf[2] = face(1) + face(3);
+  }
+  sub_dissipative_q<D>(g, w.q + 1, w.T, tf, F);
+  for (int v = 0; v < 5; ++v) G[v] = F[v];
 }
 
 }  // namespace cfd
