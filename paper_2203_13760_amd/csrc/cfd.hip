@@ -84,6 +84,7 @@ struct cfd_solver {
   double* nntape = nullptr;   // Rusanov-NN per-face records of the reverse (adjoint scratch)
   double* nnbar = nullptr;    // caller's weight-gradient accumulator (may be NULL)
   NNTape tape{};
+  int seg_inv[3] = {1, 1, 1}, seg_dis[3] = {1, 1, 1};  // segments of the marching face reverses
   int npart = 0;
   bool images = false;        // the sweeps store the halo images of the next primitives
   DevCtl* ctl = nullptr;
@@ -589,6 +590,11 @@ static cfd_status run_graph(cfd_solver* s, double* U, int mode, double fixed_dt,
 // derivative-adjoint accumulators. Allocated on the first adjoint call.
 static cfd_status ensure_adjoint_scratch(cfd_solver* s) {
   if (s->A1) return CFD_OK;
+  for (int ax = 1; ax < 3; ++ax) {
+    const double groups = (double)((s->g.n[0] + 63) / 64) * s->g.n[3 - ax];
+    s->seg_inv[ax] = best_segment(s->g.n[ax], groups, 1.0, 1.5, 2);
+    s->seg_dis[ax] = best_segment(s->g.n[ax], groups, 1.0, 4.0, 2);
+  }
   // the marching face reverses address cells with 32-bit offsets
   if (s->ncell >= (1LL << 31)) return fail(CFD_EINVAL, "grid too large for the adjoint (2^31 padded cells or more)");
   const size_t st = sizeof(double) * 5 * (size_t)s->ncell;
@@ -641,17 +647,29 @@ static void launch_face_adj(cfd_solver* s, const double* P, const double* Rbar, 
     if (g.inviscid)
       hipLaunchKernelGGL(k_xadj_inv, blocks((g.n[0] + 6) * rows, kXInvNew), dim3(kBlock), 0, st, P, Rbar, rscale,
                          s->Wbar, g);
-    if (g.viscous || g.heat)
-      hipLaunchKernelGGL(k_xadj_dis, blocks((g.n[0] + 1 + kXDisCtx) * rows, kXDisNew), dim3(kBlock), 0, sd, P,
-                         Rbar, rscale, s->Wbar, s->Dbar, g);
+    const dim3 db = blocks((g.n[0] + 1 + kXDisCtx) * rows, kXDisNew);
+    if (g.viscous && g.heat)
+      hipLaunchKernelGGL(k_xadj_dis<PHYS_NS>, db, dim3(kBlock), 0, sd, P, Rbar, rscale, s->Wbar, s->Dbar, g);
+    else if (g.viscous || g.heat)
+      hipLaunchKernelGGL(k_xadj_dis<PHYS_ANY>, db, dim3(kBlock), 0, sd, P, Rbar, rscale, s->Wbar, s->Dbar, g);
   } else {
+    // segments of its own for each part: the inviscid one's seed and end are
+    // worth more cells
+    Geom gi = g, gd = g;
+    gi.seg = s->seg_inv[D];
+    gd.seg = s->seg_dis[D];
     int gx = 0, gy = 0;
-    sweep_march_blocks<D>(g, gx, gy);
-    if (g.inviscid)
-      hipLaunchKernelGGL(k_march_adj_inv<D>, dim3(gx, gy), dim3(kBlock), 0, st, P, Rbar, rscale, s->Wbar, g);
-    if (g.viscous || g.heat)
-      hipLaunchKernelGGL(k_march_adj_dis<D>, dim3(gx, gy), dim3(kBlock), 0, sd, P, Rbar, rscale, s->Wbar, s->Dbar,
-                         g);
+    if (g.inviscid) {
+      sweep_march_blocks<D>(gi, gx, gy);
+      hipLaunchKernelGGL(k_march_adj_inv<D>, dim3(gx, gy), dim3(kBlock), 0, st, P, Rbar, rscale, s->Wbar, gi);
+    }
+    sweep_march_blocks<D>(gd, gx, gy);
+    if (g.viscous && g.heat)
+      hipLaunchKernelGGL((k_march_adj_dis<D, PHYS_NS>), dim3(gx, gy), dim3(kBlock), 0, sd, P, Rbar, rscale, s->Wbar,
+                         s->Dbar, gd);
+    else if (g.viscous || g.heat)
+      hipLaunchKernelGGL((k_march_adj_dis<D, PHYS_ANY>), dim3(gx, gy), dim3(kBlock), 0, sd, P, Rbar, rscale, s->Wbar,
+                         s->Dbar, gd);
   }
 }
 

@@ -31,6 +31,9 @@ namespace cfd {
 __device__ __forceinline__ void atomic_add(double* p, double v) {
   if (v != 0.0) unsafeAtomicAdd(p, v);
 }
+__device__ __forceinline__ void atomic_add_at(double* base, unsigned off, double v) {
+  atomic_add(reinterpret_cast<double*>(reinterpret_cast<char*>(base) + off), v);
+}
 
 // Face numbering for axis D: face f in [0, n_D] lies between cells f-1 and f.
 // D = 0: f runs fastest, so the lanes of a wavefront hold consecutive faces of
@@ -84,6 +87,53 @@ __device__ __forceinline__ bool face_gbar(const Geom& g, const double* __restric
   return any != 0.0;
 }
 
+// Reverse of the dissipative flux of one face (sub_dissipative_q), from the
+// velocities u[0..3] and tangential sums t[0..3] of the four cells around it
+// and Gbar, the adjoint of G = F - F^d: what the cells' adjoints are formed
+// from - cell m takes cdn[m] d[v] + crc[m] f[v] for its velocities (in the order
+// u_D, u_T1, u_T2), cdn[m] T for T~ and crc[m] t[k] for its tangential sums. The
+// heat flux is linear in T~, so no T~ values are needed.
+struct DisRev {
+  double d[3], f[3], t[3], T;
+};
+
+template <int D, int PHYS>
+__device__ __forceinline__ void dissipative_rev(const Geom& g, const double (*u)[3], const double (*t)[3],
+                                                const double* Gb, DisRev& r) {
+  constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
+  const double i24 = g.idx[D] * (1.0 / 24.0);
+  const double Eb = -Gb[4];
+  if (with_viscous<PHYS>(g)) {
+    auto dn = [&](int v) { return fma(27.0, u[2][v] - u[1][v], u[0][v] - u[3][v]) * i24; };
+    auto rc = [&](int v) { return rc4(u[0][v], u[1][v], u[2][v], u[3][v]); };
+    auto rt = [&](int k) { return rc4(t[0][k], t[1][k], t[2][k], t[3][k]); };
+    const double tDD = g.mu * fma(4.0 / 3.0, dn(D), (-2.0 / 3.0) * rt(2));
+    const double tD1 = g.mu * (rt(0) + dn(T1)), tD2 = g.mu * (rt(1) + dn(T2));
+    const double bDD = g.mu * fma(Eb, rc(D), -Gb[1 + D]);
+    const double bD1 = g.mu * fma(Eb, rc(T1), -Gb[1 + T1]), bD2 = g.mu * fma(Eb, rc(T2), -Gb[1 + T2]);
+    r.d[0] = (4.0 / 3.0 * i24) * bDD;
+    r.d[1] = i24 * bD1;
+    r.d[2] = i24 * bD2;
+    r.f[0] = (1.0 / 16.0) * (Eb * tDD);
+    r.f[1] = (1.0 / 16.0) * (Eb * tD1);
+    r.f[2] = (1.0 / 16.0) * (Eb * tD2);
+    r.t[0] = (1.0 / 16.0) * bD1;
+    r.t[1] = (1.0 / 16.0) * bD2;
+    r.t[2] = (-2.0 / 48.0) * bDD;
+  }
+  r.T = g.kappa * i24 * Eb;
+}
+// cdn and crc without the factors dissipative_rev has applied.
+constexpr double kCdn[4] = {1.0, -27.0, 27.0, -1.0}, kCrc[4] = {-1.0, 9.0, 9.0, -1.0};
+
+// Component of Dbar a tangential sum's adjoint goes to: the mixed derivatives
+// u_D along T1 and T2 in their own, and the sum of the two derivatives along
+// their own axes in component (D, D), which fold_dbar hands to both.
+template <int D>
+__device__ __forceinline__ int dbar_comp(int k) {
+  return D * 3 + (k == 0 ? (D + 1) % 3 : (k == 1 ? (D + 2) % 3 : D));
+}
+
 // ---------------------------------------------------------------------------
 // x faces: one lane per slot of a row, as in the forward x sweep; the
 // neighbouring cells of a row are neighbouring lanes, so a cell's inputs are
@@ -103,7 +153,7 @@ __device__ __forceinline__ bool face_gbar(const Geom& g, const double* __restric
 // supply shuffles and collect sums.
 constexpr int kXInvNew = 60;
 
-__global__ void __launch_bounds__(kBlock) k_xadj_inv(const double* P, const double* __restrict__ Rbar,
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) k_xadj_inv(const double* P, const double* __restrict__ Rbar,
                                                      double rscale, double* Wbar, Geom g) {
   const int lane = threadIdx.x & 63;
   const int wave = (xcd_major_block(blockIdx.x, gridDim.x) * kBlock + (int)threadIdx.x) >> 6;
@@ -145,17 +195,19 @@ __global__ void __launch_bounds__(kBlock) k_xadj_inv(const double* P, const doub
   asm volatile("" ::: "memory");  // reload the window below instead of keeping it live
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
-    const double qrb = lane_shl1(WLb[v]);  // face x+1: cotangent of the right-face value of x
+    const double up = lane_shl1(WLb[v]);  // every lane takes part in the shift
+    const double qrb = rev ? up : 0.0;    // face x+1: cotangent of the right-face value of x
+    const double qlb = rev ? WRb[v] : 0.0;
     double gq[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (rev) {
-      const double* q = P + v * g.vs + c0;
-      weno5_pair_rev(q[0], q[1], q[2], q[3], q[4], qrb, WRb[v], gq);
-    }
+    const double* q = P + v * g.vs + c0;
+    weno5_pair_rev(q[0], q[1], q[2], q[3], q[4], qrb, qlb, gq);
+    pin(gq[0]);
+    pin(gq[4]);
     // cell x receives gq[4] from lane - 2, gq[3] from lane - 1, gq[2] from
     // itself, gq[1] from lane + 1 and gq[0] from lane + 2
-    const double up = lane_shr1(lane_shr1(gq[4]) + gq[3]);
-    const double down = lane_shl1(lane_shl1(gq[0]) + gq[1]);
-    if (inrange) atomic_add(Wbar + v * g.vs + cx, up + gq[2] + down);
+    const double lo = lane_shr1(lane_shr1(gq[4]) + gq[3]);
+    const double hi = lane_shl1(lane_shl1(gq[0]) + gq[1]);
+    if (inrange) atomic_add(Wbar + v * g.vs + cx, lo + gq[2] + hi);
   }
 }
 
@@ -169,6 +221,7 @@ __global__ void __launch_bounds__(kBlock) k_xadj_inv(const double* P, const doub
 constexpr int kXDisCtx = 3;
 constexpr int kXDisNew = 64 - kXDisCtx;
 
+template <int PHYS>
 __global__ void __launch_bounds__(kBlock) k_xadj_dis(const double* __restrict__ P, const double* __restrict__ Rbar,
                                                      double rscale, double* Wbar, double* Dbar, Geom g) {
   const int lane = threadIdx.x & 63;
@@ -189,85 +242,74 @@ __global__ void __launch_bounds__(kBlock) k_xadj_dis(const double* __restrict__ 
   const bool face = inrange && f >= 0 && lane >= kXDisCtx;
   const long long co = cell_at(g, inrange ? f + 1 : 0, j, k);  // the lane's cell f+1
   // inputs of cell f+1, then of cells f, f-1, f-2 from the lanes below
-  double u[4][3], d[4][4], r[3][5];
+  double u[4][3], d[4][3], r[3][5];
+  const bool vis = with_viscous<PHYS>(g), heat = with_heat<PHYS>(g);
 #pragma unroll
-  for (int v = 0; v < 3; ++v) u[3][v] = g.viscous ? P[(1 + v) * g.vs + co] : 0.0;
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) d[3][kk] = 0.0;
-  if (g.viscous) tangential_at_flat<0>(g, P, co, d[3]);
+  for (int v = 0; v < 3; ++v) {
+    u[3][v] = vis ? P[(1 + v) * g.vs + co] : 0.0;
+    d[3][v] = 0.0;
+  }
+  if (vis) {
+    double x[4][4];
+    tangential_load<0>(g, P, co, x);
+    __builtin_amdgcn_sched_barrier(0);
+    tangential_combine3<0>(g, x, d[3]);
+  }
 #pragma unroll
   for (int v = 0; v < 5; ++v) r[0][v] = inrange && f + 1 >= 0 && f + 1 < n ? Rbar[v * g.vs + co] : 0.0;
 #pragma unroll
   for (int m = 2; m >= 0; --m) {
 #pragma unroll
-    for (int v = 0; v < 3; ++v) u[m][v] = lane_shr1(u[m + 1][v]);
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) d[m][kk] = lane_shr1(d[m + 1][kk]);
+    for (int v = 0; v < 3; ++v) {
+      u[m][v] = lane_shr1(u[m + 1][v]);
+      d[m][v] = lane_shr1(d[m + 1][v]);
+    }
   }
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     r[1][v] = lane_shr1(r[0][v]);  // cell f
     r[2][v] = lane_shr1(r[1][v]);  // cell f-1
   }
-  struct RegSink {
-    double qb[4][4];   // cells f-2 .. f+1: u, v, w, T~
-    double tgb[4][4];  // cells f-2 .. f+1: derivative inputs
-    __device__ void q(int m, int v, double x) { qb[m - 1][v == 5 ? 3 : v - 1] += x; }
-    __device__ void tg(int m, int kk, double x) { tgb[m - 1][kk] += x; }
-  } sink;
+  const double gsc = face ? rscale * g.idx[0] : 0.0;  // lanes without a face contribute zeros
+  double Gb[5];
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int v = 0; v < 5; ++v) Gb[v] = face ? gsc * (r[1][v] - r[2][v]) : 0.0;
+  DisRev R;
+  dissipative_rev<0, PHYS>(g, u, d, Gb, R);
+  if (!face) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) sink.qb[m][v] = sink.tgb[m][v] = 0.0;
-  if (face) {
-    FaceWindow w;
-#pragma unroll
-    for (int m = 0; m < 6; ++m)
-#pragma unroll
-      for (int v = 0; v < 5; ++v) w.q[m][v] = 0.0;
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      w.T[m] = 0.0;
-#pragma unroll
-      for (int v = 0; v < 3; ++v) w.q[1 + m][1 + v] = u[m][v];
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) w.tg[m][kk] = d[m][kk];
-    }
-    const double gsc = rscale * g.idx[0];
-    double Gb[5];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) Gb[v] = gsc * (r[1][v] - r[2][v]);
-    Geom gd = g;
-    gd.inviscid = 0;  // the inviscid part is k_xadj_inv
-    face_flux_rev<0>(gd, w, Gb, sink);
+    for (int v = 0; v < 3; ++v) R.d[v] = R.f[v] = R.t[v] = 0.0;
+    R.T = 0.0;
   }
   // cell f+1 collects its share from faces f, f+1, f+2, f+3 (this lane and
   // the three above), up to the end of its row
   const bool above = inrange && f < n;
-  auto gather = [&](const double (&c)[4][4], int v) {
-    double a = c[0][v];
+  auto gather = [&](double wd, const double* cd, double wf, const double* cf) {
+    double a = fma(wd, cd[0], wf * cf[0]);
 #pragma unroll
     for (int m = 1; m < 4; ++m) {
       const double b = lane_shl1(a);  // every lane takes part in the shift
-      a = (above ? b : 0.0) + c[m][v];
+      a = fma(wd, cd[m], fma(wf, cf[m], above ? b : 0.0));
     }
     return a;
   };
-  const int wslot[4] = {1, 2, 3, 5};  // u, v, w, T~ in Wbar
-  const int comp[4] = {0 * 3 + 1, 1 * 3 + 1, 0 * 3 + 2, 2 * 3 + 2};
-  const bool tact[4] = {g.act[1] != 0, g.act[1] != 0, g.act[2] != 0, g.act[2] != 0};
+  if (vis) {
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    if (v == 3 ? !g.heat : !g.viscous) continue;
-    const double t = gather(sink.qb, v);
-    if (inrange) atomic_add(Wbar + wslot[v] * g.vs + co, t);
+    for (int v = 0; v < 3; ++v) {
+      const double a = gather(R.d[v], kCdn, R.f[v], kCrc);
+      if (inrange) atomic_add(Wbar + (1 + v) * g.vs + co, a);
+    }
   }
-  if (g.viscous) {
+  if (heat) {
+    const double a = gather(R.T, kCdn, 0.0, kCrc);
+    if (inrange) atomic_add(Wbar + 5 * g.vs + co, a);
+  }
+  if (vis) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      if (!tact[kk]) continue;
-      const double t = gather(sink.tgb, kk);
-      if (inrange) atomic_add(Dbar + comp[kk] * g.vs + co, t);
+    for (int k = 0; k < 3; ++k) {
+      if (k < 2 && !g.act[1 + k]) continue;
+      const double a = gather(0.0, kCdn, R.t[k], kCrc);
+      if (inrange) atomic_add(Dbar + dbar_comp<0>(k) * g.vs + co, a);
     }
   }
 }
@@ -283,22 +325,22 @@ __global__ void __launch_bounds__(kBlock) k_xadj_dis(const double* __restrict__ 
 // variable; a cell near a segment end gets a share from each of the two
 // segments). Launch shape: sweep_march_blocks<AX>.
 
-// Column, segment and first/last face of the marching wavefront; false for a
-// lane without a column. The segment of cells [s0, s1) owns faces s0 .. s1-1,
-// and the last segment also face n (the upper boundary).
+// Column, segment and first/last face of the marching wavefront, all uniform;
+// false for a wavefront without a column. The lane's x is i (at or past the
+// row's end in lanes without a cell). The segment of cells [s0, s1) owns faces
+// s0 .. s1-1, and the last segment also face n (the upper boundary).
 template <int AX>
 __device__ __forceinline__ bool march_adj_column(const Geom& g, int& i, int& o, int& s0, int& fe) {
   constexpr int OT = AX == 1 ? 2 : 1;
   const int logical = xcd_major_block(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int by = logical / gridDim.x, bx = logical - by * gridDim.x;
-  i = bx * 64 + (threadIdx.x & 63);
+  i = bx * 64 + (int)(threadIdx.x & 63);
   const int sl = g.seg;
   const int nseg = (g.n[AX] + sl - 1) / sl;
-  const long long col = (long long)by * (kBlock >> 6) + (threadIdx.x >> 6);
-  if (i >= g.n[0] || col >= (long long)g.n[OT] * nseg) return false;
-  o = (int)(col / nseg);
-  const int seg = (int)(col - (long long)o * nseg);
-  s0 = seg * sl;
+  const int col = uniform(by * (kBlock >> 6) + wave_in_block());
+  if (col >= g.n[OT] * nseg) return false;
+  o = uniform(col / nseg);
+  s0 = (col - o * nseg) * sl;
   const int s1 = min(s0 + sl, g.n[AX]);
   fe = s1 == g.n[AX] ? s1 : s1 - 1;
   return true;
@@ -317,17 +359,13 @@ __device__ __forceinline__ long long march_adj_cell(const Geom& g, int i, int o,
 // A pair shared with the neighbouring segment is reversed in both, each with
 // its own face's share of the cotangent (the reverse is linear in it).
 // The window holds cells f-3 .. f+2 in registers, and the per-cell sums of
-// the five cells a pair reverse touches live in a lane-private LDS ring.
-// Cell offsets are 32-bit (the adjoint requires fewer than 2^31 padded
-// cells): one address register per cell instead of one per cell and
-// variable. The window, the HLLC reverse and the carried states still need
-// about 380 registers, so the kernel runs one wavefront per SIMD; at two it
-// spills, and reloading the window at every face instead (which fits two)
-// ran 1.3x slower, the reloads' latency exposed.
+// the five cells a pair reverse touches live in a lane-private LDS ring. With
+// scalar bases and the variables reversed one after another (pin) it fits two
+// wavefronts per SIMD; before, at 384 registers, it ran one.
 constexpr int kMarchRing = 5;
 
 template <int AX>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
 k_march_adj_inv(const double* __restrict__ P, const double* __restrict__ Rbar, double rscale, double* Wbar,
                 Geom g) {
   __shared__ double ring[kMarchRing * 5 * kBlock];
@@ -336,62 +374,68 @@ k_march_adj_inv(const double* __restrict__ P, const double* __restrict__ Rbar, d
   const int tid = threadIdx.x;
 #pragma unroll
   for (int e = 0; e < kMarchRing * 5; ++e) ring[e * kBlock + tid] = 0.0;
-  const int st = (int)g.s[AX];
-  const long long vs = g.vs;
+  const long long st = g.s[AX], vs = g.vs;
   const int n = g.n[AX];
   const double gs_scale = rscale * g.idx[AX];
-  int c = (int)march_adj_cell<AX>(g, i, o, s0 - 3);  // window cell 0: cell f-3 of face f = s0
+  const long long c1 = march_adj_cell<AX>(g, 0, o, s0 - 3);  // window cell 0: cell f-3 of face f = s0, at x = 0
+  const unsigned off = (unsigned)min(i, g.n[0] - 1) * 8u;
+  const bool in = i < g.n[0];
   double w[6][5];
 #pragma unroll
-  for (int m = 0; m < 6; ++m) load_prims(P, vs, c + m * st, w[m]);
+  for (int m = 0; m < 6; ++m)
+#pragma unroll
+    for (int v = 0; v < 5; ++v) w[m][v] = ld_at(P + v * vs + c1 + m * st, off);
   double WLc[5], WRbc[5], rl[5];
   {
     double unused[5];
-    double q[5][5];
-#pragma unroll
-    for (int m = 0; m < 5; ++m)
-#pragma unroll
-      for (int v = 0; v < 5; ++v) q[m][v] = w[m][v];
-    recon_pair<SCH_JS>(q, WLc, unused);  // cell s0-1: left state of face s0
+    recon_pair<SCH_JS>(w, WLc, unused);  // cell s0-1: left state of face s0
   }
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     WRbc[v] = 0.0;  // face s0-1 belongs to the previous segment
-    rl[v] = s0 >= 1 ? Rbar[v * vs + c + 2 * st] : 0.0;
+    rl[v] = s0 >= 1 ? ld_at(Rbar + v * vs + c1 + 2 * st, off) : 0.0;
   }
   int r0 = 0;  // ring slot of window cell 0
   for (int f = s0; f <= fe; ++f) {
-    const bool more = f < fe;
-    double nq[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, rr[5];
-    if (more) load_prims(P, vs, c + 6 * st, nq);
+    const long long c = c1 + uniform(f - s0) * st;
+    // the entering cell (after the last face one already held)
+    const long long ce = f < fe ? c + 6 * st : c + 5 * st;
+    double nq[5], rr[5];
 #pragma unroll
-    for (int v = 0; v < 5; ++v) rr[v] = f < n ? Rbar[v * vs + c + 3 * st] : 0.0;
+    for (int v = 0; v < 5; ++v) nq[v] = ld_at(P + v * vs + ce, off);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) rr[v] = f < n ? ld_at(Rbar + v * vs + c + 3 * st, off) : 0.0;
+    // pair of cell f (window cells 1..5): left state of face f+1, right state of face f
+    double nWL[5], WR[5];
+    recon_pair<SCH_JS>(w + 1, nWL, WR);
     double Gb[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) Gb[v] = gs_scale * (rr[v] - rl[v]);
-    // pair of cell f (window cells 1..5): left state of face f+1, right state of face f
-    double nWL[5], WR[5];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) weno5_pair(w[1][v], w[2][v], w[3][v], w[4][v], w[5][v], nWL[v], WR[v]);
     double WLb[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, WRb[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     hllc_rev<AX>(g.gamma, g.gm1i, WLc, WR, Gb, WLb, WRb);
-    // pair of cell f-1 (window cells 0..4) with the cotangents of faces f and f-1
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      pin(WLb[v]);
+      pin(WRb[v]);
+    }
+    // pair of cell f-1 (window cells 0..4) with the cotangents of faces f and
+    // f-1; cell f-3 is complete for this segment
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
       double gq[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+      pin(w[2][v]);
       weno5_pair_rev(w[0][v], w[1][v], w[2][v], w[3][v], w[4][v], WLb[v], WRbc[v], gq);
 #pragma unroll
       for (int m = 0; m < 5; ++m) {
         const int slot = r0 + m < kMarchRing ? r0 + m : r0 + m - kMarchRing;
-        ring[(slot * 5 + v) * kBlock + tid] += gq[m];
+        double& a = ring[(slot * 5 + v) * kBlock + tid];
+        if (m == 0) {
+          if (in) atomic_add_at(Wbar + v * vs + c, off, a + gq[0]);
+          a = 0.0;
+        } else {
+          a += gq[m];
+        }
       }
-    }
-    // cell f-3 is complete for this segment
-#pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      double& a = ring[(r0 * 5 + v) * kBlock + tid];
-      atomic_add(Wbar + v * vs + c, a);
-      a = 0.0;
     }
     r0 = r0 + 1 < kMarchRing ? r0 + 1 : 0;
 #pragma unroll
@@ -403,9 +447,10 @@ k_march_adj_inv(const double* __restrict__ P, const double* __restrict__ Rbar, d
       WRbc[v] = WRb[v];
       rl[v] = rr[v];
     }
-    c += st;
   }
+  if (!in) return;
   // the pair of cell fe (window cells 0..4) with the cotangent of face fe only
+  const long long c = c1 + (long long)(fe + 1 - s0) * st;
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     double gq[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
@@ -413,130 +458,138 @@ k_march_adj_inv(const double* __restrict__ P, const double* __restrict__ Rbar, d
 #pragma unroll
     for (int m = 0; m < 5; ++m) {
       const int slot = r0 + m < kMarchRing ? r0 + m : r0 + m - kMarchRing;
-      atomic_add(Wbar + v * vs + c + m * st, ring[(slot * 5 + v) * kBlock + tid] + gq[m]);
+      atomic_add_at(Wbar + v * vs + c + m * st, off, ring[(slot * 5 + v) * kBlock + tid] + gq[m]);
     }
   }
 }
 
 // Dissipative part (viscous and heat flux). Face f reads window cells
-// f-2 .. f+1 (u, v, w, T~ and the four tangential-derivative inputs of each,
-// formed from P as in the forward marches); the adjoints of those inputs
-// (Wbar u, v, w, T~ and Dbar) are summed in registers and cell f-2 is added
-// to memory after face f.
-template <int AX>
+// f-2 .. f+1 (u, v, w and the tangential sums of each, formed from P as in the
+// forward marches); the adjoints of those inputs (Wbar u, v, w, T~ and Dbar)
+// are summed in registers and cell f-2 is added to memory after face f.
+template <int AX, int PHYS>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
 k_march_adj_dis(const double* __restrict__ P, const double* __restrict__ Rbar, double rscale, double* Wbar,
                 double* Dbar, Geom g) {
   constexpr int T1 = (AX + 1) % 3, T2 = (AX + 2) % 3;
   int i, o, s0, fe;
   if (!march_adj_column<AX>(g, i, o, s0, fe)) return;
-  const int st = (int)g.s[AX];  // 32-bit cell offsets, as in k_march_adj_inv
-  const long long vs = g.vs;
+  const long long st = g.s[AX], vs = g.vs;
   const int n = g.n[AX];
   const double gs_scale = rscale * g.idx[AX];
-  Geom gd = g;
-  gd.inviscid = 0;  // the inviscid part is k_march_adj_inv
-  int c = (int)march_adj_cell<AX>(g, i, o, s0 - 2);  // window cell 0: cell f-2 of face f = s0
-  // q[1..4] (u, v, w) and tg[0..3]: cells f-2 .. f+1. The heat flux is
-  // linear in T~, so its reverse needs no T~ values.
-  FaceWindow win;
-#pragma unroll
-  for (int m = 0; m < 6; ++m)
-#pragma unroll
-    for (int v = 0; v < 5; ++v) win.q[m][v] = 0.0;
+  const long long c1 = march_adj_cell<AX>(g, 0, o, s0 - 2);  // window cell 0: cell f-2 of face f = s0, at x = 0
+  const unsigned off = (unsigned)min(i, g.n[0] - 1) * 8u;
+  const bool in = i < g.n[0];
+  const bool vis = with_viscous<PHYS>(g), heat = with_heat<PHYS>(g);
+  const long long sT1 = g.act[T1] ? g.s[T1] : 0, sT2 = g.act[T2] ? g.s[T2] : 0;
+  const double w1 = g.act[T1] ? g.idx[T1] * (1.0 / 12.0) : 0.0, w2 = g.act[T2] ? g.idx[T2] * (1.0 / 12.0) : 0.0;
+  double u[4][3], tg[4][3];  // cells f-2 .. f+1
+  Diff4 d[4];
+  auto tang_load = [&](long long cc) {
+    d[0].load(P + (1 + AX) * vs + cc, sT1, off);
+    d[1].load(P + (1 + T1) * vs + cc, sT1, off);
+    d[2].load(P + (1 + AX) * vs + cc, sT2, off);
+    d[3].load(P + (1 + T2) * vs + cc, sT2, off);
+  };
+  auto tang_sum = [&](double* t) {
+    t[0] = d[0].diff() * w1;
+    t[1] = d[2].diff() * w2;
+    t[2] = fma(d[1].diff(), w1, d[3].diff() * w2);
+  };
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
-    win.T[m] = 0.0;
 #pragma unroll
-    for (int v = 1; v < 4; ++v) win.q[1 + m][v] = g.viscous ? P[v * vs + c + m * st] : 0.0;
-    if (g.viscous) tangential_at<AX>(g, P, c + m * st, win.tg[m]);
-    else
-#pragma unroll
-      for (int k = 0; k < 4; ++k) win.tg[m][k] = 0.0;
+    for (int v = 0; v < 3; ++v) u[m][v] = vis ? ld_at(P + (1 + v) * vs + c1 + m * st, off) : 0.0;
+    tg[m][0] = tg[m][1] = tg[m][2] = 0.0;
+    if (vis) {
+      tang_load(c1 + m * st);
+      tang_sum(tg[m]);
+    }
   }
-  struct RegSink {
-    double qb[4][4];   // window cells 0..3: u, v, w, T~
-    double tgb[4][4];  // window cells 0..3: derivative inputs
-    __device__ void q(int m, int v, double x) { qb[m - 1][v == 5 ? 3 : v - 1] += x; }
-    __device__ void tg(int m, int k, double x) { tgb[m - 1][k] += x; }
-  } sink;
+  double ub[4][4], tb[4][3];  // adjoints of cells f-2 .. f+1: u_D, u_T1, u_T2, T~; the tangential sums
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int m = 0; m < 4; ++m) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) sink.qb[m][v] = sink.tgb[m][v] = 0.0;
+    for (int v = 0; v < 4; ++v) ub[m][v] = 0.0;
+    tb[m][0] = tb[m][1] = tb[m][2] = 0.0;
+  }
   double rl[5];
 #pragma unroll
-  for (int v = 0; v < 5; ++v) rl[v] = s0 >= 1 ? Rbar[v * vs + c + st] : 0.0;
-  const int wslot[4] = {1, 2, 3, 5};  // u, v, w, T~ in Wbar
-  const int comp[4] = {AX * 3 + T1, T1 * 3 + T1, AX * 3 + T2, T2 * 3 + T2};
-  const bool tact[4] = {g.act[T1] != 0, g.act[T1] != 0, g.act[T2] != 0, g.act[T2] != 0};
-  for (int f = s0; f <= fe; ++f) {
-    const bool more = f < fe;
-    double nq[3] = {0.0, 0.0, 0.0}, ntr[4][4], rr[5];
-    if (more && g.viscous) {
+  for (int v = 0; v < 5; ++v) rl[v] = s0 >= 1 ? ld_at(Rbar + v * vs + c1 + st, off) : 0.0;
+  const int slot[4] = {1 + AX, 1 + T1, 1 + T2, 5};
+  auto put = [&](long long cc, const double* b, const double* t) {
+    if (!in) return;
 #pragma unroll
-      for (int v = 1; v < 4; ++v) nq[v - 1] = P[v * vs + c + 4 * st];
-      tangential_load<AX>(g, P, c + 4 * st, ntr);
+    for (int v = 0; v < 4; ++v)
+      if (v == 3 ? heat : vis) atomic_add_at(Wbar + slot[v] * vs + cc, off, b[v]);
+    if (vis) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (k == 2 || g.act[k == 0 ? T1 : T2]) atomic_add_at(Dbar + dbar_comp<AX>(k) * vs + cc, off, t[k]);
+    }
+  };
+  for (int f = s0; f <= fe; ++f) {
+    const long long c = c1 + uniform(f - s0) * st;
+    const long long ce = f < fe ? c + 4 * st : c + 3 * st;  // the entering cell (after the last face one already held)
+    double nq[3], rr[5];
+    if (vis) {
+#pragma unroll
+      for (int v = 0; v < 3; ++v) nq[v] = ld_at(P + (1 + v) * vs + ce, off);
+      tang_load(ce);
     }
 #pragma unroll
-    for (int v = 0; v < 5; ++v) rr[v] = f < n ? Rbar[v * vs + c + 2 * st] : 0.0;
+    for (int v = 0; v < 5; ++v) rr[v] = f < n ? ld_at(Rbar + v * vs + c + 2 * st, off) : 0.0;
+    __builtin_amdgcn_sched_barrier(0);
     double Gb[5];
 #pragma unroll
     for (int v = 0; v < 5; ++v) Gb[v] = gs_scale * (rr[v] - rl[v]);
-    face_flux_rev<AX>(gd, win, Gb, sink);
-    // cell f-2 is complete for this segment
+    DisRev r;
+    dissipative_rev<AX, PHYS>(g, u, tg, Gb, r);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      if (v == 3 ? g.heat : g.viscous) atomic_add(Wbar + wslot[v] * vs + c, sink.qb[0][v]);
-    }
-    if (g.viscous) {
+    for (int m = 0; m < 4; ++m) {
+      if (vis) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (tact[k]) atomic_add(Dbar + comp[k] * vs + c, sink.tgb[0][k]);
+        for (int v = 0; v < 3; ++v) {
+          ub[m][v] = fma(kCdn[m], r.d[v], fma(kCrc[m], r.f[v], ub[m][v]));
+          tb[m][v] = fma(kCrc[m], r.t[v], tb[m][v]);
+        }
+      }
+      if (heat) ub[m][3] = fma(kCdn[m], r.T, ub[m][3]);
     }
-    double ntg[4] = {0.0, 0.0, 0.0, 0.0};
-    if (more && g.viscous) tangential_combine<AX>(g, ntr, ntg);
+    put(c, ub[0], tb[0]);  // cell f-2 is complete for this segment
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        sink.qb[m][v] = sink.qb[m + 1][v];
-        sink.tgb[m][v] = sink.tgb[m + 1][v];
-        win.tg[m][v] = win.tg[m + 1][v];
+      for (int v = 0; v < 4; ++v) ub[m][v] = ub[m + 1][v];
+#pragma unroll
+      for (int v = 0; v < 3; ++v) {
+        tb[m][v] = tb[m + 1][v];
+        tg[m][v] = tg[m + 1][v];
+        u[m][v] = u[m + 1][v];
       }
-#pragma unroll
-      for (int v = 1; v < 4; ++v) win.q[1 + m][v] = win.q[2 + m][v];
     }
+    ub[3][3] = 0.0;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      sink.qb[3][v] = sink.tgb[3][v] = 0.0;
-      win.tg[3][v] = ntg[v];
+    for (int v = 0; v < 3; ++v) {
+      ub[3][v] = tb[3][v] = 0.0;
+      if (vis) u[3][v] = nq[v];
     }
-#pragma unroll
-    for (int v = 1; v < 4; ++v) win.q[4][v] = nq[v - 1];
+    if (vis) tang_sum(tg[3]);
 #pragma unroll
     for (int v = 0; v < 5; ++v) rl[v] = rr[v];
-    c += st;
   }
   // cells fe-1 .. fe+1 (window cells 0..2) hold the rest of this segment's sums
+  const long long c = c1 + (long long)(fe + 1 - s0) * st;
 #pragma unroll
-  for (int m = 0; m < 3; ++m) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      if (v == 3 ? g.heat : g.viscous) atomic_add(Wbar + wslot[v] * vs + c + m * st, sink.qb[m][v]);
-    }
-    if (g.viscous) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (tact[k]) atomic_add(Dbar + comp[k] * vs + c + m * st, sink.tgb[m][k]);
-    }
-  }
+  for (int m = 0; m < 3; ++m) put(c + m * st, ub[m], tb[m]);
 }
 
 // Transposed centred differences of Dbar at padded cell cc (coordinates q),
 // added to wb[1..3]: phi_bar(m) += (Dbar(m+2) - 8 Dbar(m+1) + 8 Dbar(m-1) -
-// Dbar(m-2)) / (12 dx_t). CHECK selects the range checks a halo image needs;
-// an interior cell's +-2 neighbours always lie inside the padded block.
+// Dbar(m-2)) / (12 dx_t), where the adjoint of du_t/dx_t is the sum of the
+// (D, D) components of the other two face directions. CHECK selects the range
+// checks a halo image needs; an interior cell's +-2 neighbours always lie
+// inside the padded block.
 template <bool CHECK>
 __device__ __forceinline__ void fold_dbar(const Geom& g, const double* __restrict__ Dbar, long long cc,
                                           const int* q, double* wb) {
@@ -546,16 +599,22 @@ __device__ __forceinline__ void fold_dbar(const Geom& g, const double* __restric
     const long long st = g.s[t];
     const int lo = -g.h[t], hi = g.n[t] + g.h[t];
     const int y = q[t];
-    const double i12 = g.idx[t] / 12.0;
-#pragma unroll
-    for (int comp = 0; comp < 3; ++comp) {
-      const double* Db = Dbar + (comp * 3 + t) * g.vs + cc;
+    const double i12 = g.idx[t] * (1.0 / 12.0);
+    auto diff = [&](int comp) {
+      const double* Db = Dbar + comp * g.vs + cc;
       double acc = 0.0;
       if (!CHECK || y + 2 < hi) acc += Db[2 * st];
       if (!CHECK || y + 1 < hi) acc -= 8.0 * Db[st];
       if (!CHECK || y - 1 >= lo) acc += 8.0 * Db[-st];
       if (!CHECK || y - 2 >= lo) acc -= Db[-2 * st];
-      wb[1 + comp] += acc * i12;
+      return acc;
+    };
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      if (a != t) {
+        if (g.act[a]) wb[1 + a] += diff(a * 3 + t) * i12;       // du_a/dx_t, from the faces normal to a
+        if (g.act[a]) wb[1 + t] += diff(a * 3 + a) * i12;       // du_t/dx_t, from the faces normal to a
+      }
     }
   }
 }
