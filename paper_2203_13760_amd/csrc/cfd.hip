@@ -74,7 +74,7 @@ struct cfd_solver {
   double* A2 = nullptr;
   double* A3 = nullptr;
   double* Wbar = nullptr; // 6 x padded
-  double* Dbar = nullptr; // 9 x padded (viscous runs)
+  double* Dbar = nullptr; // 9 x padded (viscous runs; after Wbar in its array)
   // a second pair, cleared on the side stream during one right-hand-side
   // adjoint for the next one of the same step adjoint (the two swap)
   double* Wbar2 = nullptr;
@@ -598,12 +598,9 @@ static cfd_status ensure_adjoint_scratch(cfd_solver* s) {
   // the marching face reverses address cells with 32-bit offsets
   if (s->ncell >= (1LL << 31)) return fail(CFD_EINVAL, "grid too large for the adjoint (2^31 padded cells or more)");
   const size_t st = sizeof(double) * 5 * (size_t)s->ncell;
+  const size_t wd = sizeof(double) * (s->g.viscous ? 6 + kGradComps : 6) * (size_t)s->ncell;
   bool ok = hipMalloc(&s->A1, st) == hipSuccess && hipMalloc(&s->A2, st) == hipSuccess &&
-            hipMalloc(&s->Wbar, sizeof(double) * 6 * (size_t)s->ncell) == hipSuccess &&
-            hipMalloc(&s->Wbar2, sizeof(double) * 6 * (size_t)s->ncell) == hipSuccess;
-  if (ok && s->g.viscous)
-    ok = hipMalloc(&s->Dbar, sizeof(double) * kGradComps * (size_t)s->ncell) == hipSuccess &&
-         hipMalloc(&s->Dbar2, sizeof(double) * kGradComps * (size_t)s->ncell) == hipSuccess;
+            hipMalloc(&s->Wbar, wd) == hipSuccess && hipMalloc(&s->Wbar2, wd) == hipSuccess;
   long long F = 0;
   if (s->g.nn) {
     for (int d = 0; d < 3; ++d)
@@ -613,11 +610,15 @@ static cfd_status ensure_adjoint_scratch(cfd_solver* s) {
   }
   if (!ok) {
     (void)hipGetLastError();
-    double* b[] = {s->A1, s->A2, s->Wbar, s->Dbar, s->Wbar2, s->Dbar2, s->nntape};
+    double* b[] = {s->A1, s->A2, s->Wbar, s->Wbar2, s->nntape};
     for (double* x : b)
       if (x) (void)hipFree(x);
-    s->A1 = s->A2 = s->Wbar = s->Dbar = s->Wbar2 = s->Dbar2 = s->nntape = nullptr;
+    s->A1 = s->A2 = s->Wbar = s->Wbar2 = s->nntape = nullptr;
     return fail(CFD_ENOMEM, "adjoint scratch allocation failed");
+  }
+  if (s->g.viscous) {
+    s->Dbar = s->Wbar + 6 * s->ncell;
+    s->Dbar2 = s->Wbar2 + 6 * s->ncell;
   }
   if (s->g.nn) {
     NNTape& t = s->tape;
@@ -633,58 +634,84 @@ static cfd_status ensure_adjoint_scratch(cfd_solver* s) {
   return CFD_OK;
 }
 
-// The face reverses of axis D: the inviscid part on st, the dissipative part on sd.
-template <int D>
-static void launch_face_adj(cfd_solver* s, const double* P, const double* Rbar, double rscale, hipStream_t st,
-                            hipStream_t sd) {
+// Blocks of the face reverses of axis D, inviscid and dissipative part.
+static int adj_blocks(const cfd_solver* s, int D, bool dis) {
   const Geom& g = s->g;
-  if constexpr (D == 0) {
+  if (!g.act[D]) return 0;
+  if (D == 0) {
     const long long rows = (long long)g.n[1] * g.n[2];
-    auto blocks = [&](long long slots, int per_wave) {
-      const long long waves = (slots + per_wave - 1) / per_wave;
-      return dim3((unsigned)((waves + (kBlock / 64) - 1) / (kBlock / 64)));
-    };
-    if (g.inviscid)
-      hipLaunchKernelGGL(k_xadj_inv, blocks((g.n[0] + 6) * rows, kXInvNew), dim3(kBlock), 0, st, P, Rbar, rscale,
-                         s->Wbar, g);
-    const dim3 db = blocks((g.n[0] + 1 + kXDisCtx) * rows, kXDisNew);
-    if (g.viscous && g.heat)
-      hipLaunchKernelGGL(k_xadj_dis<PHYS_NS>, db, dim3(kBlock), 0, sd, P, Rbar, rscale, s->Wbar, s->Dbar, g);
-    else if (g.viscous || g.heat)
-      hipLaunchKernelGGL(k_xadj_dis<PHYS_ANY>, db, dim3(kBlock), 0, sd, P, Rbar, rscale, s->Wbar, s->Dbar, g);
-  } else {
-    // segments of its own for each part: the inviscid one's seed and end are
-    // worth more cells
-    Geom gi = g, gd = g;
-    gi.seg = s->seg_inv[D];
-    gd.seg = s->seg_dis[D];
-    int gx = 0, gy = 0;
-    if (g.inviscid) {
-      sweep_march_blocks<D>(gi, gx, gy);
-      hipLaunchKernelGGL(k_march_adj_inv<D>, dim3(gx, gy), dim3(kBlock), 0, st, P, Rbar, rscale, s->Wbar, gi);
-    }
-    sweep_march_blocks<D>(gd, gx, gy);
-    if (g.viscous && g.heat)
-      hipLaunchKernelGGL((k_march_adj_dis<D, PHYS_NS>), dim3(gx, gy), dim3(kBlock), 0, sd, P, Rbar, rscale, s->Wbar,
-                         s->Dbar, gd);
-    else if (g.viscous || g.heat)
-      hipLaunchKernelGGL((k_march_adj_dis<D, PHYS_ANY>), dim3(gx, gy), dim3(kBlock), 0, sd, P, Rbar, rscale, s->Wbar,
-                         s->Dbar, gd);
+    const long long slots = dis ? (g.n[0] + 1 + kXDisCtx) * rows : (g.n[0] + 6) * rows;
+    const int per_wave = dis ? kXDisNew : kXInvNew;
+    return (int)(((slots + per_wave - 1) / per_wave + 3) / 4);
   }
+  const int seg = dis ? s->seg_dis[D] : s->seg_inv[D];
+  const long long cols = (long long)g.n[3 - D] * ((g.n[D] + seg - 1) / seg);
+  return (int)((g.n[0] + 63) / 64 * ((cols + 3) / 4));
+}
+
+// The face reverses: the inviscid parts on st, the dissipative ones on sd.
+template <int PHYS>
+static void launch_faces_adj(cfd_solver* s, const double* P, const double* Rbar, double rscale, hipStream_t st,
+                             hipStream_t sd) {
+  const Geom& g = s->g;
+  const dim3 blk(kBlock);
+  if (g.inviscid) {
+    if (g.act[0]) hipLaunchKernelGGL(k_xadj_inv, dim3(adj_blocks(s, 0, false)), blk, 0, st, P, Rbar, rscale, s->Wbar, g);
+    if (g.act[1]) hipLaunchKernelGGL(k_march_adj_inv<1>, dim3(adj_blocks(s, 1, false)), blk, 0, st, P, Rbar, rscale, s->Wbar, g, s->seg_inv[1]);
+    if (g.act[2]) hipLaunchKernelGGL(k_march_adj_inv<2>, dim3(adj_blocks(s, 2, false)), blk, 0, st, P, Rbar, rscale, s->Wbar, g, s->seg_inv[2]);
+  }
+  if constexpr (PHYS != PHYS_EULER) {
+    if (g.act[0]) hipLaunchKernelGGL(k_xadj_dis<PHYS>, dim3(adj_blocks(s, 0, true)), blk, 0, sd, P, Rbar, rscale, s->Wbar, s->Dbar, g);
+    if (g.act[1]) hipLaunchKernelGGL((k_march_adj_dis<1, PHYS>), dim3(adj_blocks(s, 1, true)), blk, 0, sd, P, Rbar, rscale, s->Wbar, s->Dbar, g, s->seg_dis[1]);
+    if (g.act[2]) hipLaunchKernelGGL((k_march_adj_dis<2, PHYS>), dim3(adj_blocks(s, 2, true)), blk, 0, sd, P, Rbar, rscale, s->Wbar, s->Dbar, g, s->seg_dis[2]);
+  }
+}
+
+// The same in one launch.
+template <int PHYS>
+static void launch_faces_adj_one(cfd_solver* s, const double* P, const double* Rbar, double rscale, hipStream_t st) {
+  const Geom& g = s->g;
+  AdjBlocks ab;
+  int end = 0, n = 0;
+  auto add = [&](int D, bool dis) {
+    if (dis ? PHYS != PHYS_EULER : g.inviscid != 0) end += adj_blocks(s, D, dis);
+    ab.end[n++] = end;
+  };
+  add(1, false);
+  add(2, false);
+  add(1, true);
+  add(2, true);
+  add(0, false);
+  add(0, true);
+  for (int d = 0; d < 3; ++d) {
+    ab.seg_inv[d] = s->seg_inv[d];
+    ab.seg_dis[d] = s->seg_dis[d];
+  }
+  if (end) hipLaunchKernelGGL(k_faces_adj<PHYS>, dim3(end), dim3(kBlock), 0, st, P, Rbar, rscale, s->Wbar, s->Dbar, g, ab);
+}
+
+// f gets the flux terms the dissipative reverses are compiled for.
+template <class F>
+static void with_adj_phys(const Geom& g, F&& f) {
+  if (!g.viscous && !g.heat) f(Const<PHYS_EULER>{});
+  else if (g.viscous && g.heat) f(Const<PHYS_NS>{});
+  else f(Const<PHYS_ANY>{});
 }
 
 // out.out = (the combination in out) + (dR/dU(U))^T (rscale Rbar) at the
 // interior cells, with U given by its primitives P (padded, halos included;
 // rho, u, v, w, p are read).
-// Padded cells from which a right-hand-side adjoint uses its second stream.
+// Padded cells from which the face reverses run as a launch per axis and part,
+// on two streams; below, in one launch on one stream, where the reverses' own
+// latency rules: a kept step and its adjoint at 20^3 298 -> 180 us in one
+// launch, 40^3 412 -> 304, 100^2 180 -> 120, 300^2 264 -> 216, 64^3 666 -> 650,
+// but 80^3 1093 -> 1104, 128^3 3519 -> 3661.
 constexpr long long kAdjForkMinCells = 1LL << 18;
 
-// Clear the accumulators Wbar, Dbar (graph-safe fill kernels).
-static void enqueue_clear_adj(cfd_solver* s, double* Wb, double* Db, hipStream_t st) {
-  hipLaunchKernelGGL(k_zero, dim3(grid_for(6 * s->ncell)), dim3(kBlock), 0, st, Wb, 6 * s->ncell);
-  if (s->g.viscous)
-    hipLaunchKernelGGL(k_zero, dim3(grid_for(kGradComps * s->ncell)), dim3(kBlock), 0, st, Db,
-                       kGradComps * s->ncell);
+// Clear the accumulators Wbar and Dbar, which are one array (graph-safe fill kernel).
+static void enqueue_clear_adj(cfd_solver* s, double* Wb, hipStream_t st) {
+  const long long n = (s->g.viscous ? 6 + kGradComps : 6) * s->ncell;
+  hipLaunchKernelGGL(k_zero, dim3(grid_for(n)), dim3(kBlock), 0, st, Wb, n);
 }
 
 // cleared: s->Wbar, s->Dbar are already zero (cleared on the side stream by
@@ -695,14 +722,12 @@ static cfd_status enqueue_rhs_adjoint(cfd_solver* s, const double* P, const doub
                                       double rscale, const AdjOut& out, hipStream_t st, bool cleared = false,
                                       bool clear_next = false) {
   const Geom& g = s->g;
-  // Small grids (a few microseconds per kernel) keep everything on one
-  // stream: there the fork and join cost more than the overlap gains, and
-  // each call clears its own pair.
+  // on one stream each call clears its own pair
   const bool big = s->ncell >= kAdjForkMinCells;
   cleared = cleared && big;
   clear_next = clear_next && big;
   if (!cleared) {
-    enqueue_clear_adj(s, s->Wbar, s->Dbar, st);
+    enqueue_clear_adj(s, s->Wbar, st);
     CFD_LAUNCHED();
   }
   // the inviscid reverses (FP64-bound) and the dissipative ones (bound by
@@ -732,25 +757,25 @@ static cfd_status enqueue_rhs_adjoint(cfd_solver* s, const double* P, const doub
       CFD_LAUNCHED();
     }
   } else {
-    if (g.act[0]) launch_face_adj<0>(s, P, Rbar, rscale, st, sd);
-    if (g.act[1]) launch_face_adj<1>(s, P, Rbar, rscale, st, sd);
-    if (g.act[2]) launch_face_adj<2>(s, P, Rbar, rscale, st, sd);
+    with_adj_phys(g, [&](auto phys) {
+      constexpr int PHYS = decltype(phys)::value;
+      if (s->ncell < kAdjForkMinCells) launch_faces_adj_one<PHYS>(s, P, Rbar, rscale, st);
+      else launch_faces_adj<PHYS>(s, P, Rbar, rscale, st, sd);
+    });
     CFD_LAUNCHED();
   }
   if (fork) {
     if (clear_next) {
-      enqueue_clear_adj(s, s->Wbar2, s->Dbar2, s->side);
+      enqueue_clear_adj(s, s->Wbar2, s->side);
       CFD_LAUNCHED();
     }
     CFD_HIP(hipEventRecord(s->ev_join, s->side));
     CFD_HIP(hipStreamWaitEvent(st, s->ev_join, 0));
   }
-  if (g.viscous) {
-    hipLaunchKernelGGL(k_adj_dbar_halo, dim3(halo_blocks(g)), dim3(kBlock), 0, st, (const double*)s->Dbar, s->Wbar,
-                       g);
-    CFD_LAUNCHED();
-  }
-  hipLaunchKernelGGL(k_adj_halo, dim3(halo_blocks(g)), dim3(kBlock), 0, st, s->Wbar, g);
+  if (g.viscous)
+    hipLaunchKernelGGL(k_adj_halo<true>, dim3(halo_blocks(g)), dim3(kBlock), 0, st, s->Wbar, (const double*)s->Dbar, g);
+  else
+    hipLaunchKernelGGL(k_adj_halo<false>, dim3(halo_blocks(g)), dim3(kBlock), 0, st, s->Wbar, (const double*)nullptr, g);
   CFD_LAUNCHED();
   hipLaunchKernelGGL(k_adj_fold, plane_grid(g), dim3(kBlock), 0, st, P, (const double*)s->Wbar,
                      (const double*)(g.viscous ? s->Dbar : nullptr), out, g);
@@ -873,7 +898,7 @@ void cfd_destroy(cfd_solver* s) {
   if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);
   if (s->ev_join) (void)hipEventDestroy(s->ev_join);
   double* bufs[] = {s->U1, s->U2,   s->Pb[0], s->Pb[1], s->Pb[2], s->Racc,    s->A1,
-                    s->A2, s->A3,   s->Wbar,  s->Dbar,  s->Wbar2, s->Dbar2, s->partial, s->nna, s->nntape};
+                    s->A2, s->A3,   s->Wbar,  s->Wbar2, s->partial, s->nna, s->nntape};
   for (double* b : bufs)
     if (b) (void)hipFree(b);
   if (s->ctl) (void)hipFree(s->ctl);

@@ -13,12 +13,10 @@
 //      (one atomic per cell and variable). y and z faces
 //      (k_march_adj_inv/dis): marching wavefronts, the reverse of the forward
 //      marches. The inviscid and dissipative reverses run on two streams;
-//   3. k_adj_dbar_halo (viscous): the transposed centred differences of
-//      Dbar, added to Wbar at the halo cells (k_adj_fold adds the interior
-//      cells' share);
-//   4. k_adj_halo: the transposed halo fill, every halo cell's Wbar added to
-//      its interior source cell;
-//   5. k_adj_fold: per interior cell, the transposed primitive map at the
+//   3. k_adj_halo: the transposed halo fill, every halo cell's Wbar (viscous:
+//      with its transposed centred differences of Dbar; k_adj_fold adds the
+//      interior cells' share) added to its interior source cell;
+//   4. k_adj_fold: per interior cell, the transposed primitive map at the
 //      state (from its primitives) gives Ubar.
 // The atomics make the summation order, and so the last bits, vary between
 // runs; everything else is deterministic.
@@ -153,10 +151,10 @@ __device__ __forceinline__ int dbar_comp(int k) {
 // supply shuffles and collect sums.
 constexpr int kXInvNew = 60;
 
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) k_xadj_inv(const double* P, const double* __restrict__ Rbar,
-                                                     double rscale, double* Wbar, Geom g) {
+__device__ __forceinline__ void xadj_inv_body(const double* P, const double* __restrict__ Rbar, double rscale,
+                                              double* Wbar, const Geom& g, int block) {
   const int lane = threadIdx.x & 63;
-  const int wave = (xcd_major_block(blockIdx.x, gridDim.x) * kBlock + (int)threadIdx.x) >> 6;
+  const int wave = (block * kBlock + (int)threadIdx.x) >> 6;
   const int n = g.n[0];
   const int S = n + 6;
   const int total = S * g.n[1] * g.n[2];
@@ -211,6 +209,11 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
   }
 }
 
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
+k_xadj_inv(const double* P, const double* __restrict__ Rbar, double rscale, double* Wbar, Geom g) {
+  xadj_inv_body(P, Rbar, rscale, Wbar, g, xcd_major_block(blockIdx.x, gridDim.x));
+}
+
 // Dissipative part: slot s of a row is face f = s - 3 (f = -3 .. n), and its
 // lane loads the inputs of cell f+1 (u, v, w and the four tangential
 // derivatives). Face f takes those of cells f-2 .. f+1 from itself and the
@@ -222,10 +225,10 @@ constexpr int kXDisCtx = 3;
 constexpr int kXDisNew = 64 - kXDisCtx;
 
 template <int PHYS>
-__global__ void __launch_bounds__(kBlock) k_xadj_dis(const double* __restrict__ P, const double* __restrict__ Rbar,
-                                                     double rscale, double* Wbar, double* Dbar, Geom g) {
+__device__ __forceinline__ void xadj_dis_body(const double* __restrict__ P, const double* __restrict__ Rbar,
+                                              double rscale, double* Wbar, double* Dbar, const Geom& g, int block) {
   const int lane = threadIdx.x & 63;
-  const int wave = (xcd_major_block(blockIdx.x, gridDim.x) * kBlock + (int)threadIdx.x) >> 6;
+  const int wave = (block * kBlock + (int)threadIdx.x) >> 6;
   const int n = g.n[0];
   const int S = n + 1 + kXDisCtx;
   const int total = S * g.n[1] * g.n[2];
@@ -314,6 +317,12 @@ __global__ void __launch_bounds__(kBlock) k_xadj_dis(const double* __restrict__ 
   }
 }
 
+template <int PHYS>
+__global__ void __launch_bounds__(kBlock) k_xadj_dis(const double* __restrict__ P, const double* __restrict__ Rbar,
+                                                     double rscale, double* Wbar, double* Dbar, Geom g) {
+  xadj_dis_body<PHYS>(P, Rbar, rscale, Wbar, Dbar, g, xcd_major_block(blockIdx.x, gridDim.x));
+}
+
 // ---------------------------------------------------------------------------
 // Marching face reverses along y and z (AX = 1, 2), the reverse counterparts
 // of the forward marches: a wavefront holds 64 consecutive x of one column
@@ -330,12 +339,11 @@ __global__ void __launch_bounds__(kBlock) k_xadj_dis(const double* __restrict__ 
 // row's end in lanes without a cell). The segment of cells [s0, s1) owns faces
 // s0 .. s1-1, and the last segment also face n (the upper boundary).
 template <int AX>
-__device__ __forceinline__ bool march_adj_column(const Geom& g, int& i, int& o, int& s0, int& fe) {
+__device__ __forceinline__ bool march_adj_column(const Geom& g, int block, int sl, int& i, int& o, int& s0, int& fe) {
   constexpr int OT = AX == 1 ? 2 : 1;
-  const int logical = xcd_major_block(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
-  const int by = logical / gridDim.x, bx = logical - by * gridDim.x;
+  const int gx = (g.n[0] + 63) / 64;
+  const int by = block / gx, bx = block - by * gx;
   i = bx * 64 + (int)(threadIdx.x & 63);
-  const int sl = g.seg;
   const int nseg = (g.n[AX] + sl - 1) / sl;
   const int col = uniform(by * (kBlock >> 6) + wave_in_block());
   if (col >= g.n[OT] * nseg) return false;
@@ -365,12 +373,11 @@ __device__ __forceinline__ long long march_adj_cell(const Geom& g, int i, int o,
 constexpr int kMarchRing = 5;
 
 template <int AX>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
-k_march_adj_inv(const double* __restrict__ P, const double* __restrict__ Rbar, double rscale, double* Wbar,
-                Geom g) {
-  __shared__ double ring[kMarchRing * 5 * kBlock];
+__device__ __forceinline__ void march_adj_inv_body(const double* __restrict__ P, const double* __restrict__ Rbar,
+                                                   double rscale, double* Wbar, const Geom& g, int seg, int block,
+                                                   double* ring) {
   int i, o, s0, fe;
-  if (!march_adj_column<AX>(g, i, o, s0, fe)) return;
+  if (!march_adj_column<AX>(g, block, seg, i, o, s0, fe)) return;
   const int tid = threadIdx.x;
 #pragma unroll
   for (int e = 0; e < kMarchRing * 5; ++e) ring[e * kBlock + tid] = 0.0;
@@ -463,17 +470,25 @@ k_march_adj_inv(const double* __restrict__ P, const double* __restrict__ Rbar, d
   }
 }
 
+template <int AX>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
+k_march_adj_inv(const double* __restrict__ P, const double* __restrict__ Rbar, double rscale, double* Wbar, Geom g,
+                int seg) {
+  __shared__ double ring[kMarchRing * 5 * kBlock];
+  march_adj_inv_body<AX>(P, Rbar, rscale, Wbar, g, seg, xcd_major_block(blockIdx.x, gridDim.x), ring);
+}
+
 // Dissipative part (viscous and heat flux). Face f reads window cells
 // f-2 .. f+1 (u, v, w and the tangential sums of each, formed from P as in the
 // forward marches); the adjoints of those inputs (Wbar u, v, w, T~ and Dbar)
 // are summed in registers and cell f-2 is added to memory after face f.
 template <int AX, int PHYS>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
-k_march_adj_dis(const double* __restrict__ P, const double* __restrict__ Rbar, double rscale, double* Wbar,
-                double* Dbar, Geom g) {
+__device__ __forceinline__ void march_adj_dis_body(const double* __restrict__ P, const double* __restrict__ Rbar,
+                                                   double rscale, double* Wbar, double* Dbar, const Geom& g, int seg,
+                                                   int block) {
   constexpr int T1 = (AX + 1) % 3, T2 = (AX + 2) % 3;
   int i, o, s0, fe;
-  if (!march_adj_column<AX>(g, i, o, s0, fe)) return;
+  if (!march_adj_column<AX>(g, block, seg, i, o, s0, fe)) return;
   const long long st = g.s[AX], vs = g.vs;
   const int n = g.n[AX];
   const double gs_scale = rscale * g.idx[AX];
@@ -584,6 +599,41 @@ k_march_adj_dis(const double* __restrict__ P, const double* __restrict__ Rbar, d
   for (int m = 0; m < 3; ++m) put(c + m * st, ub[m], tb[m]);
 }
 
+template <int AX, int PHYS>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
+k_march_adj_dis(const double* __restrict__ P, const double* __restrict__ Rbar, double rscale, double* Wbar,
+                double* Dbar, Geom g, int seg) {
+  march_adj_dis_body<AX, PHYS>(P, Rbar, rscale, Wbar, Dbar, g, seg, xcd_major_block(blockIdx.x, gridDim.x));
+}
+
+// All face reverses in one launch, for grids whose reverses take some
+// microseconds each: block ranges in the order y and z inviscid, y and z
+// dissipative, x inviscid, x dissipative (the longest chains first). One after
+// another they would each leave most of the chip idle.
+struct AdjBlocks {
+  int end[6];  // cumulative
+  int seg_inv[3], seg_dis[3];
+};
+
+template <int PHYS>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
+k_faces_adj(const double* __restrict__ P, const double* __restrict__ Rbar, double rscale, double* Wbar, double* Dbar,
+            Geom g, AdjBlocks ab) {
+  __shared__ double ring[kMarchRing * 5 * kBlock];
+  const int b = blockIdx.x;
+  if (b < ab.end[0]) return march_adj_inv_body<1>(P, Rbar, rscale, Wbar, g, ab.seg_inv[1], b, ring);
+  if (b < ab.end[1]) return march_adj_inv_body<2>(P, Rbar, rscale, Wbar, g, ab.seg_inv[2], b - ab.end[0], ring);
+  if constexpr (PHYS != PHYS_EULER) {
+    if (b < ab.end[2])
+      return march_adj_dis_body<1, PHYS>(P, Rbar, rscale, Wbar, Dbar, g, ab.seg_dis[1], b - ab.end[1]);
+    if (b < ab.end[3])
+      return march_adj_dis_body<2, PHYS>(P, Rbar, rscale, Wbar, Dbar, g, ab.seg_dis[2], b - ab.end[2]);
+  }
+  if (b < ab.end[4]) return xadj_inv_body(P, Rbar, rscale, Wbar, g, b - ab.end[3]);
+  if constexpr (PHYS != PHYS_EULER)
+    xadj_dis_body<PHYS>(P, Rbar, rscale, Wbar, Dbar, g, b - ab.end[4]);
+}
+
 // Transposed centred differences of Dbar at padded cell cc (coordinates q),
 // added to wb[1..3]: phi_bar(m) += (Dbar(m+2) - 8 Dbar(m+1) + 8 Dbar(m-1) -
 // Dbar(m-2)) / (12 dx_t), where the adjoint of du_t/dx_t is the sum of the
@@ -600,14 +650,15 @@ __device__ __forceinline__ void fold_dbar(const Geom& g, const double* __restric
     const int lo = -g.h[t], hi = g.n[t] + g.h[t];
     const int y = q[t];
     const double i12 = g.idx[t] * (1.0 / 12.0);
+    // out of the padded block (CHECK): the cell's own entry with weight 0, so
+    // that all loads go out together
+    const bool h2 = !CHECK || y + 2 < hi, h1 = !CHECK || y + 1 < hi, l1 = !CHECK || y - 1 >= lo, l2 = !CHECK || y - 2 >= lo;
+    const long long oh2 = h2 ? 2 * st : 0, oh1 = h1 ? st : 0, ol1 = l1 ? st : 0, ol2 = l2 ? 2 * st : 0;
     auto diff = [&](int comp) {
       const double* Db = Dbar + comp * g.vs + cc;
-      double acc = 0.0;
-      if (!CHECK || y + 2 < hi) acc += Db[2 * st];
-      if (!CHECK || y + 1 < hi) acc -= 8.0 * Db[st];
-      if (!CHECK || y - 1 >= lo) acc += 8.0 * Db[-st];
-      if (!CHECK || y - 2 >= lo) acc -= Db[-2 * st];
-      return acc;
+      const double x[4] = {Db[oh2], Db[oh1], Db[-ol1], Db[-ol2]};
+      if (!CHECK) return fma(8.0, x[2] - x[1], x[0] - x[3]);
+      return (h2 ? x[0] : 0.0) - (h1 ? 8.0 * x[1] : 0.0) + (l1 ? 8.0 * x[2] : 0.0) - (l2 ? x[3] : 0.0);
     };
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -619,39 +670,31 @@ __device__ __forceinline__ void fold_dbar(const Geom& g, const double* __restric
   }
 }
 
-// Transposed centred differences of Dbar at the halo cells: Wbar(u, v, w)[c]
-// += the adjoint the tangential derivatives give halo cell c, before
-// k_adj_halo adds the halo cells to their interior sources (the interior
-// cells' own share is formed in k_adj_fold). One thread per halo cell, each
-// updating its own cell.
-__global__ void __launch_bounds__(kBlock) k_adj_dbar_halo(const double* __restrict__ Dbar, double* __restrict__ Wbar,
-                                                          Geom g) {
-  int i, j, k;
-  if (!halo_cell(g, (long long)blockIdx.x * kBlock + threadIdx.x, i, j, k)) return;
-  const long long c = cell_at(g, i, j, k);
-  const int q[3] = {i, j, k};
-  double wb[4] = {0.0, 0.0, 0.0, 0.0};
-  fold_dbar<true>(g, Dbar, c, q, wb);
-#pragma unroll
-  for (int v = 1; v < 4; ++v) Wbar[v * g.vs + c] += wb[v];
-}
-
 // Transposed halo fill of the primitive adjoints: every halo cell adds its
-// adjoint to its interior source cell (the wall-normal velocity's through the
-// image's sign at a reflecting wall), with atomics, since an edge cell can
-// own several halo cells. One thread per halo cell, numbered as in the
-// primitive halo refresh.
-__global__ void __launch_bounds__(kBlock) k_adj_halo(double* Wbar, Geom g) {
+// adjoint - with Dbar its share of the transposed centred differences too
+// (the interior cells' own share is formed in k_adj_fold) - to its interior
+// source cell (the wall-normal velocity's through the image's sign at a
+// reflecting wall), with atomics, since an edge cell can own several halo
+// cells. One thread per halo cell, numbered as in the primitive halo refresh.
+template <bool DBAR>
+__global__ void __launch_bounds__(kBlock) k_adj_halo(double* Wbar, const double* __restrict__ Dbar, Geom g) {
   int i, j, k;
   if (!halo_cell(g, (long long)blockIdx.x * kBlock + threadIdx.x, i, j, k)) return;
   const int si = bc_source(i, g.n[0], g.bc[0], g.bc[1]);
   const int sj = bc_source(j, g.n[1], g.bc[2], g.bc[3]);
   const int sk = bc_source(k, g.n[2], g.bc[4], g.bc[5]);
   const long long c = cell_at(g, i, j, k), s = cell_at(g, si, sj, sk);
+  double wb[6];
+#pragma unroll
+  for (int v = 0; v < 6; ++v) wb[v] = Wbar[v * g.vs + c];
+  if constexpr (DBAR) {
+    const int q[3] = {i, j, k};
+    fold_dbar<true>(g, Dbar, c, q, wb);
+  }
   const double f[6] = {1.0, bc_sign(i, g.n[0], g.bc[0], g.bc[1]), bc_sign(j, g.n[1], g.bc[2], g.bc[3]),
                        bc_sign(k, g.n[2], g.bc[4], g.bc[5]), 1.0, 1.0};
 #pragma unroll
-  for (int v = 0; v < 6; ++v) atomic_add(Wbar + v * g.vs + s, f[v] * Wbar[v * g.vs + c]);
+  for (int v = 0; v < 6; ++v) atomic_add(Wbar + v * g.vs + s, f[v] * wb[v]);
 }
 
 // The destination of a right-hand-side adjoint: out = a X + b Y + c Z + the
@@ -668,7 +711,7 @@ struct AdjOut {
   int zero_halo;
 };
 
-// Per cell s, after k_adj_halo (and, with viscous fluxes, k_adj_dbar_halo):
+// Per cell s, after k_adj_halo:
 // Wbar[s] plus (Dbar non-null) the transposed centred differences of Dbar at
 // s, then the transposed primitive map at the state, given by its primitives
 // P[s] (rho, u, v, w, p), into the destination o.
