@@ -185,6 +185,15 @@ cfd_status cfd_advance_fixed(cfd_solver* s, double* U, int32_t n_steps, double d
  * device when the solver holds a captured step (which it then discards). */
 cfd_status cfd_set_nn_weights(cfd_solver* s, const double* theta, double* theta_bar);
 
+/* Gradient of a mean squared error of primitives (the loss of §7.4), added to
+ * a cotangent: Ubar += d/dU [ scale * mean((W(U) - Wt)^2) ], W = (rho, u, v, p)
+ * of the interior cells of U, the mean over the cells and the four variables.
+ * Wt holds 4 blocks of interior cells [nz][ny][nx]; U and Ubar are padded
+ * states, of which interior cells are read and updated. Ubar must not alias U
+ * or Wt (CFD_EINVAL). */
+cfd_status cfd_prim_mse_adjoint(cfd_solver* s, const double* U, const double* Wt, double scale, double* Ubar,
+                                void* stream);
+
 /* Discrete adjoint of cfd_rhs: Ubar += (dR/dU)^T Rbar, evaluated at U
  * (interior cells of Rbar are read; its halo is ignored). The transposed halo
  * fill folds halo contributions back into their source cells, so the halo

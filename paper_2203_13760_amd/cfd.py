@@ -49,7 +49,7 @@ EXPORTS = (
     "cfd_compute_dt", "cfd_rk3_step", "cfd_advance", "cfd_advance_fixed", "cfd_rhs_adjoint",
     "cfd_rk3_step_adjoint", "cfd_rk3_step_stages", "cfd_rk3_step_adjoint_stages", "cfd_rk3_step_prims",
     "cfd_rk3_step_adjoint_prims", "cfd_profile_stage", "cfd_check", "cfd_last_error",
-    "cfd_set_nn_weights", "cfd_rk3_step_noalloc",
+    "cfd_set_nn_weights", "cfd_rk3_step_noalloc", "cfd_prim_mse_adjoint",
     "cfd_batch_create", "cfd_batch_destroy", "cfd_batch_footprint", "cfd_batch_add", "cfd_batch_remove",
     "cfd_batch_state", "cfd_batch_step", "cfd_batch_finish", "cfd_batch_copy_state", "cfd_batch_count",
 )
@@ -89,6 +89,7 @@ def load():
         "cfd_rk3_step_adjoint_prims": ([vp, dp, C.c_double, dp, dp, vp], st),
         "cfd_profile_stage": ([vp, dp, C.c_int32, C.POINTER(C.c_double), vp], st),
         "cfd_set_nn_weights": ([vp, dp, dp], st),
+        "cfd_prim_mse_adjoint": ([vp, dp, dp, C.c_double, dp, vp], st),
         "cfd_rk3_step_noalloc": ([cfgp, dp, C.c_double, dp, vp], st),
         "cfd_check": ([vp, C.POINTER(C.c_int32)], st),
         "cfd_last_error": ([], C.c_char_p),
@@ -225,6 +226,11 @@ def cfd_rk3_step_prims(h, U, dt, P_out, stream=None):
 def cfd_rk3_step_adjoint_prims(h, P, dt, Ubar_np1, Ubar_n, stream=None):
     _check(load().cfd_rk3_step_adjoint_prims(h, _ptr(P), float(dt), _ptr(Ubar_np1), _ptr(Ubar_n),
                                              _stream(stream)))
+
+
+def cfd_prim_mse_adjoint(h, U, Wt, scale, Ubar, stream=None):
+    """Ubar += d/dU [scale * mean((W(U) - Wt)^2)], W = (rho, u, v, p), Wt (4, nz, ny, nx)."""
+    _check(load().cfd_prim_mse_adjoint(h, _ptr(U), _ptr(Wt), float(scale), _ptr(Ubar), _stream(stream)))
 
 
 def cfd_set_nn_weights(h, theta, theta_bar=None):

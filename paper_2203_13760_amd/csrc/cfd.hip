@@ -751,9 +751,11 @@ static cfd_status enqueue_rhs_adjoint(cfd_solver* s, const double* P, const doub
                        s->tape, ax);
     CFD_LAUNCHED();
     if (s->nnbar) {
-      hipLaunchKernelGGL(k_nn_wgrad, dim3(kNNRows * kNNChunks), dim3(kBlock), 0, st, s->tape);
-      hipLaunchKernelGGL(k_nn_wgrad_sum, dim3((kNNParams + kBlock - 1) / kBlock), dim3(kBlock), 0, st,
-                         (const double*)s->tape.part, s->nnbar);
+      const int per = nn_chunk_faces(s->tape.F);
+      const int chunks = (int)((s->tape.F + per - 1) / per);
+      hipLaunchKernelGGL(k_nn_wgrad, dim3(kNNJobs * chunks), dim3(64), 0, st, s->tape, per);
+      hipLaunchKernelGGL(k_nn_wgrad_sum, dim3((kNNParams + 63) / 64), dim3(64), 0, st, (const double*)s->tape.part,
+                         s->nnbar, chunks);
       CFD_LAUNCHED();
     }
   } else {
@@ -1113,6 +1115,16 @@ cfd_status cfd_rk3_step_adjoint(cfd_solver* s, const double* Un, double dt, cons
   if ((rc = enqueue_fluxes(s, s->Pb[1], io, true, st))) return rc;
   const double* const Pk[3] = {s->Pb[0], s->Pb[1], s->Pb[2]};
   return enqueue_step_reverse(s, Pk, dt, Ubar_np1, Ubar_n, st);
+}
+
+cfd_status cfd_prim_mse_adjoint(cfd_solver* s, const double* U, const double* Wt, double scale, double* Ubar,
+                                void* stream) {
+  if (!s || !U || !Wt || !Ubar) return fail(CFD_EINVAL, "NULL argument");
+  if (Ubar == U || Ubar == Wt) return fail(CFD_EINVAL, "Ubar must not alias the inputs");
+  hipLaunchKernelGGL(k_prim_mse_adj, dim3(grid_for(s->nint, 1LL << 31)), dim3(kBlock), 0, (hipStream_t)stream, U, Wt,
+                     2.0 * scale / (4.0 * (double)s->nint), Ubar, s->g);
+  CFD_LAUNCHED();
+  return CFD_OK;
 }
 
 cfd_status cfd_set_nn_weights(cfd_solver* s, const double* theta, double* theta_bar) {

@@ -16,7 +16,7 @@ __host__ __device__ __forceinline__ void weno3_rev(double a, double b, double c,
   const double s0 = e0 * e0, s1 = e1 * e1;
   const double w0 = s1, w1 = 2.0 * s0;
   const double A = 3.0 * b - a, B = b + c;
-  const double iD = 1.0 / (2.0 * (w0 + w1));
+  const double iD = rcp_nr(2.0 * (w0 + w1));
   const double q = (w0 * A + w1 * B) * iD;
   // reverse
   const double Nb = qbar * iD;

@@ -304,15 +304,14 @@ class RusanovNNTrainer:
         output against the targets T; the library adds the weight gradient
         (loss scale 1) to theta_bar. A fixed launch sequence with no host
         synchronisation and no allocation (capturable)."""
-        sv, case = self.solver, self.case
+        sv = self.solver
         for k in range(1, self.n_unroll + 1):
             self.S[k].copy_(self.S[k - 1])
-            sv.step(self.S[k], self.dt)
+            sv.step_fixed(self.S[k], self.dt)
         ub, ub_prev = self.ubar
         ub.zero_()
         for k in range(self.n_unroll, 0, -1):
-            g = primitive_mse_grad(interior(case, self.S[k]), self.T[k - 1], self.gamma, 1.0 / self.n_unroll)
-            interior(case, ub).add_(g)
+            sv.prim_mse_adjoint(self.S[k], self.T[k - 1], 1.0 / self.n_unroll, ub)
             sv.step_adjoint(self.S[k - 1], self.dt, ub, ub_prev)
             ub, ub_prev = ub_prev, ub
 

@@ -86,6 +86,11 @@ class Solver:
         cfd.cfd_rk3_step(self.h, U, float(dt), out)
         return out
 
+    def step_fixed(self, U, dt):
+        """One step of the given size in place (step without the scalar it returns)."""
+        cfd.cfd_rk3_step(self.h, U, float(dt), None)
+        return U
+
     def advance(self, U, n_steps, t_end=0.0, t=None):
         """n_steps CFL steps in place (stopping at t_end > 0); t is a device scalar."""
         if t is None:
@@ -130,6 +135,12 @@ class Solver:
         Ubar_n = self.empty_state() if Ubar_n is None else Ubar_n
         cfd.cfd_rk3_step_adjoint_prims(self.h, P, float(dt), Ubar_np1, Ubar_n)
         return Ubar_n
+
+    def prim_mse_adjoint(self, U, Wt, scale, Ubar):
+        """Adds the gradient of scale * mean((W(U) - Wt)^2) over interior cells and
+        W = (rho, u, v, p) to Ubar (Wt: (4, nz, ny, nx))."""
+        cfd.cfd_prim_mse_adjoint(self.h, U, Wt, float(scale), Ubar)
+        return Ubar
 
     def set_nn_weights(self, theta, theta_bar=None):
         """Rusanov-NN weights (a device float64 tensor of cfd.CFD_NN_PARAMS values,
