@@ -14,6 +14,7 @@
 #include "kernels_adj.hpp"
 #include "kernels_nn.hpp"
 #include "kernels_fwd.hpp"
+#include "kernels_line.hpp"
 
 using namespace cfd;
 
@@ -549,6 +550,30 @@ static cfd_status enqueue_fill_halo(cfd_solver* s, double* U, hipStream_t st) {
   return CFD_OK;
 }
 
+// Grids whose steps run in one workgroup (k_line).
+static bool line_grid(const Geom& g) {
+  return g.act[0] && !g.act[1] && !g.act[2] && g.n[0] <= kLineCells && !g.roe && !g.nn;
+}
+
+// n steps of a line grid on U in place: launches of at most kLineSteps steps, so
+// that no kernel runs for long.
+constexpr int kLineSteps = 4096;
+static cfd_status enqueue_line(cfd_solver* s, double* U, int n, double fixed_dt, double t_end, double* t_dev,
+                               double* dt_out, hipStream_t st) {
+  const Geom& g = s->g;
+  const dim3 blk(64 * ((g.n[0] + kLineNew - 1) / kLineNew));
+  for (int done = 0; done < n; done += kLineSteps) {
+    const int k = std::min(n - done, kLineSteps);
+    with_scheme(g, [&](auto sch, auto phys) {
+      constexpr int SCH = decltype(sch)::value, PHYS = decltype(phys)::value == PHYS_EULER ? PHYS_EULER : PHYS_ANY;
+      if constexpr (SCH != SCH_ROE && SCH != SCH_W3_NN)
+        hipLaunchKernelGGL((k_line<SCH, PHYS>), dim3(1), blk, 0, st, U, g, s->ctl, k, fixed_dt, t_end, t_dev, dt_out);
+    });
+    CFD_LAUNCHED();
+  }
+  return enqueue_fill_halo(s, U, st);
+}
+
 // Replay `n` copies of a captured single-step graph on stream st. The graph
 // is re-captured when its key (pointers and scalars) changes.
 static cfd_status run_graph(cfd_solver* s, double* U, int mode, double fixed_dt, double t_end, double* t_dev,
@@ -963,6 +988,7 @@ cfd_status cfd_rk3_step(cfd_solver* s, double* U, double dt, double* dt_used_dev
   if (!std::isfinite(dt)) return fail(CFD_EINVAL, "dt must be finite");
   hipStream_t st = (hipStream_t)stream;
   const double fixed = dt > 0.0 ? dt : 0.0;
+  if (line_grid(s->g)) return enqueue_line(s, U, 1, fixed, 0.0, nullptr, dt_used_dev, st);
   cfd_status rc = enqueue_step_prologue(s, U, fixed, 0.0, nullptr, dt_used_dev, st);
   if (rc) return rc;
   if ((rc = enqueue_step(s, U, fixed, false, 0.0, nullptr, st))) return rc;
@@ -975,6 +1001,7 @@ cfd_status cfd_advance(cfd_solver* s, double* U, int32_t n_steps, double t_end, 
   if (n_steps < 0) return fail(CFD_EINVAL, "n_steps must be >= 0");
   if (n_steps == 0) return CFD_OK;
   hipStream_t st = (hipStream_t)stream;
+  if (line_grid(s->g)) return enqueue_line(s, U, n_steps, 0.0, t_end > 0.0 ? t_end : 0.0, t_dev, nullptr, st);
   cfd_status rc = run_graph(s, U, 1, 0.0, t_end > 0.0 ? t_end : 0.0, t_dev, n_steps, st);
   if (rc) return rc;
   return enqueue_fill_halo(s, U, st);
@@ -985,6 +1012,7 @@ cfd_status cfd_advance_fixed(cfd_solver* s, double* U, int32_t n_steps, double d
   if (n_steps < 0 || !(dt > 0.0) || !std::isfinite(dt)) return fail(CFD_EINVAL, "need n_steps >= 0 and dt > 0");
   if (n_steps == 0) return CFD_OK;
   hipStream_t st = (hipStream_t)stream;
+  if (line_grid(s->g)) return enqueue_line(s, U, n_steps, dt, 0.0, nullptr, nullptr, st);
   cfd_status rc = run_graph(s, U, 2, dt, 0.0, nullptr, n_steps, st);
   if (rc) return rc;
   return enqueue_fill_halo(s, U, st);
@@ -1284,6 +1312,7 @@ cfd_status cfd_rk3_step_noalloc(const cfd_config* cfg, double* U, double dt, dou
   hipLaunchKernelGGL(k_zero, dim3(1), dim3(kBlock), 0, st, base + kCflSlots, 32LL);
   CFD_LAUNCHED();
   const double fixed = dt > 0.0 ? dt : 0.0;
+  if (line_grid(s.g)) return enqueue_line(&s, U, 1, fixed, 0.0, nullptr, dt_used_dev, st);
   if ((rc = enqueue_step_prologue(&s, U, fixed, 0.0, nullptr, dt_used_dev, st))) return rc;
   if ((rc = enqueue_step(&s, U, fixed, false, 0.0, nullptr, st))) return rc;
   return enqueue_fill_halo(&s, U, st);

@@ -398,17 +398,22 @@ __device__ __forceinline__ void face_adj_nn_body(const double* __restrict__ P, c
   }
   nn_features_rev<D>(g, WL, WR, ft, fb, WLb, WRb);
   if (!has) return;
-  // WENO3-JS reverse into the stencil cells cl-1 .. cl+2, variables v = q mod 4
+  // WENO3-JS reverse into the stencil cells cl-1 .. cl+2: quarter q takes
+  // variable q, quarter 0 also variable 4
+  for (int v = q; v < 5; v += 4) {
+    double lb = WLb[0], rb = WRb[0];
 #pragma unroll
-  for (int v = 0; v < 5; ++v) {
-    if ((v & 3) != q) continue;
+    for (int m = 1; m < 5; ++m) {
+      lb = v == m ? WLb[m] : lb;
+      rb = v == m ? WRb[m] : rb;
+    }
     double* w = Wbar + v * g.vs + cl;
     const double* qv = P + v * g.vs + cl;
     const double a = qv[-st], b = qv[0], c = qv[st], d = qv[2 * st];
     double gs[4] = {0.0, 0.0, 0.0, 0.0};
-    weno3_rev(a, b, c, WLb[v], gs);
+    weno3_rev(a, b, c, lb, gs);
     double gr[3] = {0.0, 0.0, 0.0};
-    weno3_rev(d, c, b, WRb[v], gr);
+    weno3_rev(d, c, b, rb, gr);
     gs[3] += gr[0];
     gs[2] += gr[1];
     gs[1] += gr[2];
