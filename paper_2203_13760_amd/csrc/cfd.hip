@@ -960,11 +960,8 @@ cfd_status cfd_rhs(cfd_solver* s, double* U, double* R, void* stream) {
   if (!s || !U || !R) return fail(CFD_EINVAL, "NULL argument");
   if (U == R) return fail(CFD_EINVAL, "U and R must not alias");
   hipStream_t st = (hipStream_t)stream;
-  cfd_status rc;
-  if ((rc = enqueue_fill_halo(s, U, st))) return rc;
-  hipLaunchKernelGGL(k_zero, dim3(grid_for(5 * s->ncell)), dim3(kBlock), 0, st, R, 5 * s->ncell);
+  hipLaunchKernelGGL(k_prim_rhs, plane_grid(s->g), dim3(kBlock), 0, st, U, s->P, R, s->g);
   CFD_LAUNCHED();
-  if ((rc = enqueue_prim(s, U, 0, nullptr, st))) return rc;
   StageIO io{};
   io.R = R;
   io.dtp = nullptr;

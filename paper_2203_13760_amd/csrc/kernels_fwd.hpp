@@ -279,12 +279,14 @@ constexpr int kBadFace = 8;
 __device__ __forceinline__ void check_face_states(const Geom& g, bool use, double* WL, double* WR,
                                                   const double* qa, const double* qb, int& bad) {
   const bool ok = !use || (WL[0] > 0.0 && WL[4] > 0.0 && WR[0] > 0.0 && WR[4] > 0.0);
-  bad |= ok ? 0 : kBadFace;
-  if (g.safe) {
+  if (__builtin_expect(__any(!ok), 0)) {  // a branch of the whole wavefront, hardly ever taken
+    bad |= ok ? 0 : kBadFace;
+    if (g.safe) {
 #pragma unroll
-    for (int v = 0; v < 5; ++v) {
-      WL[v] = ok ? WL[v] : qa[v];
-      WR[v] = ok ? WR[v] : qb[v];
+      for (int v = 0; v < 5; ++v) {
+        WL[v] = ok ? WL[v] : qa[v];
+        WR[v] = ok ? WR[v] : qb[v];
+      }
     }
   }
 }
@@ -341,6 +343,35 @@ __global__ void __launch_bounds__(kBlock) k_prim(const double* __restrict__ U, d
                                                  double* __restrict__ partial) {
   if (step_disabled(dtp)) return;
   prim_body(U, P, g, ctl, what, partial, plane_index(g), blockIdx.y * gridDim.x + blockIdx.x);
+}
+
+// Prologue of a right-hand side in one pass over the padded grid: the
+// primitives of U, its halo cells refreshed in place from the interior cells
+// that are read for them anyway, and the halo cells of R set to zero (the
+// sweeps write R's interior).
+__global__ void __launch_bounds__(kBlock) k_prim_rhs(double* U, double* __restrict__ P, double* __restrict__ R, Geom g) {
+  const PlaneIdx q = plane_index(g);
+  if (!q.in) return;
+  const int si = bc_source(q.i, g.n[0], g.bc[0], g.bc[1]);
+  const int sj = bc_source(q.j, g.n[1], g.bc[2], g.bc[3]);
+  const int sk = bc_source(q.k, g.n[2], g.bc[4], g.bc[5]);
+  const long long s = cell_at(g, si, sj, sk), c = q.c;
+  double u[5], w[6];
+#pragma unroll
+  for (int v = 0; v < 5; ++v) u[v] = U[v * g.vs + s];
+  u[1] *= bc_sign(q.i, g.n[0], g.bc[0], g.bc[1]);
+  u[2] *= bc_sign(q.j, g.n[1], g.bc[2], g.bc[3]);
+  u[3] *= bc_sign(q.k, g.n[2], g.bc[4], g.bc[5]);
+  if (s != c) {
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      U[v * g.vs + c] = u[v];
+      R[v * g.vs + c] = 0.0;
+    }
+  }
+  cons_to_prim(g, u, w);
+#pragma unroll
+  for (int v = 0; v < 5; ++v) P[v * g.vs + c] = w[v];
 }
 
 // CFL rate maxima of a state (interior cells only), for cfd_compute_dt.
@@ -648,19 +679,18 @@ __device__ __forceinline__ void finish_prims(const StageIO& io, double smax, int
 
 // Value of x in the lane below (lane - 1) across the whole wavefront, by one
 // DPP move per 32-bit half (wavefront shift right by one lane, a VALU
-// operation instead of an LDS permute); lane 0 receives 0.
+// operation instead of an LDS permute); lane 0 receives 0 (by the bound
+// control, so that no register has to be cleared beforehand).
+__device__ __forceinline__ int dpp_shr1(int x) { return __builtin_amdgcn_update_dpp(x, x, 0x138, 0xf, 0xf, true); }
+__device__ __forceinline__ int dpp_shl1(int x) { return __builtin_amdgcn_update_dpp(x, x, 0x130, 0xf, 0xf, true); }
 __device__ __forceinline__ double lane_shr1(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x138, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x138, 0xf, 0xf, false);
-  return __hiloint2double(hi, lo);
+  return __hiloint2double(dpp_shr1(__double2hiint(x)), dpp_shr1(__double2loint(x)));
 }
 
 // Value of x in the lane above (lane + 1), wavefront shift left by one lane;
 // lane 63 receives 0.
 __device__ __forceinline__ double lane_shl1(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x130, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x130, 0xf, 0xf, false);
-  return __hiloint2double(hi, lo);
+  return __hiloint2double(dpp_shl1(__double2hiint(x)), dpp_shl1(__double2loint(x)));
 }
 
 // x sweep: every interior row holds kXCtx context slots followed by its nx+1

@@ -89,9 +89,8 @@ __host__ __device__ __forceinline__ void weno5_pair_rev(double a, double b, doub
   const double sL = eL * eL, sC = eC * eC, sR = eR * eR;
   const double pCR = sC * sR, pLC = sL * sC;
   const double w1 = 6.0 * (sL * sR), w2 = 3.0 * pLC, v2 = 3.0 * pCR;
-  const double m3 = 3.0 * dm, p3 = 3.0 * dp;
-  const double X0 = fma(2.0, Db, m3), X1 = fma(2.0, dp, dm), X2 = p3 - Dd;
-  const double Y0 = fma(2.0, Dd, -p3), Y1 = fma(2.0, dm, dp), Y2 = m3 + Db;
+  const double X2 = fma(3.0, dp, -Dd), Y2 = fma(3.0, dm, Db);
+  const double X0 = Y2 + Db, X1 = fma(2.0, dp, dm), Y0 = Dd - X2, Y1 = fma(2.0, dm, dp);
   const double nr = fma(pCR, X0, fma(w1, X1, w2 * X2));
   const double nl = fma(pLC, Y0, -fma(w1, Y1, v2 * Y2));
   const double dr = pCR + (w1 + w2), dl = pLC + (w1 + v2);
