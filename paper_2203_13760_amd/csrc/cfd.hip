@@ -736,7 +736,7 @@ constexpr long long kAdjForkMinCells = 1LL << 18;
 // Clear the accumulators Wbar and Dbar, which are one array (graph-safe fill kernel).
 static void enqueue_clear_adj(cfd_solver* s, double* Wb, hipStream_t st) {
   const long long n = (s->g.viscous ? 6 + kGradComps : 6) * s->ncell;
-  hipLaunchKernelGGL(k_zero, dim3(grid_for(n)), dim3(kBlock), 0, st, Wb, n);
+  hipLaunchKernelGGL(k_zero, dim3(grid_for((n + 1) / 2, kZeroBlocks)), dim3(kBlock), 0, st, Wb, n);
 }
 
 // cleared: s->Wbar, s->Dbar are already zero (cleared on the side stream by

@@ -1372,11 +1372,21 @@ __host__ __device__ __forceinline__ void sweep_march_blocks(const Geom& g, int& 
 // tangential stencil (whose z neighbours lie a plane apart) across a face.
 constexpr int kSweepAxes[3] = {1, 2, 0};
 
-// Zero a buffer (graph-safe replacement for a memset node).
+// Zero a buffer (graph-safe replacement for a memset node), 16 bytes a store
+// where the buffer is aligned to them. Launched with at most kZeroBlocks
+// blocks: bound by the writes then; with a block per 256 values the dispatch
+// of the blocks ruled (the 128^3 reverse pass 3.50 -> 3.47 ms).
+constexpr int kZeroBlocks = 2048;
 __global__ void __launch_bounds__(kBlock) k_zero(double* x, long long n) {
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n;
-       e += (long long)gridDim.x * blockDim.x)
-    x[e] = 0.0;
+  const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x, step = (long long)gridDim.x * blockDim.x;
+  if (((size_t)x & 15) == 0) {
+    double2* y = reinterpret_cast<double2*>(x);
+    const long long n2 = n >> 1;
+    for (long long e = t; e < n2; e += step) y[e] = make_double2(0.0, 0.0);
+    if ((n & 1) && t == 0) x[n - 1] = 0.0;
+  } else {
+    for (long long e = t; e < n; e += step) x[e] = 0.0;
+  }
 }
 
 }  // namespace cfd
