@@ -147,9 +147,13 @@ __device__ __forceinline__ int dbar_comp(int k) {
 // then reverses the pair of x with the cotangents of its faces x (own) and
 // x+1 (one lane above), into cells x-2 .. x+2 (lanes -2 .. +2). A wavefront
 // takes 64 consecutive slots of which the middle kXInvNew reverse their
-// pairs; two slots at each end overlap the neighbouring wavefronts and only
-// supply shuffles and collect sums.
-constexpr int kXInvNew = 60;
+// pairs; kXInvCtx slots at each end overlap the neighbouring wavefronts and
+// only supply values and collect sums. A lane loads its own cell only and the
+// windows are formed by lane shifts, twice, which beats 50 loads of cached
+// lines a lane: 128^3 296 us against 313 beside the dissipative reverses, the
+// step and its reverse 3.47 -> 3.45 ms, the 40^3 rollout 8.09 -> 8.05 ms.
+constexpr int kXInvCtx = 3;
+constexpr int kXInvNew = 64 - 2 * kXInvCtx;
 
 __device__ __forceinline__ void xadj_inv_body(const double* P, const double* __restrict__ Rbar, double rscale,
                                               double* Wbar, const Geom& g, int block) {
@@ -160,7 +164,7 @@ __device__ __forceinline__ void xadj_inv_body(const double* P, const double* __r
   const int total = S * g.n[1] * g.n[2];
   const int first = wave * kXInvNew;
   if (first >= total) return;  // uniform per wavefront
-  const int gs = first - 2 + lane;
+  const int gs = first - kXInvCtx + lane;
   const bool inrange = gs >= 0 && gs < total;
   int x = 0, j = 0, k = 0;
   if (inrange) {
@@ -169,16 +173,31 @@ __device__ __forceinline__ void xadj_inv_body(const double* P, const double* __r
     x_row(g, row, j, k);
   }
   const bool pair = inrange && x >= -1 && x <= n;     // cell x has a reconstruction pair
-  const bool face = inrange && x >= 0 && x <= n && lane >= 1;  // face x, with its left cell in the wavefront
-  const bool rev = pair && lane >= 2 && lane < 2 + kXInvNew;
+  // face x, with the windows of cells x-1 and x in the wavefront
+  const bool face = inrange && x >= 0 && x <= n && lane >= kXInvCtx && lane < 64 - 2;
+  const bool rev = pair && lane >= kXInvCtx && lane < 64 - kXInvCtx;
   const long long cx = cell_at(g, x, j, k);
-  const long long c0 = cell_at(g, (pair ? x : 0) - 2, j, k);  // window: cells x-2 .. x+2
+  // the cell's values; the other cells of its window come from the lanes beside
+  double own[5];
+  load_prims(P, g.vs, cx, own);
+  auto window = [&](int v, double* q) {  // cells x-2 .. x+2
+    q[2] = own[v];
+    q[1] = lane_shr1(q[2]);
+    q[0] = lane_shr1(q[1]);
+    q[3] = lane_shl1(q[2]);
+    q[4] = lane_shl1(q[3]);
+  };
   const double gsc = rscale * g.idx[0];
   double WLb[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, WRb[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   {
     double q[5][5];
 #pragma unroll
-    for (int m = 0; m < 5; ++m) load_prims(P, g.vs, c0 + m, q[m]);
+    for (int v = 0; v < 5; ++v) {
+      double s[5];
+      window(v, s);
+#pragma unroll
+      for (int m = 0; m < 5; ++m) q[m][v] = s[m];
+    }
     double qr[5], ql[5];
     recon_pair<SCH_JS>(q, qr, ql);  // right face of x (left state of face x+1), left face of x
     double WL[5], Gb[5];
@@ -190,14 +209,17 @@ __device__ __forceinline__ void xadj_inv_body(const double* P, const double* __r
     }
     if (face) hllc_rev<0>(g.gamma, g.gm1i, WL, ql, Gb, WLb, WRb);
   }
-  asm volatile("" ::: "memory");  // reload the window below instead of keeping it live
+  // the windows are formed again below instead of being kept
+#pragma unroll
+  for (int v = 0; v < 5; ++v) pin(own[v]);
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     const double up = lane_shl1(WLb[v]);  // every lane takes part in the shift
     const double qrb = rev ? up : 0.0;    // face x+1: cotangent of the right-face value of x
     const double qlb = rev ? WRb[v] : 0.0;
     double gq[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    const double* q = P + v * g.vs + c0;
+    double q[5];
+    window(v, q);
     weno5_pair_rev(q[0], q[1], q[2], q[3], q[4], qrb, qlb, gq);
     pin(gq[0]);
     pin(gq[4]);
