@@ -31,7 +31,8 @@ MI355X_HBM_PEAK = 8.0e12
 DIVERGENCE_FLOPS_PER_CELL_AXIS = 15
 RK_FLOPS_PER_CELL = 20
 GRADIENT_FLOPS_PER_CELL = 45  # 9 fourth-order centred velocity derivatives, 5 flops each
-KERNELS = ("k_prim", "k_sweep_x", "k_sweep_y", "k_sweep_z", "k_prim_halo")
+# slots of cfd_profile_stage; the march along y with the x faces is the x slot
+KERNELS = ("k_prim", "k_sweep_mx", "k_sweep_y", "k_sweep_z", "k_prim_halo")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hit256_traffic.txt")
 
 
@@ -405,14 +406,15 @@ def main():
     # nine fourth-order central derivatives of a cell (5 flops each) are
     # credited a third to each sweep
     grad = GRADIENT_FLOPS_PER_CELL / 3.0
-    # the sweeps run z, y, x; the x sweep, the last, also applies the stage
-    # update and forms the primitives of the updated cells
+    # a stage is the z march (with its share of the stage update) and the march
+    # along y that also forms the x faces (counted as the x sweep), which
+    # finishes the update and forms the primitives of the updated cells
     flops = {
         0: parts["prim_per_cell"] * (n + 6) ** 3,
-        1: face * faces_per_axis + (DIVERGENCE_FLOPS_PER_CELL_AXIS + grad + RK_FLOPS_PER_CELL
-                                    + parts["prim_per_cell"]) * cells,
-        2: face * faces_per_axis + (DIVERGENCE_FLOPS_PER_CELL_AXIS + grad) * cells,
-        3: face * faces_per_axis + (DIVERGENCE_FLOPS_PER_CELL_AXIS + grad) * cells,
+        1: 2 * face * faces_per_axis + (2 * (DIVERGENCE_FLOPS_PER_CELL_AXIS + grad) + RK_FLOPS_PER_CELL / 2
+                                        + parts["prim_per_cell"]) * cells,
+        2: 0.0,
+        3: face * faces_per_axis + (DIVERGENCE_FLOPS_PER_CELL_AXIS + grad + RK_FLOPS_PER_CELL / 2) * cells,
         4: 0.0,
     }[dom]
     achieved = flops / (ms[dom] * 1e-3)
@@ -429,7 +431,7 @@ def main():
         roofline["traffic_hbm_frac"] = (rd + wr) / (ms[dom] * 1e-3) / MI355X_HBM_PEAK
         # a stage of a run of steps: the sweeps and the primitives' halo refresh
         # (the primitive pass runs once per run, before the first step)
-        stage = KERNELS[1:]
+        stage = (KERNELS[1], KERNELS[3], KERNELS[4])
         if all(k in traffic for k in stage):
             stage_bytes = sum(sum(traffic[k]) for k in stage)
             roofline["stage_traffic_bytes"] = stage_bytes

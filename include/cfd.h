@@ -257,12 +257,14 @@ cfd_status cfd_rk3_step_adjoint_prims(cfd_solver* s, const double* P, double dt,
 /* Measurement aid: enqueue the kernels of TVD-RK3 stages on U as a run of
  * steps runs them (stage r % 3 + 1 in repetition r, with dt = 1e-12, written to
  * solver scratch, so U is not modified; the third stage also forms the CFL
- * maxima and health bits of its output): the primitive pass, the x/y/z sweeps
- * (the last one also storing the primitives of the updated cells), and the
- * halo refresh of those primitives. Runs them `reps` times (1..4096) back to
+ * maxima and health bits of its output): the primitive pass, the sweeps (the
+ * last one also storing the primitives of the updated cells), and the halo
+ * refresh of those primitives. Runs them `reps` times (1..4096) back to
  * back, each kernel bracketed by HIP events on `stream`, synchronises once,
  * and writes the average duration in milliseconds of each kernel to
- * ms_out[0..4] in that order (0 for sweeps the configuration does not launch).
+ * ms_out[0..4]: the primitive pass, the x, y and z sweep (a sweep that covers
+ * x and another axis counts as x; 0 for sweeps the configuration does not
+ * launch), the halo refresh.
  * Within a run of steps the primitive pass runs once, before the first step. */
 cfd_status cfd_profile_stage(cfd_solver* s, const double* U, int32_t reps, double* ms_out, void* stream);
 
@@ -278,8 +280,8 @@ cfd_status cfd_check(cfd_solver* s, int32_t* status_out);
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid allocation): cfd_rk3_step of U in place for the configuration cfg,
  * with no solver handle and no device allocation or free. Its scratch (CFL
- * slots, control block, two stage states, two right-hand-side accumulators and
- * three primitive buffers: 38 doubles per padded cell) is one static device
+ * slots, control block, two stage states, a right-hand-side accumulator and
+ * three primitive buffers) is one static device
  * array of 112 MiB, allocated with the library on every device it runs on and
  * held until the process ends; the grid may have at most
  * CFD_NOALLOC_MAX_PADDED_CELLS padded cells (CFD_EINVAL otherwise, before any

@@ -73,7 +73,6 @@ struct cfd_solver {
   double* Racc = nullptr; // 5 x padded
   double* A1 = nullptr;   // adjoint scratch (allocated on the first adjoint call)
   double* A2 = nullptr;
-  double* A3 = nullptr;
   double* Wbar = nullptr; // 6 x padded
   double* Dbar = nullptr; // 9 x padded (viscous runs; after Wbar in its array)
   // a second pair, cleared on the side stream during one right-hand-side
@@ -925,7 +924,7 @@ void cfd_destroy(cfd_solver* s) {
   if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);
   if (s->ev_join) (void)hipEventDestroy(s->ev_join);
   double* bufs[] = {s->U1, s->U2,   s->Pb[0], s->Pb[1], s->Pb[2], s->Racc,    s->A1,
-                    s->A2, s->A3,   s->Wbar,  s->Wbar2, s->partial, s->nna, s->nntape};
+                    s->A2, s->Wbar,  s->Wbar2, s->partial, s->nna, s->nntape};
   for (double* b : bufs)
     if (b) (void)hipFree(b);
   if (s->ctl) (void)hipFree(s->ctl);

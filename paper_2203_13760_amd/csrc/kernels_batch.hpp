@@ -2,7 +2,7 @@
 //
 // Many independent grids (mixed sizes, 2D and 3D, different physics) are
 // resident at once. For every phase of a TVD-RK3 stage (primitives, step size,
-// x/y/z sweeps, primitive halo) one persistent launch covers the work of the
+// sweeps, primitive halo) one persistent launch covers the work of the
 // resident grids of a sub-batch (its width chosen on the host from the
 // phase's blocks): the work of grid k is blocks [prefix[k], prefix[k+1]) of
 // that phase, and each workgroup takes blocks of the concatenated range, finds
@@ -11,10 +11,10 @@
 // each keeps its own state, scratch and CFL step, so a grid's result does not
 // depend on which other grids share the launch.
 //
-// As in the single-grid step, a grid with an active x axis gets the
-// primitives of each stage's output from its x sweep (which applies the stage
-// update) plus a halo pass, and the CFL rate maxima of U^{n+1} from the third
-// x sweep; its primitives of a new state are formed once, on admission. A grid
+// As in the single-grid step, a grid with an active x axis gets the primitives
+// of each stage's output from its last sweep (which applies the stage update)
+// plus a halo pass, and the CFL rate maxima of U^{n+1} from that of the third
+// stage; its primitives of a new state are formed once, on admission. A grid
 // without an x axis takes a primitive pass at the start of every stage.
 #pragma once
 #include <type_traits>
@@ -23,11 +23,11 @@
 
 namespace cfd {
 
-// PH_SX/SY/SZ: the sweep of that axis where it does not apply the stage
-// update except the x sweep (which applies it whenever x is active);
-// PH_SLAST: the last march of grids without an x axis, which applies the
-// update. Keeping those rare updating marches in a phase of their own keeps
-// the y and z phases to one sweep mode and within the register file.
+// PH_SZ: the z march of a grid with three active axes; PH_SX: the last sweep of
+// a grid with an x axis (the march with the x faces, or the x sweep alone);
+// PH_SY and PH_SLAST: the first and the updating march of a grid without x.
+// Keeping those rare marches in phases of their own keeps the others to one
+// sweep mode and within the register file.
 enum BatchPhase { PH_PRIM = 0, PH_DT, PH_SX, PH_SY, PH_SZ, PH_SLAST, PH_HALO, PH_COUNT };
 
 constexpr int kBatchMaxGrids = 512;
@@ -42,9 +42,9 @@ struct GridWork {
   double* partial; // CFL rate slots
   DevCtl* ctl;
   int npart;
-  int last_axis;   // the last swept axis (the lowest active one) applies the stage update
+  int last_axis;   // without x: the last marched axis applies the stage update
   int first_axis;
-  int xpn;         // x is active: the x sweep stores the next primitives
+  int xpn;         // x is active: the last sweep stores the next primitives
   int pgx;         // x blocks of a plane-indexed launch
   int sgx[3], sgy[3];  // launch shapes of the marching sweeps (axes 1, 2)
 };

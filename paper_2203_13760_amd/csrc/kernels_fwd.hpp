@@ -1,20 +1,21 @@
 // Forward kernels of one right-hand-side evaluation / TVD-RK3 stage (gfx950).
 //
-// Per stage:  prim  : U_k -> P = (rho,u,v,w,p,T~) on the padded grid, halos by
-//                     gather from their interior source cells (so U's own halo
-//                     is never read), plus the CFL rate max;
-//             sweep : one kernel per active axis; each face flux is computed
-//                     once in registers and differenced into its two cells,
-//                     the tangential velocity derivatives of the viscous flux
-//                     formed from P on the way.
-//                     x: one lane per face, wavefront shuffles carry the
-//                        left-face flux; y, z: one lane per column segment
-//                        marching along the axis with a register window.
-//                     The last active axis applies the RK3 stage update and
-//                     may also store the primitives of the updated cell for
-//                     the next stage (with the CFL rate and health bits), so
-//                     that within a run of steps the prim pass reduces to a
-//                     halo refresh of P.
+// Primitives: U -> P = (rho,u,v,w,p) on the padded grid once per call, halos
+// by gather from their interior source cells (so U's own halo is never read),
+// plus the CFL rate max. After that the last sweep of a stage stores the
+// primitives of the cells it updates, with their CFL rate and health bits, and
+// either their halo images too (small grids) or a halo pass follows.
+//
+// Sweeps: each face flux is computed once in registers and differenced into
+// its two cells, the tangential velocity derivatives of the viscous flux
+// formed from P on the way.
+//   cell-centred schemes, 3D: a z march (lanes along x, a register window
+//     moving along z) that leaves V = a Un + b (Uk - dt D_z) in R, then a y
+//     march whose rows also form their x faces between neighbouring lanes and
+//     that stores the new state;
+//   2D: that second sweep alone, with the whole update;
+//   1D and the Roe splitting: one sweep per active axis (x: one lane per face,
+//     lane shifts carry the left-face flux).
 #pragma once
 #include "physics.hpp"
 
@@ -447,46 +448,17 @@ __device__ __forceinline__ void load_prims(const double* __restrict__ P, long lo
   for (int v = 0; v < 5; ++v) q[v] = P[v * vs + c];
 }
 
-// Tangential velocity derivatives at a cell for faces normal to D (the
-// layout of FaceWindow::tg), fourth-order central differences of the
-// primitives across the cell (§3.4):
+// Tangential velocity derivatives at a cell for faces normal to D,
+// fourth-order central differences of the primitives across the cell (§3.4):
 // d u_D / d x_T1, d u_T1 / d x_T1, d u_D / d x_T2, d u_T2 / d x_T2. The
 // tangential coordinates of every cell a face stencil touches are interior, so
 // the +-2 neighbours lie inside the padded block.
-__device__ __forceinline__ double central4(const double* __restrict__ q, long long st, double i12) {
-  return (q[-2 * st] - 8.0 * q[-st] + 8.0 * q[st] - q[2 * st]) * i12;
-}
-
-template <int D>
-__device__ __forceinline__ void tangential_at(const Geom& g, const double* __restrict__ P, long long c,
-                                              double* tg) {
-  constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
-  const double* uD = P + (1 + D) * g.vs + c;
-  if (g.act[T1]) {
-    const long long st = g.s[T1];
-    const double i12 = g.idx[T1] * (1.0 / 12.0);
-    tg[0] = central4(uD, st, i12);
-    tg[1] = central4(P + (1 + T1) * g.vs + c, st, i12);
-  } else {
-    tg[0] = 0.0;
-    tg[1] = 0.0;
-  }
-  if (g.act[T2]) {
-    const long long st = g.s[T2];
-    const double i12 = g.idx[T2] * (1.0 / 12.0);
-    tg[2] = central4(uD, st, i12);
-    tg[3] = central4(P + (1 + T2) * g.vs + c, st, i12);
-  } else {
-    tg[2] = 0.0;
-    tg[3] = 0.0;
-  }
-}
-
-// The same without branches, in two halves: the sixteen loads, and the
-// arithmetic. An inactive axis gets stride 0 and weight 0 (the difference of
-// a cell with itself is exactly 0). Callers issue all loads before any use (a
-// scheduling barrier keeps the compiler from interleaving loads and uses,
-// which serialises their latencies).
+//
+// In two halves: the sixteen loads, and the arithmetic, without branches. An
+// inactive axis gets stride 0 and weight 0 (the difference of a cell with
+// itself is exactly 0). Callers issue all loads before any use (a scheduling
+// barrier keeps the compiler from interleaving loads and uses, which
+// serialises their latencies).
 template <int D>
 __device__ __forceinline__ void tangential_load(const Geom& g, const double* __restrict__ P, long long c,
                                                 double (&x)[4][4]) {
@@ -502,15 +474,6 @@ __device__ __forceinline__ void tangential_load(const Geom& g, const double* __r
     x[m][2] = q[m][st[m]];
     x[m][3] = q[m][2 * st[m]];
   }
-}
-
-template <int D>
-__device__ __forceinline__ void tangential_combine(const Geom& g, const double (&x)[4][4], double* tg) {
-  constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
-  const double w1 = g.act[T1] ? g.idx[T1] * (1.0 / 12.0) : 0.0, w2 = g.act[T2] ? g.idx[T2] * (1.0 / 12.0) : 0.0;
-  const double w[4] = {w1, w1, w2, w2};
-#pragma unroll
-  for (int m = 0; m < 4; ++m) tg[m] = (x[m][0] - 8.0 * x[m][1] + 8.0 * x[m][2] - x[m][3]) * w[m];
 }
 
 // The three sums the cell-centred sweeps carry (layout of sub_dissipative_q):
@@ -530,15 +493,6 @@ __device__ __forceinline__ void tangential_at3(const Geom& g, const double* __re
   double x[4][4];
   tangential_load<D>(g, P, c, x);
   tangential_combine3<D>(g, x, tg);
-}
-
-template <int D>
-__device__ __forceinline__ void tangential_at_flat(const Geom& g, const double* __restrict__ P, long long c,
-                                                   double* tg) {
-  double x[4][4];
-  tangential_load<D>(g, P, c, x);
-  __builtin_amdgcn_sched_barrier(0);
-  tangential_combine<D>(g, x, tg);
 }
 
 // Halo images of one axis of an interior coordinate c: the low halo cells
@@ -701,8 +655,8 @@ __device__ __forceinline__ double lane_shl1(double x) {
 // from itself and the three lanes below it (context slots only supply the
 // first faces of their row); the left-face flux of a cell comes from the lane
 // below. The first kXCtx+1 slots of a wavefront overlap its predecessor and
-// only seed these shuffles. One slot per lane keeps the kernel at four
-// wavefronts per SIMD (126 VGPRs with the default scheme).
+// only seed these shuffles. One slot per lane keeps the kernel at three
+// wavefronts per SIMD.
 constexpr int kXCtx = 3;
 constexpr int kXFaces = 64 - (kXCtx + 1);  // faces a wavefront emits
 
@@ -711,7 +665,7 @@ constexpr int kXFaces = 64 - (kXCtx + 1);  // faces a wavefront emits
 // inner. The blocks one XCD runs at a time then cover a few planes of a
 // narrow band, so the y and z neighbours the tangential stencils read are
 // mostly still in that XCD's L2. At 256^3 bands of 32 rows measured 1 %
-// faster than 16 or 64 (8: 2 % slower).
+// faster than 16 or 64 (8: 2 % slower), with the WENO5 x sweep.
 constexpr int kXBand = 32;
 
 __device__ __forceinline__ void x_row(const Geom& g, int row, int& j, int& k) {
@@ -1364,12 +1318,9 @@ __host__ __device__ __forceinline__ void sweep_march_blocks(const Geom& g, int& 
   gy = (int)(((long long)g.n[OT] * nseg + 3) / 4);
 }
 
-// Order of the per-axis sweeps of a stage: y, z, x over the active axes. The
-// first writes the right-hand side, the later ones accumulate into it, and x,
-// the last whenever it is active, applies the stage update and stores the next
-// primitives. The y march goes first because it writes without reading the
-// accumulator, which leaves it the registers to hold the loads of its
-// tangential stencil (whose z neighbours lie a plane apart) across a face.
+// Order of the sweeps where a stage has one per active axis (the Roe splitting,
+// grids with one active axis or without x): y, z, x. The last stores the new
+// state and the next primitives.
 constexpr int kSweepAxes[3] = {1, 2, 0};
 
 // Zero a buffer (graph-safe replacement for a memset node), 16 bytes a store

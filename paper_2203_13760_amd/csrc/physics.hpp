@@ -384,7 +384,6 @@ struct FaceWindow {
   double q[6][5];
   double T[4];
   double tg[4][4];
-  double a;  // Rusanov-NN: the face's alpha
 };
 
 // Fourth-order central interpolation to the face between b and c (§3.4).
