@@ -220,7 +220,10 @@ __device__ __forceinline__ void xadj_inv_body(const double* P, const double* __r
     double gq[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     double q[5];
     window(v, q);
-    weno5_pair_rev(q[0], q[1], q[2], q[3], q[4], qrb, qlb, gq);
+    // only whole windows of one row are reversed: the others (wavefront ends
+    // with shifted-in zeros, row ends) can overflow in the normalisers, and a
+    // zero cotangent times infinity is NaN
+    if (rev) weno5_pair_rev(q[0], q[1], q[2], q[3], q[4], qrb, qlb, gq);
     pin(gq[0]);
     pin(gq[4]);
     // cell x receives gq[4] from lane - 2, gq[3] from lane - 1, gq[2] from
