@@ -296,21 +296,19 @@ struct Sweep {
 static int plan_sweeps(const Geom& g, bool rk, Sweep* out) {
   int act = 0, n = 0;
   for (int d = 0; d < 3; ++d) act += g.act[d];
+  auto mode = [rk](bool first, bool last) {
+    if (rk && last) return first ? MODE_WRITE_RK : MODE_ACC_RK;
+    return first ? MODE_WRITE : MODE_ACC;
+  };
   if (!face_by_face(g) && g.act[0] && act > 1) {
-    if (act == 3) out[n++] = {Sweep::MARCH, 2, rk ? MODE_STAGE : MODE_WRITE};
-    out[n++] = {Sweep::MARCH_X, g.act[1] ? 1 : 2,
-                act == 3 ? (rk ? MODE_ADD_RK : MODE_ACC) : (rk ? MODE_WRITE_RK : MODE_WRITE)};
+    if (act == 3) out[n++] = {Sweep::MARCH, 2, mode(true, false)};
+    out[n++] = {Sweep::MARCH_X, g.act[1] ? 1 : 2, mode(act == 2, true)};
     return n;
   }
   for (int d : kSweepAxes) {
     if (!g.act[d]) continue;
-    const bool first = n == 0, last = n == act - 1;
-    int mode;
-    if (!rk) mode = first ? MODE_WRITE : MODE_ACC;
-    else if (!g.act[0]) mode = !last ? MODE_WRITE : (first ? MODE_WRITE_RK : MODE_ACC_RK);
-    else if (last) mode = first ? MODE_WRITE_RK : MODE_ADD_RK;
-    else mode = first ? MODE_STAGE : MODE_ADD_STAGE;
-    out[n++] = {d == 0 ? Sweep::X : Sweep::MARCH, d, mode};
+    out[n] = {d == 0 ? Sweep::X : Sweep::MARCH, d, mode(n == 0, n == act - 1)};
+    ++n;
   }
   return n;
 }
@@ -328,14 +326,7 @@ static void launch_march(int mode, const double* P, const StageIO& io, const Geo
     case MODE_WRITE: hipLaunchKernelGGL((k_sweep_march<AX, MODE_WRITE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g); break;
     case MODE_ACC: hipLaunchKernelGGL((k_sweep_march<AX, MODE_ACC, false, SCH, PA>), grid, blk, 0, st, P, io, g); break;
     case MODE_ACC_RK: hipLaunchKernelGGL((k_sweep_march<AX, MODE_ACC_RK, true, SCH, PA>), grid, blk, 0, st, P, io, g); break;
-    case MODE_WRITE_RK: hipLaunchKernelGGL((k_sweep_march<AX, MODE_WRITE_RK, true, SCH, PA>), grid, blk, 0, st, P, io, g); break;
-    case MODE_STAGE:
-      if constexpr (face || AX == 2)
-        hipLaunchKernelGGL((k_sweep_march<AX, MODE_STAGE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g);
-      break;
-    default:
-      if constexpr (face && AX == 2)
-        hipLaunchKernelGGL((k_sweep_march<AX, MODE_ADD_STAGE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g);
+    default: hipLaunchKernelGGL((k_sweep_march<AX, MODE_WRITE_RK, true, SCH, PA>), grid, blk, 0, st, P, io, g); break;
   }
 }
 
@@ -350,14 +341,14 @@ static void launch_x(int mode, bool img, const double* P, const StageIO& io, con
     else hipLaunchKernelGGL((k_sweep_x<MODE_WRITE_RK, true, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
   } else if constexpr (face) {
     if (mode == MODE_ACC) hipLaunchKernelGGL((k_sweep_x<MODE_ACC, false, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
-    else hipLaunchKernelGGL((k_sweep_x<MODE_ADD_RK, true, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
+    else hipLaunchKernelGGL((k_sweep_x<MODE_ACC_RK, true, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
   }
 }
 
 template <int AX, int MODE, int SCH, int PHYS>
 static void launch_mx_mode(bool img, const double* P, const StageIO& io, const Geom& g, hipStream_t st) {
   const dim3 grid((unsigned)sweep_mx_blocks(g, AX)), blk(kBlock);
-  constexpr bool rk = mode_last(MODE);
+  constexpr bool rk = mode_rk(MODE);
   if (rk && img) hipLaunchKernelGGL((k_sweep_mx<AX, MODE, rk, SCH, PHYS, rk>), grid, blk, 0, st, P, io, g);
   else hipLaunchKernelGGL((k_sweep_mx<AX, MODE, rk, SCH, PHYS, false>), grid, blk, 0, st, P, io, g);
 }
@@ -374,7 +365,7 @@ static void launch_mx(int ax, int mode, bool img, const double* P, const StageIO
       case MODE_WRITE: return launch_mx_mode<1, MODE_WRITE, SCH, PHYS>(img, P, io, g, st);
       case MODE_ACC: return launch_mx_mode<1, MODE_ACC, SCH, PHYS>(img, P, io, g, st);
       case MODE_WRITE_RK: return launch_mx_mode<1, MODE_WRITE_RK, SCH, PHYS>(img, P, io, g, st);
-      default: launch_mx_mode<1, MODE_ADD_RK, SCH, PHYS>(img, P, io, g, st);
+      default: launch_mx_mode<1, MODE_ACC_RK, SCH, PHYS>(img, P, io, g, st);
     }
   }
 }

@@ -137,7 +137,7 @@ __device__ __forceinline__ void batch_item(const BatchTable* __restrict__ tab, i
       } else {
         batch_phys(g, [&](auto phys) {
           constexpr int PHYS = decltype(phys)::value;
-          if (g.act[1] && g.act[2]) sweep_mx_body<1, MODE_ADD_RK, true, SCH_JS, PHYS>(P, io, g, local);
+          if (g.act[1] && g.act[2]) sweep_mx_body<1, MODE_ACC_RK, true, SCH_JS, PHYS>(P, io, g, local);
           else if (g.act[1]) sweep_mx_body<1, MODE_WRITE_RK, true, SCH_JS, PHYS>(P, io, g, local);
           else sweep_mx_body<2, MODE_WRITE_RK, true, SCH_JS, PHYS_ANY>(P, io, g, local);
         });
@@ -152,7 +152,7 @@ __device__ __forceinline__ void batch_item(const BatchTable* __restrict__ tab, i
       batch_march<1, MODE_WRITE, PHYS_ANY>(w, P, io, local);
     } else {
       // the z march of a grid with three active axes, before its last sweep
-      batch_phys(g, [&](auto phys) { batch_march<2, MODE_STAGE, decltype(phys)::value>(w, P, io, local); });
+      batch_phys(g, [&](auto phys) { batch_march<2, MODE_WRITE, decltype(phys)::value>(w, P, io, local); });
     }
   }
 }

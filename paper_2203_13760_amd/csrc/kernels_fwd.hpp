@@ -10,9 +10,9 @@
 // its two cells, the tangential velocity derivatives of the viscous flux
 // formed from P on the way.
 //   cell-centred schemes, 3D: a z march (lanes along x, a register window
-//     moving along z) that leaves V = a Un + b (Uk - dt D_z) in R, then a y
-//     march whose rows also form their x faces between neighbouring lanes and
-//     that stores the new state;
+//     moving along z) that leaves -D_z in R, then a y march whose rows also
+//     form their x faces between neighbouring lanes and that stores the new
+//     state;
 //   2D: that second sweep alone, with the whole update;
 //   1D and the Roe splitting: one sweep per active axis (x: one lane per face,
 //     lane shifts carry the left-face flux).
@@ -33,17 +33,13 @@ constexpr int kGradComps = 9;  // adjoint of d u_a / d x_b accumulated at compon
 
 // What a sweep does with the divergence D of its axis: MODE_WRITE stores
 // R = -D, MODE_ACC R -= D; the RK modes apply the stage update with R = -D
-// (MODE_WRITE_RK) or R - D (MODE_ACC_RK). MODE_STAGE, MODE_ADD_STAGE and
-// MODE_ADD_RK split the update of a stage between sweeps: the first stores
-// V = a Un + b (Uk - dt D) in R, one in between V -= b dt D, and the last the
-// new state V - b dt D, so that the last one, which also writes the next
-// primitives, reads one array instead of three or four.
-enum SweepMode {
-  MODE_WRITE = 0, MODE_ACC = 1, MODE_ACC_RK = 2, MODE_WRITE_RK = 3, MODE_STAGE = 4, MODE_ADD_STAGE = 5, MODE_ADD_RK = 6
-};
+// (MODE_WRITE_RK) or R - D (MODE_ACC_RK) and store a new state and its
+// primitives. The update stays in one place: with its share of the state formed
+// in the first sweep (V = a Un + b (Uk - dt D_z) in R, the last sweep V - b dt D)
+// the state is rounded once more a stage, and a step of a 3D box was 12 to 28 %
+// further from its value in extended precision.
+enum SweepMode { MODE_WRITE = 0, MODE_ACC = 1, MODE_ACC_RK = 2, MODE_WRITE_RK = 3 };
 __host__ __device__ constexpr bool mode_rk(int m) { return m >= MODE_ACC_RK; }
-// modes that store a new state (and its primitives)
-__host__ __device__ constexpr bool mode_last(int m) { return m == MODE_ACC_RK || m == MODE_WRITE_RK || m == MODE_ADD_RK; }
 
 struct StageIO {
   double* R;         // right-hand-side accumulator (padded layout)
@@ -553,9 +549,8 @@ __device__ __forceinline__ void emit_fetch(const StageIO& io, long long vs, long
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     const long long e = v * vs + c;
-    constexpr bool add = MODE == MODE_ADD_RK || MODE == MODE_ADD_STAGE;
-    if (MODE == MODE_ACC || MODE == MODE_ACC_RK || add) in.r[v] = ld_at(io.R + e, off);
-    if (mode_rk(MODE) && !add) {
+    if (MODE == MODE_ACC || MODE == MODE_ACC_RK) in.r[v] = ld_at(io.R + e, off);
+    if (mode_rk(MODE)) {
       in.un[v] = with_un ? ld_at(io.Un + e, off) : 0.0;
       in.uk[v] = ld_at(io.Uk + e, off);
     }
@@ -573,13 +568,10 @@ __device__ __forceinline__ void emit_put(const StageIO& io, const Geom& g, long 
     const long long e = v * g.vs + c;
     if (MODE == MODE_WRITE || MODE == MODE_ACC) {
       st_at(io.R + e, off, MODE == MODE_WRITE ? -D[v] : in.r[v] - D[v]);
-    } else if (MODE == MODE_ADD_RK || MODE == MODE_ADD_STAGE) {
-      uo[v] = fma(-(io.b * dt), D[v], in.r[v]);
-      st_at((MODE == MODE_ADD_STAGE ? io.R : io.Uout) + e, off, uo[v]);
     } else {
-      const double r = MODE == MODE_WRITE_RK || MODE == MODE_STAGE ? -D[v] : in.r[v] - D[v];
+      const double r = MODE == MODE_WRITE_RK ? -D[v] : in.r[v] - D[v];
       uo[v] = io.a * in.un[v] + io.b * (in.uk[v] + dt * r);
-      st_at((MODE == MODE_STAGE ? io.R : io.Uout) + e, off, uo[v]);
+      st_at(io.Uout + e, off, uo[v]);
     }
   }
   if constexpr (PN && mode_rk(MODE)) {
@@ -1190,10 +1182,15 @@ __device__ __forceinline__ void sweep_mx_body(const double* __restrict__ P, cons
 #pragma unroll
       for (int v = 0; v < 5; ++v) nq[v] = ld_at(P + v * g.vs + ce, off);
       if (vis) o_load(c + 4 * st);
-      // the update's loads before the face's arithmetic, as the stencils':
-      // 2D 1024^2 step 818 -> 805 us, TGV 64^3 178 -> 169 us, 256^3 unchanged
+      // the update's loads before the face's arithmetic, as the stencils', where
+      // they are ten values (2D 1024^2: 4 steps 818 -> 805 us). The fifteen of
+      // MODE_ACC_RK are loaded where they are used: held across the face they
+      // cost the third Euler wavefront and 24 B of spills with viscous fluxes,
+      // HIT 256^3 (2 steps) 11386 against 10618 us, TGV 64^3 182 against 178 us;
+      // loaded before the flux alone 10616 and 175 us, but with images (rollout
+      // at 40^3) 8.21 against 8.03 ms
       EmitIn ein;  // row f (the segment's first face uses none: row -1 may be in the halo)
-      emit_fetch<MODE>(io, g.vs, c + st, off, ein);
+      if constexpr (MODE != MODE_ACC_RK) emit_fetch<MODE>(io, g.vs, c + st, off, ein);
       __builtin_amdgcn_sched_barrier(0);
       double G[5], nWL[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
       {
@@ -1217,6 +1214,7 @@ __device__ __forceinline__ void sweep_mx_body(const double* __restrict__ P, cons
       }
       // row f is complete with this face
       if (f >= s0 && emit) {
+        if constexpr (MODE == MODE_ACC_RK) emit_fetch<MODE>(io, g.vs, c + st, off, ein);
         double D[5];
 #pragma unroll
         for (int v = 0; v < 5; ++v) D[v] = fma(G[v] - Gm[v], g.idx[AX], Dx[v]);
