@@ -842,8 +842,13 @@ __device__ __forceinline__ void sweep_x_body(const double* __restrict__ P, const
 // Blocks are taken in XCD-major order, so that the neighbouring rows and
 // planes whose velocities the derivative stencils read are being processed in
 // the same XCD and stay in its L2.
+// Three wavefronts per SIMD; two for the Roe splitting with run-time flux terms,
+// which spills 150 B a lane at three (convective and viscous 128^3, with the
+// marches below at one wavefront: two steps 3069 -> 2294 us). With all flux terms
+// it spills 20 B at three, which is still faster than two without (2001 against
+// 2085 us).
 template <int MODE, bool PN, int SCH, int PHYS, bool IMG>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) k_sweep_x(const double* __restrict__ P, StageIO io, Geom g) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SCH == SCH_ROE && PHYS == PHYS_ANY ? 2 : 3))) k_sweep_x(const double* __restrict__ P, StageIO io, Geom g) {
   if (step_disabled(io.dtp)) return;
   sweep_x_body<MODE, PN, SCH, PHYS, IMG>(P, io, g, xcd_major_block(blockIdx.x, gridDim.x));
 }
@@ -1049,8 +1054,10 @@ __device__ __forceinline__ void sweep_march_body(const double* __restrict__ P, c
   else if (bad && io.ctl) atomicOr(&io.ctl->status, bad);
 }
 
+// Two wavefronts per SIMD; one for the Roe splitting with run-time flux terms,
+// which spills 68 to 148 B a lane at two.
 template <int AX, int MODE, bool PN, int SCH, int PHYS>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SCH == SCH_ROE && PHYS == PHYS_ANY ? 1 : 2)))
 k_sweep_march(const double* __restrict__ P, StageIO io, Geom g) {
   if (step_disabled(io.dtp)) return;
   // XCD-major block order (see k_sweep_x): consecutive column groups, hence
