@@ -322,11 +322,13 @@ static void launch_march(int mode, const double* P, const StageIO& io, const Geo
   // sweeps that a cell-centred scheme runs only on grids without x take the
   // run-time flux terms
   constexpr int PA = face ? PHYS : PHYS_ANY;
-  switch (mode) {
-    case MODE_WRITE: hipLaunchKernelGGL((k_sweep_march<AX, MODE_WRITE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g); break;
-    case MODE_ACC: hipLaunchKernelGGL((k_sweep_march<AX, MODE_ACC, false, SCH, PA>), grid, blk, 0, st, P, io, g); break;
-    case MODE_ACC_RK: hipLaunchKernelGGL((k_sweep_march<AX, MODE_ACC_RK, true, SCH, PA>), grid, blk, 0, st, P, io, g); break;
-    default: hipLaunchKernelGGL((k_sweep_march<AX, MODE_WRITE_RK, true, SCH, PA>), grid, blk, 0, st, P, io, g); break;
+  if (mode == MODE_WRITE) {
+    hipLaunchKernelGGL((k_sweep_march<AX, MODE_WRITE, false, SCH, PHYS>), grid, blk, 0, st, P, io, g);
+  } else if (mode == MODE_WRITE_RK) {
+    hipLaunchKernelGGL((k_sweep_march<AX, MODE_WRITE_RK, true, SCH, PA>), grid, blk, 0, st, P, io, g);
+  } else if constexpr (AX == 2) {  // y is always the first march
+    if (mode == MODE_ACC) hipLaunchKernelGGL((k_sweep_march<AX, MODE_ACC, false, SCH, PA>), grid, blk, 0, st, P, io, g);
+    else hipLaunchKernelGGL((k_sweep_march<AX, MODE_ACC_RK, true, SCH, PA>), grid, blk, 0, st, P, io, g);
   }
 }
 
