@@ -15,6 +15,7 @@
 #include "kernels_nn.hpp"
 #include "kernels_fwd.hpp"
 #include "kernels_line.hpp"
+#include "segments.hpp"
 
 using namespace cfd;
 
@@ -140,20 +141,6 @@ static cfd_status validate(const cfd_config* c) {
   return CFD_OK;
 }
 
-// Lanes of a march with x faces: wavefronts per march segment, either strips
-// of kMxNew cells of one row each, or all rows' slots one after another (rows
-// shorter than a strip share wavefronts), whichever takes fewer; strips too
-// where the byte offsets between the rows of one wavefront would not fit in
-// 32 bits.
-static void choose_mx_lanes(Geom& g) {
-  const int ot = g.act[1] ? 2 : 1;
-  const long long S = g.n[0] + 2 * kMxCtx, rows = g.n[ot];
-  const long long strips = (g.n[0] + kMxNew - 1) / kMxNew * rows, flat = (S * rows + kMxNew - 1) / kMxNew;
-  const double span = 8.0 * ((64.0 / S + 2.0) * (double)g.s[ot] + g.N[0]);
-  g.xs = strips <= flat || span >= 4.0e9;
-  g.xg = (int)(g.xs ? strips : flat);
-}
-
 static void make_geom(const cfd_config& c, Geom& g) {
   std::memset(&g, 0, sizeof(g));
   double inv2 = 0.0;
@@ -189,56 +176,6 @@ static void make_geom(const cfd_config& c, Geom& g) {
   g.safe = (c.flags & CFD_F_SAFE_RECON) ? 1 : 0;
   g.viscous = ((c.flags & CFD_F_VISCOUS) && c.mu > 0.0) ? 1 : 0;
   g.heat = ((c.flags & CFD_F_HEAT) && c.mu > 0.0) ? 1 : 0;
-}
-
-// Time of `waves` wavefronts over the chip's 1024 SIMDs, `res` of them resident
-// on one at a time, in units of one wavefront's pure issue time: measured, a
-// SIMD with w wavefronts of a march takes w + 0.6 (one alone 1.6: nothing
-// hides its latencies), so that 331^2 marches with x faces in segments of 2,
-// 3, 4 and 8 rows (one wavefront per SIMD or less) run 11, 14, 17 and 28 us.
-static double waves_time(double waves, int res) {
-  const double w = waves / 1024.0, full = std::floor(w / res);
-  if (full >= 3) return w * (res + 0.6) / res + 0.3;
-  const double rem = std::ceil(w - full * res);
-  return full * (res + 0.6) + (rem > 0 ? rem + 0.6 : 0.0);
-}
-
-// Segment length along an axis of n cells that makes `groups(1 segment)`
-// wavefronts finish first: long segments seldom recompute their seed (worth
-// `seed` cells), short ones give the SIMDs more wavefronts. `face` is the work
-// per cell next to the first face's, `res` the resident wavefronts per SIMD.
-static int best_segment(int n, double groups, double face, double seed, int res) {
-  int best = 1;
-  double cost = 0.0;
-  for (int s = 1; s <= std::min(n, 256); ++s) {
-    const double c = (face * s + 1.0 + seed) * waves_time(groups * ((n + s - 1) / s), res);
-    if (s == 1 || c < cost) {
-      cost = c;
-      best = s;
-    }
-  }
-  return best;
-}
-
-// March segments of a single-grid solver. Against the fixed rule of 8 to 128
-// cells by powers of two (at least 1024 wavefronts): the implosion at 128^2
-// 1208 -> 590 us per 20 steps, KH 331^2 1079 -> 571 us and 1024^2 1130 -> 814 us
-// per 10 and 4 steps, a TGV step at 32^3 210 -> 97 us and at 128^3 1018 -> 822 us,
-// HIT 256^3 12.04 -> 11.02 ms per two steps. The serving batch chooses its
-// own (batch_segment): it fills the chip with many grids.
-static void choose_segment(Geom& g) {
-  const bool euler = g.inviscid && !g.viscous && !g.heat;
-  const int res = euler && !g.roe ? 4 : 2;
-  int seg = 0;
-  for (int ax = 1; ax < 3; ++ax) {
-    if (!g.act[ax]) continue;
-    const double groups = (double)((g.n[0] + 63) / 64) * g.n[3 - ax];
-    const int s = best_segment(g.n[ax], groups, 1.0, g.roe ? 4.0 : 3.0, res);
-    seg = seg ? std::min(seg, s) : s;
-  }
-  g.seg = seg ? seg : 1;
-  const int mx = g.act[1] ? 1 : 2;
-  g.segx = best_segment(g.n[mx], (double)g.xg, 2.0, 1.5, euler ? 3 : 2);
 }
 
 // ---------------------------------------------------------------------------
@@ -277,9 +214,6 @@ static void with_scheme(const Geom& g, F&& f) {
   else if (g.rusanov) with_phys<SCH_JS_RUS>(g, f);
   else with_phys<SCH_JS>(g, f);
 }
-
-// The Roe splitting projects face by face; the others reconstruct per cell.
-static bool face_by_face(const Geom& g) { return g.roe; }
 
 // The sweeps of a stage, in order. Cell-centred schemes with x and another
 // axis active: on three axes the z march, then the y march with the x faces;
@@ -413,16 +347,6 @@ static cfd_status enqueue_nn_alpha(cfd_solver* s, const double* P, hipStream_t s
   CFD_LAUNCHED();
   return CFD_OK;
 }
-
-// Whether the last sweep of a stage stores the halo images of the primitives it
-// writes (cell-centred schemes with an x axis, up to kImagesMaxCells padded
-// cells; else a pass of its own copies them). The pass is a launch of 4 to 5 us per
-// stage, the images cost the sweep registers and scattered stores: without ->
-// with them the implosion at 128^2 500 -> 412 us (20 steps), KH 331^2 583 ->
-// 528 us, a TGV step at 32^3 95 -> 87 us, but at 64^3 171 -> 180 us, KH 600^2
-// 556 -> 579 us and HIT 256^3 11.2 -> 11.6 ms.
-constexpr long long kImagesMaxCells = 1LL << 18;
-static bool stores_images(const Geom& g) { return !face_by_face(g) && g.act[0] && g.vs <= kImagesMaxCells; }
 
 // Enqueue the sweeps over primitives P. With rk set, the last one applies the
 // stage update into io.Uout and stores the primitives of the updated interior
@@ -870,9 +794,9 @@ cfd_status cfd_create(const cfd_config* cfg, cfd_solver** out) {
   if (!s) return fail(CFD_ENOMEM, "host allocation failed");
   s->cfg = *cfg;
   make_geom(*cfg, s->g);
-  choose_segment(s->g);
-  s->ncell = s->g.vs;
   s->images = stores_images(s->g);
+  choose_segment(s->g, s->images);
+  s->ncell = s->g.vs;
   s->nint = (long long)cfg->n[0] * cfg->n[1] * cfg->n[2];
   const size_t st = sizeof(double) * 5 * (size_t)s->ncell;
   bool ok = hipMalloc(&s->U1, st) == hipSuccess && hipMalloc(&s->U2, st) == hipSuccess &&
@@ -1276,9 +1200,9 @@ cfd_status cfd_rk3_step_noalloc(const cfd_config* cfg, double* U, double dt, dou
   cfd_solver s{};
   s.cfg = *cfg;
   make_geom(*cfg, s.g);
-  choose_segment(s.g);
-  s.ncell = s.g.vs;
   s.images = stores_images(s.g);
+  choose_segment(s.g, s.images);
+  s.ncell = s.g.vs;
   s.nint = (long long)cfg->n[0] * cfg->n[1] * cfg->n[2];
   if (s.ncell > noalloc_max_cells())
     return fail(CFD_EINVAL, "grid too large for the allocation-free step: " + std::to_string(s.ncell) +
