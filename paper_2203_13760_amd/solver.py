@@ -87,7 +87,9 @@ class Solver:
         return out
 
     def step_fixed(self, U, dt):
-        """One step of the given size in place (step without the scalar it returns)."""
+        """One step of the given size (> 0) in place (step without the scalar it returns)."""
+        if not float(dt) > 0.0:
+            raise cfd.CfdError(cfd.CFD_EINVAL, "need dt > 0")
         cfd.cfd_rk3_step(self.h, U, float(dt), None)
         return U
 
