@@ -162,12 +162,14 @@ cfd_status cfd_rk3_step(cfd_solver* s, double* U, double dt, double* dt_used_dev
  * kept on the device in *t_dev (device memory, read and updated). With
  * t_end > 0 the last step is clipped to end exactly at t_end, and steps
  * after that are device-side no-ops, so no host synchronisation is needed.
- * The step sequence is replayed from a captured HIP graph. */
+ * The step sequence is replayed from a captured HIP graph; 1D grids along x of
+ * up to 992 cells (not with ROE or RUSANOV_NN) run up to 4096 steps in one
+ * launch instead. */
 cfd_status cfd_advance(cfd_solver* s, double* U, int32_t n_steps, double t_end, double* t_dev,
                        void* stream);
 
 /* n_steps steps with a fixed dt (the paper's fixed-step rollout used for
- * differentiation, §4.5), graph-replayed like cfd_advance. */
+ * differentiation, §4.5), enqueued like cfd_advance's. */
 cfd_status cfd_advance_fixed(cfd_solver* s, double* U, int32_t n_steps, double dt, void* stream);
 
 /* Rusanov-NN weights (§7.4) of a solver created with CFD_F_RUSANOV_NN.
@@ -264,7 +266,9 @@ cfd_status cfd_rk3_step_adjoint_prims(cfd_solver* s, const double* P, double dt,
  * and writes the average duration in milliseconds of each kernel to
  * ms_out[0..4]: the primitive pass, the x, y and z sweep (a sweep that covers
  * x and another axis counts as x; 0 for sweeps the configuration does not
- * launch), the halo refresh.
+ * launch), the halo refresh (0 where the last sweep stores the halo cells
+ * itself, on grids of up to 2^18 padded cells). 1D grids that step in one
+ * workgroup are timed with the sweeps of longer ones.
  * Within a run of steps the primitive pass runs once, before the first step. */
 cfd_status cfd_profile_stage(cfd_solver* s, const double* U, int32_t reps, double* ms_out, void* stream);
 

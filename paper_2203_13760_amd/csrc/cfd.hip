@@ -981,13 +981,15 @@ cfd_status cfd_profile_stage(cfd_solver* s, const double* U, int32_t reps, doubl
     sl[n] = 0;
     (void)hipEventRecord(e[++n], st);
     for (int i = 0; i < nplan; ++i) {
-      launch_sweep(g, plan[i], false, s->P, io, st);
+      launch_sweep(g, plan[i], s->images, s->P, io, st);
       sl[n] = 1 + (plan[i].kind == Sweep::MARCH_X ? 0 : plan[i].ax);
       (void)hipEventRecord(e[++n], st);
     }
-    hipLaunchKernelGGL(k_prim_halo, dim3(halo_blocks(g)), dim3(kBlock), 0, st, io.Pn, g, io.dtp);
-    sl[n] = 4;
-    (void)hipEventRecord(e[++n], st);
+    if (!s->images) {
+      hipLaunchKernelGGL(k_prim_halo, dim3(halo_blocks(g)), dim3(kBlock), 0, st, io.Pn, g, io.dtp);
+      sl[n] = 4;
+      (void)hipEventRecord(e[++n], st);
+    }
     if (hipGetLastError() != hipSuccess) rc = fail(CFD_EHIP, "profiled stage failed");
   }
   double acc[K] = {0, 0, 0, 0, 0};
