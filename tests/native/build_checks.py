@@ -5,7 +5,7 @@ import os
 import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-CHECKS = ["arith_check"]
+CHECKS = ["arith_check", "rcp_check"]
 FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
