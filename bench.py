@@ -408,15 +408,15 @@ def main():
     # nine fourth-order central derivatives of a cell (5 flops each) are
     # credited a third to each sweep
     grad = GRADIENT_FLOPS_PER_CELL / 3.0
-    # a stage is the z march (with its share of the stage update) and the march
-    # along y that also forms the x faces (counted as the x sweep), which
-    # finishes the update and forms the primitives of the updated cells
+    # a stage is the z march and the march along y that also forms the x faces
+    # (counted as the x sweep), applies the stage update and forms the primitives
+    # of the updated cells
     flops = {
         0: parts["prim_per_cell"] * (n + 6) ** 3,
-        1: 2 * face * faces_per_axis + (2 * (DIVERGENCE_FLOPS_PER_CELL_AXIS + grad) + RK_FLOPS_PER_CELL / 2
+        1: 2 * face * faces_per_axis + (2 * (DIVERGENCE_FLOPS_PER_CELL_AXIS + grad) + RK_FLOPS_PER_CELL
                                         + parts["prim_per_cell"]) * cells,
         2: 0.0,
-        3: face * faces_per_axis + (DIVERGENCE_FLOPS_PER_CELL_AXIS + grad + RK_FLOPS_PER_CELL / 2) * cells,
+        3: face * faces_per_axis + (DIVERGENCE_FLOPS_PER_CELL_AXIS + grad) * cells,
         4: 0.0,
     }[dom]
     achieved = flops / (ms[dom] * 1e-3)

@@ -12,7 +12,9 @@
 //      between lanes and contributions summed per cell by wavefront shifts
 //      (one atomic per cell and variable). y and z faces
 //      (k_march_adj_inv/dis): marching wavefronts, the reverse of the forward
-//      marches. The inviscid and dissipative reverses run on two streams;
+//      marches. On grids of 2^18 padded cells and more they are a launch each,
+//      the inviscid and the dissipative ones on two streams; below, all of
+//      them are one launch (k_faces_adj);
 //   3. k_adj_halo: the transposed halo fill, every halo cell's Wbar (viscous:
 //      with its transposed centred differences of Dbar; k_adj_fold adds the
 //      interior cells' share) added to its interior source cell;
@@ -234,6 +236,8 @@ __device__ __forceinline__ void xadj_inv_body(const double* P, const double* __r
   }
 }
 
+// Four wavefronts per SIMD: bound by the latency of its loads and atomics, and
+// worth the 44 B of scratch a lane that 128 registers leave.
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
 k_xadj_inv(const double* P, const double* __restrict__ Rbar, double rscale, double* Wbar, Geom g) {
   xadj_inv_body(P, Rbar, rscale, Wbar, g, xcd_major_block(blockIdx.x, gridDim.x));
@@ -351,13 +355,15 @@ __global__ void __launch_bounds__(kBlock) k_xadj_dis(const double* __restrict__ 
 // ---------------------------------------------------------------------------
 // Marching face reverses along y and z (AX = 1, 2), the reverse counterparts
 // of the forward marches: a wavefront holds 64 consecutive x of one column
-// (other transverse coordinate, segment of g.seg cells along AX) and walks
+// (other transverse coordinate, segment of `seg` cells along AX, chosen for
+// each part on its own) and walks
 // its faces in order, keeping the stencil window in registers, so every cell
 // of the column is loaded once per segment instead of once per face that
 // touches it, and a cell's adjoint is added to memory once, when the last
 // face of the segment that touches it is done (one atomic per cell and
 // variable; a cell near a segment end gets a share from each of the two
-// segments). Launch shape: sweep_march_blocks<AX>.
+// segments). One-dimensional launch: blocks of 64 x along a row first, then
+// four columns a block.
 
 // Column, segment and first/last face of the marching wavefront, all uniform;
 // false for a wavefront without a column. The lane's x is i (at or past the
