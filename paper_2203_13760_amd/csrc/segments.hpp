@@ -66,13 +66,16 @@ inline int best_segment(int n, double groups, double face, double seed, int res)
 }
 
 // Wavefronts per SIMD that the registers of a grid's marches leave room for
-// (tests/test_kernel_resources_cpu.py holds them against the built kernels).
+// (tests/test_segments_cpu.py holds them against the built kernels).
 // The march of one axis: the z march of a 3D Euler step keeps to 128 registers,
-// the others to 256; the Roe splitting with run-time flux terms takes more.
+// the others to 256; the Roe splitting with run-time flux terms takes more. On
+// Euler grids without x, where the marches run with run-time flux terms at two,
+// the lengths for four are the faster ones (300 x 300 in y and z, 4 steps: 2859
+// against 3172 us).
 inline int march_waves(const Geom& g) {
   const bool euler = g.inviscid && !g.viscous && !g.heat, ns = g.inviscid && g.viscous && g.heat;
   if (g.roe) return euler || ns ? 2 : 1;
-  return euler && g.act[0] && g.act[1] && g.act[2] ? 4 : 2;
+  return euler ? 4 : 2;
 }
 // The march with x faces: three for the Euler equations, but two where it holds
 // both states across its face and stores images (2D grids; WENO3-JS with HLLC
