@@ -1086,7 +1086,7 @@ k_sweep_march(const double* __restrict__ P, StageIO io, Geom g) {
 // at 2.6 TB/s, waited on latency.
 constexpr int kMxCtx = 3, kMxNew = 64 - 2 * kMxCtx;
 
-template <int AX, int MODE, bool PN, int SCH, int PHYS, bool IMG = false>
+template <int AX, int MODE, bool PN, int SCH, int PHYS, bool IMG = false, bool BEFORE_FLUX = false>
 __device__ __forceinline__ void sweep_mx_body(const double* __restrict__ P, const StageIO& io, const Geom& g,
                                               int block) {
   constexpr int OT = 3 - AX;  // the transverse axis of the rows
@@ -1193,9 +1193,11 @@ __device__ __forceinline__ void sweep_mx_body(const double* __restrict__ P, cons
       // they are ten values (2D 1024^2: 4 steps 818 -> 805 us). The fifteen of
       // MODE_ACC_RK are loaded where they are used: held across the face they
       // cost the third Euler wavefront and 24 B of spills with viscous fluxes,
-      // HIT 256^3 (2 steps) 11386 against 10618 us, TGV 64^3 182 against 178 us;
-      // loaded before the flux alone 10616 and 175 us, but with images (rollout
-      // at 40^3) 8.21 against 8.03 ms
+      // HIT 256^3 (2 steps) 11386 against 10618 us, TGV 64^3 182 against 178 us.
+      // BEFORE_FLUX issues them between the reconstruction and the flux, which
+      // suits the viscous single-grid sweep without images (10616 and 175 us), not
+      // the one with them (rollout at 40^3 8.21 against 8.03 ms), nor the Euler
+      // one (two wavefronts instead of three)
       EmitIn ein;  // row f (the segment's first face uses none: row -1 may be in the halo)
       if constexpr (MODE != MODE_ACC_RK) emit_fetch<MODE>(io, g.vs, c + st, off, ein);
       __builtin_amdgcn_sched_barrier(0);
@@ -1215,13 +1217,17 @@ __device__ __forceinline__ void sweep_mx_body(const double* __restrict__ P, cons
           tf[1] = T1 == 0 ? a : b;
           tf[2] = rc4(tS[0], tS[1], tS[2], tS[3]);
         }
+        if constexpr (MODE == MODE_ACC_RK && BEFORE_FLUX) {
+          emit_fetch<MODE>(io, g.vs, c + st, off, ein);
+          __builtin_amdgcn_sched_barrier(0);
+        }
         face_flux_states<AX, SCH, PHYS>(g, WLc, WR, q, T, tf, alpha, G);
 #pragma unroll
         for (int v = 0; v < 5; ++v) pin(G[v]);
       }
       // row f is complete with this face
       if (f >= s0 && emit) {
-        if constexpr (MODE == MODE_ACC_RK) emit_fetch<MODE>(io, g.vs, c + st, off, ein);
+        if constexpr (MODE == MODE_ACC_RK && !BEFORE_FLUX) emit_fetch<MODE>(io, g.vs, c + st, off, ein);
         double D[5];
 #pragma unroll
         for (int v = 0; v < 5; ++v) D[v] = fma(G[v] - Gm[v], g.idx[AX], Dx[v]);
@@ -1305,7 +1311,7 @@ template <int AX, int MODE, bool PN, int SCH, int PHYS, bool IMG>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
 k_sweep_mx(const double* __restrict__ P, StageIO io, Geom g) {
   if (step_disabled(io.dtp)) return;
-  sweep_mx_body<AX, MODE, PN, SCH, PHYS, IMG>(P, io, g, xcd_major_block(blockIdx.x, gridDim.x));
+  sweep_mx_body<AX, MODE, PN, SCH, PHYS, IMG, PHYS == PHYS_NS && !IMG>(P, io, g, xcd_major_block(blockIdx.x, gridDim.x));
 }
 
 // Blocks of a march with x faces along AX.
